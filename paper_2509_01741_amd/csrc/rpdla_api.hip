@@ -283,11 +283,11 @@ rpdla_status launch_push(const DevCfg& c, int prec, const rpdla::PushIO& io, hip
     if (prec == RPDLA_FP64) {
         auto* kern = rpdla::push_kernel<FIELD, rpdla::ElecF64>;
         const int g = persistent_blocks(kern, io.n_slots, sh.block, sh.grid_factor);
-        hipLaunchKernelGGL(kern, dim3(g), dim3(sh.block), 0, st, c, io);
+        hipLaunchKernelGGL(kern, dim3(g), dim3(sh.block), 0, st, rpdla::PushArgs{c, io});
     } else if constexpr (FIELD < 20) {
         auto* kern = rpdla::push_kernel<FIELD, rpdla::ElecMixed>;
         const int g = persistent_blocks(kern, io.n_slots, sh.block, sh.grid_factor);
-        hipLaunchKernelGGL(kern, dim3(g), dim3(sh.block), 0, st, c, io);
+        hipLaunchKernelGGL(kern, dim3(g), dim3(sh.block), 0, st, rpdla::PushArgs{c, io});
     } else {
         return fail(RPDLA_EUNSUPPORTED, "the linearly polarized focus has no mixed form");
     }
@@ -302,11 +302,11 @@ rpdla_status launch_push_rr(const DevCfg& c, bool rr, const rpdla::PushIO& io, h
     if (rr) {
         auto* kern = rpdla::push_kernel<FIELD, rpdla::ElecRR<true>>;
         const int g = persistent_blocks(kern, io.n_slots, sh.block, sh.grid_factor);
-        hipLaunchKernelGGL(kern, dim3(g), dim3(sh.block), 0, st, c, io);
+        hipLaunchKernelGGL(kern, dim3(g), dim3(sh.block), 0, st, rpdla::PushArgs{c, io});
     } else {
         auto* kern = rpdla::push_kernel<FIELD, rpdla::ElecRR<false>>;
         const int g = persistent_blocks(kern, io.n_slots, sh.block, sh.grid_factor);
-        hipLaunchKernelGGL(kern, dim3(g), dim3(sh.block), 0, st, c, io);
+        hipLaunchKernelGGL(kern, dim3(g), dim3(sh.block), 0, st, rpdla::PushArgs{c, io});
     }
     RPDLA_HIP(hipGetLastError());
     return RPDLA_OK;
@@ -318,7 +318,7 @@ rpdla_status launch_push_dp(const DevCfg& c, const rpdla::PushIO& io, hipStream_
     const Shape sh = get_shape(kKindPush, FIELD, RPDLA_FP64);
     auto* kern = rpdla::push_kernel<FIELD, rpdla::ElecDP>;
     const int g = persistent_blocks(kern, io.n_slots, sh.block, sh.grid_factor);
-    hipLaunchKernelGGL(kern, dim3(g), dim3(sh.block), 0, st, c, io);
+    hipLaunchKernelGGL(kern, dim3(g), dim3(sh.block), 0, st, rpdla::PushArgs{c, io});
     RPDLA_HIP(hipGetLastError());
     return RPDLA_OK;
 }

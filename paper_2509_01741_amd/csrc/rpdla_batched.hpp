@@ -138,7 +138,7 @@ __global__ void __launch_bounds__(256, BatchWaves<ELEC>::value) batch_push_kerne
     int64_t idx = -1;
     bool draining = false;
     ELEC e;
-    e.n = e.N = 0;
+    e.left = 0;
     while (true) {
         if (!draining) {
             while (true) {
@@ -156,9 +156,9 @@ __global__ void __launch_bounds__(256, BatchWaves<ELEC>::value) batch_push_kerne
                         if (first + a < A.atoms_per_cfg && t0 < __builtin_inf()) {
                             const int64_t ia = (int64_t)cw * A.apc + a;
                             if (elec_init(cfgs[cw], e, t0, A.x[ia], A.y[ia], A.z[ia])) {
-                                if (e.N > 0) {
+                                if (e.left > 0) {
                                     idx = js;
-                                    atomicAdd(&s_steps[cw], (unsigned long long)e.N);
+                                    atomicAdd(&s_steps[cw], (unsigned long long)e.left);
                                 } else {
                                     double ux, uy, uz, xf, yf, zf;
                                     elec_final(cfgs[cw], e, ux, uy, uz, xf, yf, zf);
@@ -189,8 +189,8 @@ __global__ void __launch_bounds__(256, BatchWaves<ELEC>::value) batch_push_kerne
             continue;
         }
         if (idx >= 0) {
-            elec_step<FIELD>(cfgs[cw], e);
-            if (e.n == e.N) {
+            elec_step<FIELD, true>(cfgs[cw], e, fm::kCoef);
+            if (e.left == 0) {
                 double ux, uy, uz, xf, yf, zf;
                 elec_final(cfgs[cw], e, ux, uy, uz, xf, yf, zf);
                 A.ux[idx] = ux; A.uy[idx] = uy; A.uz[idx] = uz;

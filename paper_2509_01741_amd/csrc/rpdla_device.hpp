@@ -53,6 +53,11 @@ struct DevCfg {
     int64_t ad_max_steps;
 };
 
+// Keep a value in scalar / vector registers from here on: the compiler no
+// longer knows it, so it cannot put a literal in its place.
+__device__ inline void keep_in_sgpr(double& v) { asm volatile("" : "+s"(v)); }
+__device__ inline void keep_in_vgpr(double& v) { asm volatile("" : "+v"(v)); }
+
 // ---------------------------------------------------------------------------
 // Philox4x64-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two
 // 64x64->128 multiplies, key bumped by the Weyl constants between rounds.
@@ -127,8 +132,9 @@ __device__ inline Cx<T> cmul(Cx<T> a, Cx<T> b)
 //   EZ = eps Im{R2 - rD R3 + E (R3/2 + rD R4/2 - 5rD^2 R5/4 + rD^3 R6/4)}
 // (E^2 = e4 iD^2 and eps E = e3 iD: the terms of the series above, term by
 // term).
-template <int ORDER, typename T>
-__device__ inline void rp_brackets(T G_re, T G_im, T zeta, T rD, T E, T& PE, T& PB, T& EZe)
+template <int ORDER, typename T, class K>
+__device__ inline void rp_brackets(T G_re, T G_im, T zeta, T rD, T E, T& PE, T& PB, T& EZe,
+                                   const K& k)
 {
     constexpr int NMAX = ORDER >= 5 ? 8 : ORDER >= 3 ? 6 : 3;
     T Rr[NMAX + 1], Ri[NMAX + 1];
@@ -151,14 +157,14 @@ __device__ inline void rp_brackets(T G_re, T G_im, T zeta, T rD, T E, T& PE, T& 
         const T a = fma(-Rr[5], v, Rr[4]);
         const T pb2 = fma(a, v, h3);
         const T pe2 = fma(a + Rr[4], v, -h3);
-        const T ez3 = fma(fma(fma(Ri[6] + Ri[6], v, T(-5.0) * Ri[5]), v, Ri[4]), v,
+        const T ez3 = fma(fma(fma(Ri[6] + Ri[6], v, -(T(k.c5) * Ri[5])), v, Ri[4]), v,
                           T(0.5) * Ri[3]);
         EZe = fma(E, ez3, EZe);
         if constexpr (ORDER >= 5) {
-            const T t8 = T(0.03125) * Rr[8], t5 = T(0.375) * Rr[5], t4 = T(0.375) * Rr[4];
-            const T pe4 = fma(fma(fma(fma(t8, rD, T(-0.375) * Rr[7]), rD, T(1.0625) * Rr[6]), rD, -t5),
+            const T t8 = T(0.03125) * Rr[8], t5 = T(k.c375) * Rr[5], t4 = T(k.c375) * Rr[4];
+            const T pe4 = fma(fma(fma(fma(t8, rD, -(T(k.c375) * Rr[7])), rD, T(k.c1_0625) * Rr[6]), rD, -t5),
                               rD, -t4);
-            const T pb4 = fma(fma(fma(fma(t8, rD, T(-0.25) * Rr[7]), rD, T(0.1875) * Rr[6]), rD, t5),
+            const T pb4 = fma(fma(fma(fma(t8, rD, T(-0.25) * Rr[7]), rD, T(k.c1875) * Rr[6]), rD, t5),
                               rD, t4);
             PE = fma(E, fma(E, pe4, pe2), PE);
             PB = fma(E, fma(E, pb4, pb2), PB);
@@ -169,31 +175,42 @@ __device__ inline void rp_brackets(T G_re, T G_im, T zeta, T rD, T E, T& PE, T& 
     }
 }
 
+// x^2 + y^2, the second product fused.  The two forms differ by rounding, and
+// a trajectory can amplify that to its leading digits: the pushes state which
+// one each stage takes (AXIS, the coordinate that is fused), so that a result
+// does not depend on how a kernel around it is compiled.
+template <int AXIS, typename T>
+__device__ inline T radius2(T x, T y)
+{
+    return AXIS == 0 ? fma(x, x, y * y) : fma(y, y, x * x);
+}
+
 // Double-precision radial field at normalized position (X, Y, Z) and retarded
 // time d = tau - Z (every field model depends on time only through d), in
 // the parts the force needs: a = (pe X, pe Y, az), b = (-pb Y, pb X, 0).
 // With LO the retarded time is the unevaluated sum d + dl (dl small): the
 // carrier phase goes to the sine/cosine as the pair (d, phi0 + dl - rD zeta),
 // so it is not rounded to a multiple of ulp(d).
-template <int ORDER, bool LO, class CFG>
+template <int ORDER, bool LO, int AXIS, class CFG>
 __device__ inline void rp_field_parts_f64(const CFG& c, double X, double Y, double Z, double d,
-                                          double dl, double& pe, double& pb, double& az)
+                                          double dl, double& pe, double& pb, double& az,
+                                          const fm::Coef& k)
 {
-    const double r2 = (X * X + Y * Y) * c.inv_w0n2;
+    const double r2 = radius2<AXIS>(X, Y) * c.inv_w0n2;
     const double zeta = Z * c.inv_zrn;
     const double iD = fm::rcp_f64(1.0 + zeta * zeta);
     const double rD = r2 * iD;
     const double psi_lo = fma(-rD, zeta, LO ? c.phi0 + dl : c.phi0);
     const double s = (LO ? d + dl : d) * c.inv_T0n;
-    const double g = c.a0_w * fm::exp_fin_f64(-rD - s * s);
+    const double g = c.a0_w * fm::exp_fin_f64(-rD - s * s, k);
     // g e^{i Psi} / D from the half-angle form: the sign (-1)^n goes on the
     // amplitude, cos Psi = 1 - sigma^2 and sin Psi = sigma kappa
     double sg, kp;
-    const unsigned sgn = fm::cis_half2_f64(d, psi_lo, &sg, &kp);
+    const unsigned sgn = fm::cis_half2_f64(d, psi_lo, &sg, &kp, k);
     const double gi = fm::flip_sign(g * (iD * iD), sgn);
     const double gs = gi * sg;
     double PE, PB, EZe;
-    rp_brackets<ORDER, double>(fma(-gs, sg, gi), gs * kp, zeta, rD, c.e2 * iD, PE, PB, EZe);
+    rp_brackets<ORDER, double>(fma(-gs, sg, gi), gs * kp, zeta, rD, c.e2 * iD, PE, PB, EZe, k);
     pe = c.er_scale * PE;
     pb = PB;
     az = c.ez_2 * EZe;
@@ -201,12 +218,13 @@ __device__ inline void rp_field_parts_f64(const CFG& c, double X, double Y, doub
 
 // The radial field in Cartesian components.  WANT_B = false skips the
 // magnetic field (ionization needs |E| only).
-template <int ORDER, bool WANT_B, bool LO, class CFG>
+template <int ORDER, bool WANT_B, bool LO, int AXIS, class CFG>
 __device__ inline void rp_field_f64(const CFG& c, double X, double Y, double Z, double d, double dl,
-                                    double& ax, double& ay, double& az, double& bx, double& by)
+                                    double& ax, double& ay, double& az, double& bx, double& by,
+                                    const fm::Coef& k)
 {
     double pe, pb;
-    rp_field_parts_f64<ORDER, LO>(c, X, Y, Z, d, dl, pe, pb, az);
+    rp_field_parts_f64<ORDER, LO, AXIS>(c, X, Y, Z, d, dl, pe, pb, az, k);
     ax = pe * X;
     ay = pe * Y;
     if constexpr (WANT_B) {
@@ -399,10 +417,10 @@ __device__ inline double lp_bound2(const CFG& c, double X, double Y, double Z)
 // Field of any model in double precision (test models included) at position
 // (X, Y, Z) and retarded time d = tau - Z; with LO the retarded time is the
 // unevaluated sum d + dl (the radial focus keeps the pair, the others add it).
-template <int FIELD, bool WANT_B, class CFG, bool LO = false>
+template <int FIELD, bool WANT_B, class CFG, bool LO = false, int AXIS = 0>
 __device__ inline void field_f64(const CFG& c, double X, double Y, double Z, double d,
                                  double& ax, double& ay, double& az, double& bx, double& by,
-                                 double& bz, double dl = 0.0)
+                                 double& bz, double dl = 0.0, const fm::Coef& k = fm::kCoef)
 {
     if constexpr (LO && !(FIELD == 1 || FIELD == 3 || FIELD == 5)) {
         d += dl;
@@ -420,7 +438,7 @@ __device__ inline void field_f64(const CFG& c, double X, double Y, double Z, dou
     } else if constexpr (FIELD == 21 || FIELD == 23 || FIELD == 25) {
         lp_field_f64<FIELD - 20, WANT_B, CFG>(c, X, Y, Z, d, ax, ay, az, bx, by, bz);
     } else {
-        rp_field_f64<FIELD, WANT_B, LO, CFG>(c, X, Y, Z, d, dl, ax, ay, az, bx, by);
+        rp_field_f64<FIELD, WANT_B, LO, AXIS, CFG>(c, X, Y, Z, d, dl, ax, ay, az, bx, by, k);
         bz = 0.0;
     }
 }

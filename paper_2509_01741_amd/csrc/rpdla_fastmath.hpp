@@ -63,6 +63,27 @@ RPDLA_HD inline double flip_sign(double v, unsigned m)
     return r;
 }
 
+// The constants of one radial-field evaluation and of the reciprocal steps, as
+// a record: a kernel with a long loop copies it into registers once (see
+// keep_in_sgpr / keep_in_vgpr in rpdla_device.hpp).  A double is no literal
+// operand on this machine, so each constant that is not in a register costs
+// two scalar moves at every use.  kCoef, the default everywhere, folds to the
+// constants themselves.  The reduction constants are held negated: fma(n, -c, x)
+// is fma(-n, c, x), and the accumulator form of the instruction is shorter.
+struct Coef {
+    double magic = kRoundMagic;
+    double log2e = kLog2e, nln2_1 = -kLn2_1, nln2_2 = -kLn2_2;
+    double ex[10] = {kExp[0], kExp[1], kExp[2], kExp[3], kExp[4],
+                     kExp[5], kExp[6], kExp[7], kExp[8], kExp[9]};
+    double inv_pi = kOneOverPi, npi_1 = -kPi_1, npi_2 = -kPi_2, npi_3 = -kPi_3;
+    double sg[7] = {kSigma[0], kSigma[1], kSigma[2], kSigma[3], kSigma[4], kSigma[5], kSigma[6]};
+    double kp[6] = {kKappa[0], kKappa[1], kKappa[2], kKappa[3], kKappa[4], kKappa[5]};
+    double ns2o8 = -kSqrt2Over8, s2 = kSqrt2;
+    // brackets of the radial field, and the third-order rsqrt step (c375)
+    double c375 = 0.375, c1_0625 = 1.0625, c1875 = 0.1875, c5 = 5.0;
+};
+constexpr Coef kCoef{};
+
 // sin r, cos r for |r| <= pi/4 (a little beyond), rotated to quadrant q.
 RPDLA_HD inline void sincos_reduced(double r, int q, double* s_out, double* c_out)
 {
@@ -118,30 +139,31 @@ RPDLA_HD inline void sincos2_f64(double x_hi, double x_lo, double* s_out, double
 // after the leading reduction step as in sincos2_f64): writes sigma and kappa
 // with cos x = (-1)^n (1 - sigma^2), sin x = (-1)^n sigma kappa, and returns
 // (-1)^n as a sign mask (0 or 2^31) for flip_sign.
-RPDLA_HD inline unsigned cis_half2_f64(double x_hi, double x_lo, double* sigma, double* kappa)
+RPDLA_HD inline unsigned cis_half2_f64(double x_hi, double x_lo, double* sigma, double* kappa,
+                                       const Coef& k = kCoef)
 {
-    const double tq = fma(x_hi + x_lo, kOneOverPi, kRoundMagic);
-    const double n = tq - kRoundMagic;
-    double r = fma(-n, kPi_1, x_hi) + x_lo;
-    r = fma(-n, kPi_2, r);
-    r = fma(-n, kPi_3, r);
+    const double tq = fma(x_hi + x_lo, k.inv_pi, k.magic);
+    const double n = tq - k.magic;
+    double r = fma(n, k.npi_1, x_hi) + x_lo;
+    r = fma(n, k.npi_2, r);
+    r = fma(n, k.npi_3, r);
     const double t = r * r;
-    double p = kSigma[6];
-    p = fma(p, t, kSigma[5]);
-    p = fma(p, t, kSigma[4]);
-    p = fma(p, t, kSigma[3]);
-    p = fma(p, t, kSigma[2]);
-    p = fma(p, t, kSigma[1]);
-    p = fma(p, t, kSigma[0]);
+    double p = k.sg[6];
+    p = fma(p, t, k.sg[5]);
+    p = fma(p, t, k.sg[4]);
+    p = fma(p, t, k.sg[3]);
+    p = fma(p, t, k.sg[2]);
+    p = fma(p, t, k.sg[1]);
+    p = fma(p, t, k.sg[0]);
     *sigma = r * p;
-    double q = kKappa[5];
-    q = fma(q, t, kKappa[4]);
-    q = fma(q, t, kKappa[3]);
-    q = fma(q, t, kKappa[2]);
-    q = fma(q, t, kKappa[1]);
-    q = fma(q, t, kKappa[0]);
-    q = fma(q, t, -kSqrt2Over8);
-    *kappa = fma(q, t, kSqrt2);
+    double q = k.kp[5];
+    q = fma(q, t, k.kp[4]);
+    q = fma(q, t, k.kp[3]);
+    q = fma(q, t, k.kp[2]);
+    q = fma(q, t, k.kp[1]);
+    q = fma(q, t, k.kp[0]);
+    q = fma(q, t, k.ns2o8);
+    *kappa = fma(q, t, k.s2);
     return (unsigned)low_word(tq) << 31;
 }
 
@@ -169,22 +191,22 @@ RPDLA_HD inline double exp_f64(double x)
 // The same exponential without the range guards, for finite arguments of
 // magnitude below 2^31 ln 2 (n rounded by the 1.5 2^52 addition): below about
 // -745 the scaling by 2^n flushes to zero by itself.
-RPDLA_HD inline double exp_fin_f64(double x)
+RPDLA_HD inline double exp_fin_f64(double x, const Coef& k = kCoef)
 {
-    const double tn = fma(x, kLog2e, kRoundMagic);
-    const double n = tn - kRoundMagic;
-    double r = fma(-n, kLn2_1, x);
-    r = fma(-n, kLn2_2, r);
-    double p = kExp[9];
-    p = fma(p, r, kExp[8]);
-    p = fma(p, r, kExp[7]);
-    p = fma(p, r, kExp[6]);
-    p = fma(p, r, kExp[5]);
-    p = fma(p, r, kExp[4]);
-    p = fma(p, r, kExp[3]);
-    p = fma(p, r, kExp[2]);
-    p = fma(p, r, kExp[1]);
-    p = fma(p, r, kExp[0]);
+    const double tn = fma(x, k.log2e, k.magic);
+    const double n = tn - k.magic;
+    double r = fma(n, k.nln2_1, x);
+    r = fma(n, k.nln2_2, r);
+    double p = k.ex[9];
+    p = fma(p, r, k.ex[8]);
+    p = fma(p, r, k.ex[7]);
+    p = fma(p, r, k.ex[6]);
+    p = fma(p, r, k.ex[5]);
+    p = fma(p, r, k.ex[4]);
+    p = fma(p, r, k.ex[3]);
+    p = fma(p, r, k.ex[2]);
+    p = fma(p, r, k.ex[1]);
+    p = fma(p, r, k.ex[0]);
     const double e = fma(r * r, p, r) + 1.0;
     return ldexp(e, low_word(tn));
 }
@@ -255,7 +277,7 @@ RPDLA_HD inline double rsqrt_mid_f64(double x)
     return fma(y, e * fma(0.375, e, 0.5), y);
 }
 
-RPDLA_HD inline double rsqrt_ge1_f64(double x)
+RPDLA_HD inline double rsqrt_ge1_f64(double x, const Coef& k = kCoef)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     double y = __builtin_amdgcn_rsq(x);
@@ -265,7 +287,7 @@ RPDLA_HD inline double rsqrt_ge1_f64(double x)
     // one third-order step: x^-1/2 = y (1 - e)^-1/2 = y (1 + e/2 + 3e^2/8 + ...),
     // e = 1 - x y^2
     const double e = fma(-x, y * y, 1.0);
-    return fma(y, e * fma(0.375, e, 0.5), y);
+    return fma(y, e * fma(k.c375, e, 0.5), y);
 }
 
 }  // namespace fm

@@ -3,6 +3,8 @@
 // the energy-angle histogram.
 #pragma once
 
+#include <type_traits>
+
 #include "rpdla_device.hpp"
 
 namespace rpdla {
@@ -465,19 +467,20 @@ __global__ void __launch_bounds__(256) ionize_key_kernel(DevCfg c, uint64_t seed
 // rounding of D itself rather than that of tau and Z separately (each up to
 // ~1e3 over the window).
 // ---------------------------------------------------------------------------
-template <int FIELD, class CFG>
+template <int FIELD, int AXIS, class CFG>
 __device__ inline void rhs_f64(const CFG& c, double d, double dl, double X, double Y, double Z,
                                double ux, double uy, double uz, double& dX, double& dY,
-                               double& dZ, double& dux, double& duy, double& duz)
+                               double& dZ, double& dux, double& duy, double& duz,
+                               const fm::Coef& k = fm::kCoef)
 {
-    const double ig = fm::rsqrt_ge1_f64(1.0 + ux * ux + uy * uy + uz * uz);
+    const double ig = fm::rsqrt_ge1_f64(1.0 + ux * ux + uy * uy + uz * uz, k);
     dX = ux * ig; dY = uy * ig; dZ = uz * ig;
     if constexpr (FIELD == 1 || FIELD == 3 || FIELD == 5) {
         // radial field: a = (pe X, pe Y, az), b = pb (-Y, X, 0), so
         // a + beta x b = ((pe - beta_z pb) X, (pe - beta_z pb) Y,
         //                 az + pb (beta_x X + beta_y Y))
         double pe, pb, az;
-        rp_field_parts_f64<FIELD, true>(c, X, Y, Z, d, dl, pe, pb, az);
+        rp_field_parts_f64<FIELD, true, AXIS>(c, X, Y, Z, d, dl, pe, pb, az, k);
         const double f = fma(-dZ, pb, pe);
         dux = -f * X;
         duy = -f * Y;
@@ -497,11 +500,22 @@ __device__ inline void rhs_f64(const CFG& c, double d, double dl, double X, doub
 // energy for a few electrons in a thousand; the compensation terms cX..cuz
 // carry what each addition lost into the next one.
 struct ElecF64 {
-    double X, Y, Z, ux, uy, uz, tau0, taue;
+    double X, Y, Z, ux, uy, uz;
     double D;                                  // retarded time tau - Z
     double cX, cY, cZ, cux, cuy, cuz, cD;
-    int64_t n, N;
+    double h_last;                             // length of the last step
+    int32_t left;                              // steps left
 };
+
+// Steps from tau0 to the window end taue, 0 when there is none (below 2^31:
+// the host limits window / dt to 2e9), and the length of the last one.
+__device__ inline int32_t step_count(double tau0, double taue, double h, double& h_last)
+{
+    const double q = ceil((taue - tau0) / h);
+    const int32_t N = q > 0.0 ? (int32_t)q : 0;
+    h_last = taue - fma((double)(N - 1), h, tau0);
+    return N;
+}
 
 constexpr double kLightSpeed = 299792458.0;            // m/s, exact
 constexpr double kInvLightSpeed = 1.0 / 299792458.0;
@@ -523,44 +537,40 @@ __device__ inline bool elec_init(const CFG& c, ElecF64& e, double t0, double x, 
     e.X = x * c.k; e.Y = y * c.k; e.Z = z * c.k;
     e.ux = e.uy = e.uz = 0.0;
     e.cX = e.cY = e.cZ = e.cux = e.cuy = e.cuz = e.cD = 0.0;
-    e.tau0 = t0 * c.omega;
+    const double tau0 = t0 * c.omega;
     // D = omega (t0 - z0/c), the quotient z0/c carried with its remainder so
     // that the retarded time is formed to the rounding of its own value
     const double zc = z * kInvLightSpeed;
     const double zr = fma(-zc, kLightSpeed, z);
     e.D = ((t0 - zc) - zr * kInvLightSpeed) * c.omega;
     const double tz = (c.window == 0) ? e.Z : 0.0;
-    e.taue = tz + c.ta_n;
-    e.n = 0;
-    e.N = 0;
-    if (!(e.tau0 >= tz - c.tb_n - c.hn)) return false;
-    e.N = (int64_t)ceil((e.taue - e.tau0) / c.hn);
+    e.left = 0;
+    if (!(tau0 >= tz - c.tb_n - c.hn)) return false;
+    e.left = step_count(tau0, tz + c.ta_n, c.hn, e.h_last);
     return true;
 }
 
-template <int FIELD, class CFG>
-__device__ inline void elec_step(const CFG& c, ElecF64& e)
+template <int FIELD, bool BATCH = false, class CFG>
+__device__ inline void elec_step(const CFG& c, ElecF64& e, const fm::Coef& k)
 {
-    const double h = c.hn;
-    const double ta = e.tau0 + (double)e.n * h;
-    const double hs = (e.n == e.N - 1) ? (e.taue - ta) : h;
+    const double hs = (e.left == 1) ? e.h_last : c.hn;
     const double hh = 0.5 * hs;
     double kX, kY, kZ, kx, ky, kz, aX, aY, aZ, ax, ay, az;
-    rhs_f64<FIELD>(c, e.D, -e.cD, e.X, e.Y, e.Z, e.ux, e.uy, e.uz, kX, kY, kZ, kx, ky, kz);
+    rhs_f64<FIELD, 1>(c, e.D, -e.cD, e.X, e.Y, e.Z, e.ux, e.uy, e.uz, kX, kY, kZ, kx, ky, kz, k);
     aX = kX; aY = kY; aZ = kZ; ax = kx; ay = ky; az = kz;
-    rhs_f64<FIELD>(c, e.D, fma(hh, 1.0 - kZ, -e.cD), e.X + hh * kX, e.Y + hh * kY,
+    rhs_f64<FIELD, 0>(c, e.D, fma(hh, 1.0 - kZ, -e.cD), e.X + hh * kX, e.Y + hh * kY,
                    e.Z + hh * kZ, e.ux + hh * kx, e.uy + hh * ky, e.uz + hh * kz, kX, kY, kZ, kx,
-                   ky, kz);
+                   ky, kz, k);
     aX += 2.0 * kX; aY += 2.0 * kY; aZ += 2.0 * kZ;
     ax += 2.0 * kx; ay += 2.0 * ky; az += 2.0 * kz;
-    rhs_f64<FIELD>(c, e.D, fma(hh, 1.0 - kZ, -e.cD), e.X + hh * kX, e.Y + hh * kY,
+    rhs_f64<FIELD, 0>(c, e.D, fma(hh, 1.0 - kZ, -e.cD), e.X + hh * kX, e.Y + hh * kY,
                    e.Z + hh * kZ, e.ux + hh * kx, e.uy + hh * ky, e.uz + hh * kz, kX, kY, kZ, kx,
-                   ky, kz);
+                   ky, kz, k);
     aX += 2.0 * kX; aY += 2.0 * kY; aZ += 2.0 * kZ;
     ax += 2.0 * kx; ay += 2.0 * ky; az += 2.0 * kz;
-    rhs_f64<FIELD>(c, e.D, fma(hs, 1.0 - kZ, -e.cD), e.X + hs * kX, e.Y + hs * kY,
+    rhs_f64<FIELD, 0>(c, e.D, fma(hs, 1.0 - kZ, -e.cD), e.X + hs * kX, e.Y + hs * kY,
                    e.Z + hs * kZ, e.ux + hs * kx, e.uy + hs * ky, e.uz + hs * kz, kX, kY, kZ, kx,
-                   ky, kz);
+                   ky, kz, k);
     const double w6 = hs * (1.0 / 6.0);
     const double sZ = aZ + kZ;
     kahan_add_f64(e.X, e.cX, w6 * (aX + kX));
@@ -571,7 +581,7 @@ __device__ inline void elec_step(const CFG& c, ElecF64& e)
     kahan_add_f64(e.uz, e.cuz, w6 * (az + kz));
     // the weighted slopes of D sum to 6 - sZ
     kahan_add_f64(e.D, e.cD, w6 * (6.0 - sZ));
-    ++e.n;
+    --e.left;
 }
 
 template <class CFG>
@@ -596,19 +606,22 @@ struct ElecRR : ElecF64 {
 };
 
 // Right-hand side with the radiation term; returns gamma^2 Q at the state.
-template <int FIELD, bool RR, class CFG>
+template <int FIELD, bool RR, int AXIS, class CFG>
 __device__ inline double rhs_rr_f64(const CFG& c, double d, double dl, double X, double Y, double Z,
                                     double ux, double uy, double uz, double& dX, double& dY,
-                                    double& dZ, double& dux, double& duy, double& duz)
+                                    double& dZ, double& dux, double& duy, double& duz,
+                                    const fm::Coef& k)
 {
     double ax, ay, az, bx, by, bz;
-    field_f64<FIELD, true, CFG, true>(c, X, Y, Z, d, ax, ay, az, bx, by, bz, dl);
-    const double ig = fm::rsqrt_ge1_f64(1.0 + ux * ux + uy * uy + uz * uz);
+    field_f64<FIELD, true, CFG, true, AXIS>(c, X, Y, Z, d, ax, ay, az, bx, by, bz, dl, k);
+    const double ig = fm::rsqrt_ge1_f64(1.0 + ux * ux + uy * uy + uz * uz, k);
     dX = ux * ig; dY = uy * ig; dZ = uz * ig;
     const double fx = ax + (dY * bz - dZ * by);
     const double fy = ay + (dZ * bx - dX * bz);
     const double fz = az + (dX * by - dY * bx);
-    const double ba = dX * ax + dY * ay + dZ * az;
+    // one product of each of the two transverse terms is fused (stated, as in radius2)
+    const double bt = FIELD < 20 ? fma(dX, ax, dY * ay) : fma(dY, ay, dX * ax);
+    const double ba = fma(dZ, az, bt);
     double q = fx * fx + fy * fy + fz * fz - ba * ba;
     q = q > 0.0 ? q : 0.0;
     dux = -fx; duy = -fy; duz = -fz;
@@ -627,31 +640,29 @@ __device__ inline bool elec_init(const CFG& c, ElecRR<RR>& e, double t0, double 
     return elec_init(c, static_cast<ElecF64&>(e), t0, x, y, z);
 }
 
-template <int FIELD, class CFG, bool RR>
-__device__ inline void elec_step(const CFG& c, ElecRR<RR>& e)
+template <int FIELD, bool BATCH = false, class CFG, bool RR>
+__device__ inline void elec_step(const CFG& c, ElecRR<RR>& e, const fm::Coef& k)
 {
-    const double h = c.hn;
-    const double ta = e.tau0 + (double)e.n * h;
-    const double hs = (e.n == e.N - 1) ? (e.taue - ta) : h;
+    const double hs = (e.left == 1) ? e.h_last : c.hn;
     const double hh = 0.5 * hs;
     double kX, kY, kZ, kx, ky, kz, aX, aY, aZ, ax, ay, az;
-    const double g2q = rhs_rr_f64<FIELD, RR>(c, e.D, -e.cD, e.X, e.Y, e.Z, e.ux, e.uy, e.uz, kX,
-                                             kY, kZ, kx, ky, kz);
+    const double g2q = rhs_rr_f64<FIELD, RR, 1>(c, e.D, -e.cD, e.X, e.Y, e.Z, e.ux, e.uy, e.uz, kX,
+                                             kY, kZ, kx, ky, kz, k);
     e.g2q = g2q > e.g2q ? g2q : e.g2q;
     aX = kX; aY = kY; aZ = kZ; ax = kx; ay = ky; az = kz;
-    rhs_rr_f64<FIELD, RR>(c, e.D, fma(hh, 1.0 - kZ, -e.cD), e.X + hh * kX, e.Y + hh * kY,
+    rhs_rr_f64<FIELD, RR, 0>(c, e.D, fma(hh, 1.0 - kZ, -e.cD), e.X + hh * kX, e.Y + hh * kY,
                           e.Z + hh * kZ, e.ux + hh * kx, e.uy + hh * ky, e.uz + hh * kz, kX, kY,
-                          kZ, kx, ky, kz);
+                          kZ, kx, ky, kz, k);
     aX += 2.0 * kX; aY += 2.0 * kY; aZ += 2.0 * kZ;
     ax += 2.0 * kx; ay += 2.0 * ky; az += 2.0 * kz;
-    rhs_rr_f64<FIELD, RR>(c, e.D, fma(hh, 1.0 - kZ, -e.cD), e.X + hh * kX, e.Y + hh * kY,
+    rhs_rr_f64<FIELD, RR, 0>(c, e.D, fma(hh, 1.0 - kZ, -e.cD), e.X + hh * kX, e.Y + hh * kY,
                           e.Z + hh * kZ, e.ux + hh * kx, e.uy + hh * ky, e.uz + hh * kz, kX, kY,
-                          kZ, kx, ky, kz);
+                          kZ, kx, ky, kz, k);
     aX += 2.0 * kX; aY += 2.0 * kY; aZ += 2.0 * kZ;
     ax += 2.0 * kx; ay += 2.0 * ky; az += 2.0 * kz;
-    rhs_rr_f64<FIELD, RR>(c, e.D, fma(hs, 1.0 - kZ, -e.cD), e.X + hs * kX, e.Y + hs * kY,
+    rhs_rr_f64<FIELD, RR, 0>(c, e.D, fma(hs, 1.0 - kZ, -e.cD), e.X + hs * kX, e.Y + hs * kY,
                           e.Z + hs * kZ, e.ux + hs * kx, e.uy + hs * ky, e.uz + hs * kz, kX, kY,
-                          kZ, kx, ky, kz);
+                          kZ, kx, ky, kz, k);
     const double w6 = hs * (1.0 / 6.0);
     const double sZ = aZ + kZ;
     kahan_add_f64(e.X, e.cX, w6 * (aX + kX));
@@ -661,7 +672,7 @@ __device__ inline void elec_step(const CFG& c, ElecRR<RR>& e)
     kahan_add_f64(e.uy, e.cuy, w6 * (ay + ky));
     kahan_add_f64(e.uz, e.cuz, w6 * (az + kz));
     kahan_add_f64(e.D, e.cD, w6 * (6.0 - sZ));
-    ++e.n;
+    --e.left;
 }
 
 
@@ -701,7 +712,7 @@ struct ElecDP {
     double y[6];          // X, Y, Z, ux, uy, uz
     double k1[6];         // derivative at y (valid once `fresh` is false)
     double tau, h, taue, g_ref, t_ref;
-    int64_t n, N;         // N = 1 while the electron runs, n = 1 when done
+    int32_t left;         // 1 while the electron runs, 0 when done
     long long acc, rej;
     bool fresh, failed;
 };
@@ -720,31 +731,31 @@ __device__ inline bool elec_init(const CFG& c, ElecDP& e, double t0, double x, d
     e.acc = e.rej = 0;
     e.fresh = true;
     e.failed = false;
-    e.n = 0;
-    e.N = 0;
+    e.left = 0;
     if (!(e.tau >= tz - c.tb_n - c.hn)) return false;
-    e.N = (e.taue > e.tau) ? 1 : 0;
+    e.left = (e.taue > e.tau) ? 1 : 0;
     return true;
 }
 
-template <int FIELD, class CFG>
-__device__ inline void dp_rhs(const CFG& c, double tau, const double* y, double* k)
+template <int FIELD, int AXIS, class CFG>
+__device__ inline void dp_rhs(const CFG& c, double tau, const double* y, double* k,
+                              const fm::Coef& co)
 {
-    rhs_f64<FIELD>(c, tau - y[2], 0.0, y[0], y[1], y[2], y[3], y[4], y[5], k[0], k[1], k[2], k[3],
-                   k[4], k[5]);
+    rhs_f64<FIELD, AXIS>(c, tau - y[2], 0.0, y[0], y[1], y[2], y[3], y[4], y[5], k[0], k[1], k[2], k[3],
+                   k[4], k[5], co);
 }
 
-template <int FIELD, class CFG>
-__device__ inline void elec_step(const CFG& c, ElecDP& e)
+template <int FIELD, bool BATCH = false, class CFG>
+__device__ inline void elec_step(const CFG& c, ElecDP& e, const fm::Coef& co)
 {
     using namespace dp;
     if (e.fresh) {
-        dp_rhs<FIELD>(c, e.tau, e.y, e.k1);
+        dp_rhs<FIELD, 1>(c, e.tau, e.y, e.k1, co);
         e.fresh = false;
     }
     if (e.acc + e.rej >= c.ad_max_steps) {
         e.failed = true;
-        e.n = e.N;
+        e.left = 0;
         return;
     }
     double hs = e.h < c.ad_hmax ? e.h : c.ad_hmax;
@@ -753,27 +764,27 @@ __device__ inline void elec_step(const CFG& c, ElecDP& e)
     double k2[6], k3[6], k4[6], k5[6], k6[6], k7[6], yt[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) yt[i] = e.y[i] + hs * (a21 * e.k1[i]);
-    dp_rhs<FIELD>(c, e.tau + c2 * hs, yt, k2);
+    dp_rhs<FIELD, 1>(c, e.tau + c2 * hs, yt, k2, co);
 #pragma unroll
     for (int i = 0; i < 6; ++i) yt[i] = e.y[i] + hs * (a31 * e.k1[i] + a32 * k2[i]);
-    dp_rhs<FIELD>(c, e.tau + c3 * hs, yt, k3);
+    dp_rhs<FIELD, 0>(c, e.tau + c3 * hs, yt, k3, co);
 #pragma unroll
     for (int i = 0; i < 6; ++i) yt[i] = e.y[i] + hs * (a41 * e.k1[i] + a42 * k2[i] + a43 * k3[i]);
-    dp_rhs<FIELD>(c, e.tau + c4 * hs, yt, k4);
+    dp_rhs<FIELD, 0>(c, e.tau + c4 * hs, yt, k4, co);
 #pragma unroll
     for (int i = 0; i < 6; ++i)
         yt[i] = e.y[i] + hs * (a51 * e.k1[i] + a52 * k2[i] + a53 * k3[i] + a54 * k4[i]);
-    dp_rhs<FIELD>(c, e.tau + c5 * hs, yt, k5);
+    dp_rhs<FIELD, 0>(c, e.tau + c5 * hs, yt, k5, co);
 #pragma unroll
     for (int i = 0; i < 6; ++i)
         yt[i] = e.y[i] + hs * (a61 * e.k1[i] + a62 * k2[i] + a63 * k3[i] + a64 * k4[i] +
                                a65 * k5[i]);
-    dp_rhs<FIELD>(c, e.tau + hs, yt, k6);
+    dp_rhs<FIELD, 0>(c, e.tau + hs, yt, k6, co);
     double y5[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i)
         y5[i] = e.y[i] + hs * (b1 * e.k1[i] + b3 * k3[i] + b4 * k4[i] + b5 * k5[i] + b6 * k6[i]);
-    dp_rhs<FIELD>(c, e.tau + hs, y5, k7);
+    dp_rhs<FIELD, 0>(c, e.tau + hs, y5, k7, co);
     double err = 0.0;
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
@@ -785,7 +796,7 @@ __device__ inline void elec_step(const CFG& c, ElecDP& e)
     }
     if (err != err) {            // the step produced no number: give up on this electron
         e.failed = true;
-        e.n = e.N;
+        e.left = 0;
         return;
     }
     if (err <= 1.0) {
@@ -793,10 +804,10 @@ __device__ inline void elec_step(const CFG& c, ElecDP& e)
 #pragma unroll
         for (int i = 0; i < 6; ++i) { e.y[i] = y5[i]; e.k1[i] = k7[i]; }
         ++e.acc;
-        if (last) { e.n = e.N; return; }
+        if (last) { e.left = 0; return; }
         if (e.tau - e.t_ref >= 0.999 * (2.0 * 3.14159265358979323846)) {
             const double g = sqrt(1.0 + e.y[3] * e.y[3] + e.y[4] * e.y[4] + e.y[5] * e.y[5]);
-            if (fabs(g - e.g_ref) <= c.ad_ktol * g) { e.n = e.N; return; }
+            if (fabs(g - e.g_ref) <= c.ad_ktol * g) { e.left = 0; return; }
             e.g_ref = g;
             e.t_ref = e.tau;
         }
@@ -879,11 +890,11 @@ __device__ inline MixedArgs mixed_args(const MixedBase& b, float hk, float kX, f
     return a;
 }
 
-template <int ORDER, class CFG>
+template <int ORDER, int AXIS, class CFG>
 __device__ inline void rp_field_parts_mixed(const CFG& c, const MixedBase& b, const MixedArgs& a,
                                             float& pe, float& pb, float& az)
 {
-    const float r2 = (a.X * a.X + a.Y * a.Y) * (float)c.inv_w0n2;
+    const float r2 = radius2<AXIS>(a.X, a.Y) * (float)c.inv_w0n2;
     const float zeta = a.zeta;
     const float iD = __builtin_amdgcn_rcpf(1.0f + zeta * zeta);
     const float rD = r2 * iD;
@@ -892,7 +903,7 @@ __device__ inline void rp_field_parts_mixed(const CFG& c, const MixedBase& b, co
     const float sn = __builtin_amdgcn_sinf(ph), cs = __builtin_amdgcn_cosf(ph);
     const float gi = g * (iD * iD);
     float PE, PB, EZe;
-    rp_brackets<ORDER, float>(gi * cs, gi * sn, zeta, rD, (float)c.e2 * iD, PE, PB, EZe);
+    rp_brackets<ORDER, float>(gi * cs, gi * sn, zeta, rD, (float)c.e2 * iD, PE, PB, EZe, fm::kCoef);
     pe = (float)c.er_w * PE;
     pb = PB * (float)c.inv_w0n;
     az = (float)c.ez_e * EZe;
@@ -914,14 +925,14 @@ __device__ inline void field_mixed(const CFG& c, const MixedBase& b, const Mixed
         ax = e; ay = 0.f; az = 0.f; bx = 0.f; by = e; bz = 0.f;
     } else {
         float pe, pb;
-        rp_field_parts_mixed<FIELD>(c, b, a, pe, pb, az);
+        rp_field_parts_mixed<FIELD, 0>(c, b, a, pe, pb, az);
         ax = pe * a.X; ay = pe * a.Y;
         bx = -pb * a.Y; by = pb * a.X;
         bz = 0.f;
     }
 }
 
-template <int FIELD, bool FIRST, class CFG>
+template <int FIELD, bool FIRST, int AXIS, class CFG>
 __device__ inline void rhs_mixed(const CFG& c, const MixedBase& b, float hk, float& dX, float& dY,
                                  float& dZ, float ux, float uy, float uz, float& dux, float& duy,
                                  float& duz)
@@ -933,7 +944,7 @@ __device__ inline void rhs_mixed(const CFG& c, const MixedBase& b, float hk, flo
     if constexpr (FIELD == 1 || FIELD == 3 || FIELD == 5) {
         // radial field: the force from its radial and axial parts, as in rhs_f64
         float pe, pb, az;
-        rp_field_parts_mixed<FIELD>(c, b, a, pe, pb, az);
+        rp_field_parts_mixed<FIELD, AXIS>(c, b, a, pe, pb, az);
         const float f = fmaf(-dZ, pb, pe);
         dux = -f * a.X;
         duy = -f * a.Y;
@@ -956,9 +967,9 @@ __device__ inline void kahan_add(float& s, float& comp, float v)
 }
 
 struct ElecMixed {
-    double X, Y, Z, tau0, taue;
+    double X, Y, Z, tau0, h_last;
     float ux, uy, uz, cx, cy, cz;
-    int64_t n, N;
+    int32_t n, left;               // steps done and left
 };
 
 template <class CFG>
@@ -968,34 +979,33 @@ __device__ inline bool elec_init(const CFG& c, ElecMixed& e, double t0, double x
     e.ux = e.uy = e.uz = 0.f; e.cx = e.cy = e.cz = 0.f;
     e.tau0 = t0 * c.omega;
     const double tz = (c.window == 0) ? e.Z : 0.0;
-    e.taue = tz + c.ta_n;
     e.n = 0;
-    e.N = 0;
+    e.left = 0;
     if (!(e.tau0 >= tz - c.tb_n - c.hn)) return false;
-    e.N = (int64_t)ceil((e.taue - e.tau0) / c.hn);
+    e.left = step_count(e.tau0, tz + c.ta_n, c.hn, e.h_last);
     return true;
 }
 
-template <int FIELD, class CFG>
-__device__ inline void elec_step(const CFG& c, ElecMixed& e)
+template <int FIELD, bool BATCH = false, class CFG>
+__device__ inline void elec_step(const CFG& c, ElecMixed& e, const fm::Coef&)
 {
     const double h = c.hn;
-    const double ta = e.tau0 + (double)e.n * h;
-    const double hsd = (e.n == e.N - 1) ? (e.taue - ta) : h;
+    const double ta = fma((double)e.n, h, e.tau0);
+    const double hsd = (e.left == 1) ? e.h_last : h;
     const float hs = (float)hsd, hh = 0.5f * hs;
     const MixedBase b = mixed_base(c, ta, e.X, e.Y, e.Z);
     float kX, kY, kZ, kx, ky, kz, aX, aY, aZ, ax, ay, az;
-    rhs_mixed<FIELD, true>(c, b, 0.f, kX, kY, kZ, e.ux, e.uy, e.uz, kx, ky, kz);
+    rhs_mixed<FIELD, true, BATCH ? 0 : 1>(c, b, 0.f, kX, kY, kZ, e.ux, e.uy, e.uz, kx, ky, kz);
     aX = kX; aY = kY; aZ = kZ; ax = kx; ay = ky; az = kz;
-    rhs_mixed<FIELD, false>(c, b, hh, kX, kY, kZ, e.ux + hh * kx, e.uy + hh * ky, e.uz + hh * kz,
+    rhs_mixed<FIELD, false, 0>(c, b, hh, kX, kY, kZ, e.ux + hh * kx, e.uy + hh * ky, e.uz + hh * kz,
                             kx, ky, kz);
     aX += 2.f * kX; aY += 2.f * kY; aZ += 2.f * kZ;
     ax += 2.f * kx; ay += 2.f * ky; az += 2.f * kz;
-    rhs_mixed<FIELD, false>(c, b, hh, kX, kY, kZ, e.ux + hh * kx, e.uy + hh * ky, e.uz + hh * kz,
+    rhs_mixed<FIELD, false, 0>(c, b, hh, kX, kY, kZ, e.ux + hh * kx, e.uy + hh * ky, e.uz + hh * kz,
                             kx, ky, kz);
     aX += 2.f * kX; aY += 2.f * kY; aZ += 2.f * kZ;
     ax += 2.f * kx; ay += 2.f * ky; az += 2.f * kz;
-    rhs_mixed<FIELD, false>(c, b, hs, kX, kY, kZ, e.ux + hs * kx, e.uy + hs * ky, e.uz + hs * kz,
+    rhs_mixed<FIELD, false, 0>(c, b, hs, kX, kY, kZ, e.ux + hs * kx, e.uy + hs * ky, e.uz + hs * kz,
                             kx, ky, kz);
     const double w6d = hsd * (1.0 / 6.0);
     const float w6 = hs * (1.0f / 6.0f);
@@ -1004,6 +1014,7 @@ __device__ inline void elec_step(const CFG& c, ElecMixed& e)
     kahan_add(e.uy, e.cy, w6 * (ay + ky));
     kahan_add(e.uz, e.cz, w6 * (az + kz));
     ++e.n;
+    --e.left;
 }
 
 template <class CFG>
@@ -1115,32 +1126,110 @@ template <class E> struct ElecWaves { static constexpr int value = 4; };
 template <> struct ElecWaves<ElecMixed> { static constexpr int value = 7; };
 template <> struct ElecWaves<ElecDP> { static constexpr int value = 1; };
 
+// Configuration constants of the radial field's step (the members of DevCfg
+// that it reads, under the same names).
+struct RadialCfg {
+    double hn, inv_zrn, inv_w0n2, e2, phi0, inv_T0n, a0_w, er_scale, ez_2, rr_kappa;
+};
+
+// What a step reads besides its electron, in registers for the whole kernel.
+// A step is bound by instruction issue (one wave on a SIMD takes 5.1 cycles
+// for each instruction, scalar ones included; four waves 4.3 for each vector
+// one, with scalar ones beside them).  Left to itself the compiler puts a
+// literal's two halves into scalar registers at each use: 195 scalar moves and
+// 20 moves of spilled scalars in an order-5 step of 841 instructions.  With
+// the 38 constants and the 9 of the configuration kept from the start (most in
+// scalar pairs; in vector registers where an instruction takes two constants,
+// as it can read one scalar operand only, and what no longer fits) the step
+// issues 595 vector and 12 scalar instructions, at the same 4 waves.  Measured:
+// 8192 slots 45.2 -> 37.0 ms (one wave per SIMD), 1e5 slots 124.3 -> 111.9 ms,
+// 2e6 slots 870 -> 838 ms, with radiation reaction 2e4 slots 92.7 -> 77.4 ms.
 template <int FIELD, class ELEC>
-__global__ void __launch_bounds__(256, ElecWaves<ELEC>::value) push_kernel(DevCfg c, PushIO io)
+struct StepRegs {
+    static constexpr bool kHold = (FIELD == 1 || FIELD == 3 || FIELD == 5) &&
+                                  !std::is_same<ELEC, ElecMixed>::value &&
+                                  !std::is_same<ELEC, ElecDP>::value;
+    using Cfg = typename std::conditional<kHold, RadialCfg, DevCfg>::type;
+    Cfg c;
+    fm::Coef k;
+    __device__ inline explicit StepRegs(const DevCfg& d)
+    {
+        if constexpr (kHold) {
+            c = RadialCfg{d.hn, d.inv_zrn, d.inv_w0n2, d.e2, d.phi0, d.inv_T0n, d.a0_w, d.er_scale,
+                          d.ez_2, d.rr_kappa};
+            keep_in_vgpr(k.magic);
+            keep_in_vgpr(k.ex[8]);
+            keep_in_vgpr(k.sg[5]);
+            keep_in_vgpr(k.kp[4]);
+            keep_in_sgpr(k.log2e); keep_in_sgpr(k.nln2_1); keep_in_sgpr(k.nln2_2);
+#pragma unroll
+            for (int i = 0; i < 10; ++i) if (i != 8) keep_in_sgpr(k.ex[i]);
+            keep_in_sgpr(k.inv_pi); keep_in_sgpr(k.npi_1); keep_in_sgpr(k.npi_2);
+#pragma unroll
+            for (int i = 0; i < 7; ++i) if (i != 5) keep_in_sgpr(k.sg[i]);
+#pragma unroll
+            for (int i = 0; i < 6; ++i) if (i != 4) keep_in_sgpr(k.kp[i]);
+            keep_in_vgpr(k.ns2o8); keep_in_vgpr(k.s2);
+            keep_in_vgpr(k.c375); keep_in_vgpr(k.c1_0625); keep_in_vgpr(k.c1875);
+            keep_in_vgpr(k.c5);
+            keep_in_vgpr(k.npi_3);
+        } else {
+            c = d;
+        }
+    }
+};
+
+struct PushArgs {
+    DevCfg c;
+    PushIO io;
+};
+
+// The kernel's arguments where they lie, read anew at each call: what only the
+// refill and the finish of an electron need does not stay in scalar registers.
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef const __attribute__((address_space(4))) PushArgs* PushArgsPtr;
+__device__ inline PushArgsPtr push_args()
 {
+    PushArgsPtr p = (PushArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+#else
+typedef const PushArgs* PushArgsPtr;   // host pass: declaration only
+__device__ PushArgsPtr push_args();
+#endif
+
+template <int FIELD, class ELEC>
+__global__ void __launch_bounds__(256, ElecWaves<ELEC>::value) push_kernel(PushArgs args)
+{
+    constexpr bool X = HasExtra<ELEC>::value;
+    const StepRegs<FIELD, ELEC> R(args.c);
     int64_t idx = -1;
     bool exhausted = false;
     ELEC e;
-    e.n = e.N = 0;
+    e.left = 0;
     while (true) {
         // refill lanes without an electron (unborn slots are consumed here)
         while (true) {
             const bool need = (idx < 0) && !exhausted;
             if (__ballot(need) == 0) break;
+            const PushArgsPtr pa = push_args();
+            const PushIO io = pa->io;
             const int64_t j = queue_take_xcd(io.queue, io.n_slots, need);
             if (need && j < 0) exhausted = true;
             if (need && j >= 0) {
                 const double t0 = io.tb[j];
                 if (!(t0 < __builtin_inf())) {
-                    write_nan<HasExtra<ELEC>::value>(io, j);
+                    write_nan<X>(io, j);
                 } else {
+                    const DevCfg c = pa->c;
                     const int64_t a = j / io.spa;
                     if (!elec_init(c, e, t0, io.x0[a], io.y0[a], io.z0[a])) {
-                        write_nan<HasExtra<ELEC>::value>(io, j);
+                        write_nan<X>(io, j);
                         continue;
                     }
                     idx = j;
-                    if (e.N <= 0) {
+                    if (e.left <= 0) {
                         elec_final(c, e, io.ux[j], io.uy[j], io.uz[j], io.xf[j], io.yf[j],
                                    io.zf[j]);
                         elec_extra(c, e, io, j);
@@ -1151,8 +1240,11 @@ __global__ void __launch_bounds__(256, ElecWaves<ELEC>::value) push_kernel(DevCf
         }
         if (__ballot(idx >= 0) == 0) break;
         if (idx >= 0) {
-            elec_step<FIELD>(c, e);
-            if (e.n == e.N) {
+            elec_step<FIELD>(R.c, e, R.k);
+            if (e.left == 0) {
+                const PushArgsPtr pa = push_args();
+                const PushIO io = pa->io;
+                const DevCfg c = pa->c;
                 elec_final(c, e, io.ux[idx], io.uy[idx], io.uz[idx], io.xf[idx], io.yf[idx],
                            io.zf[idx]);
                 elec_extra(c, e, io, idx);
