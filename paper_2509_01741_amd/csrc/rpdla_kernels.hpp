@@ -1130,6 +1130,8 @@ template <> struct ElecWaves<ElecDP> { static constexpr int value = 1; };
 // that it reads, under the same names).
 struct RadialCfg {
     double hn, inv_zrn, inv_w0n2, e2, phi0, inv_T0n, a0_w, er_scale, ez_2, rr_kappa;
+    double ad_rtol, ad_atol, ad_hmax, ad_ktol;
+    int64_t ad_max_steps;
 };
 
 // What a step reads besides its electron, in registers for the whole kernel.
@@ -1144,11 +1146,13 @@ struct RadialCfg {
 // issues 595 vector and 12 scalar instructions, at the same 4 waves.  Measured:
 // 8192 slots 45.2 -> 37.0 ms (one wave per SIMD), 1e5 slots 124.3 -> 111.9 ms,
 // 2e6 slots 870 -> 838 ms, with radiation reaction 2e4 slots 92.7 -> 77.4 ms.
+// The controlled-step form has the vector registers of 2 waves to fill and
+// takes most constants there: 1773 -> 1302 instructions in its main block, 2e6
+// slots 163.7 -> 145.3 ms.
 template <int FIELD, class ELEC>
 struct StepRegs {
     static constexpr bool kHold = (FIELD == 1 || FIELD == 3 || FIELD == 5) &&
-                                  !std::is_same<ELEC, ElecMixed>::value &&
-                                  !std::is_same<ELEC, ElecDP>::value;
+                                  !std::is_same<ELEC, ElecMixed>::value;
     using Cfg = typename std::conditional<kHold, RadialCfg, DevCfg>::type;
     Cfg c;
     fm::Coef k;
@@ -1156,23 +1160,25 @@ struct StepRegs {
     {
         if constexpr (kHold) {
             c = RadialCfg{d.hn, d.inv_zrn, d.inv_w0n2, d.e2, d.phi0, d.inv_T0n, d.a0_w, d.er_scale,
-                          d.ez_2, d.rr_kappa};
+                          d.ez_2, d.rr_kappa, d.ad_rtol, d.ad_atol, d.ad_hmax, d.ad_ktol,
+                          d.ad_max_steps};
+            constexpr bool kWide = std::is_same<ELEC, ElecDP>::value;
+            auto keep = [](double& v) {
+                if constexpr (kWide) keep_in_vgpr(v); else keep_in_sgpr(v);
+            };
             keep_in_vgpr(k.magic);
-            keep_in_vgpr(k.ex[8]);
-            keep_in_vgpr(k.sg[5]);
-            keep_in_vgpr(k.kp[4]);
             keep_in_sgpr(k.log2e); keep_in_sgpr(k.nln2_1); keep_in_sgpr(k.nln2_2);
 #pragma unroll
-            for (int i = 0; i < 10; ++i) if (i != 8) keep_in_sgpr(k.ex[i]);
+            for (int i = 0; i < 10; ++i) if (i == 8) keep_in_vgpr(k.ex[i]); else keep(k.ex[i]);
             keep_in_sgpr(k.inv_pi); keep_in_sgpr(k.npi_1); keep_in_sgpr(k.npi_2);
+            keep_in_vgpr(k.npi_3);
 #pragma unroll
-            for (int i = 0; i < 7; ++i) if (i != 5) keep_in_sgpr(k.sg[i]);
+            for (int i = 0; i < 7; ++i) if (i == 5) keep_in_vgpr(k.sg[i]); else keep(k.sg[i]);
 #pragma unroll
-            for (int i = 0; i < 6; ++i) if (i != 4) keep_in_sgpr(k.kp[i]);
+            for (int i = 0; i < 6; ++i) if (i == 4) keep_in_vgpr(k.kp[i]); else keep(k.kp[i]);
             keep_in_vgpr(k.ns2o8); keep_in_vgpr(k.s2);
             keep_in_vgpr(k.c375); keep_in_vgpr(k.c1_0625); keep_in_vgpr(k.c1875);
             keep_in_vgpr(k.c5);
-            keep_in_vgpr(k.npi_3);
         } else {
             c = d;
         }
