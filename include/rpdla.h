@@ -165,13 +165,9 @@ rpdla_status rpdla_sample_atoms_annulus(uint64_t seed, uint32_t cfg_id, uint64_t
  * (slot j*K + (k - k_first)), seconds, +INF where the state is not reached
  * in the window.  A state whose rate, bounded through the field's envelope,
  * cannot reach its threshold within the window is left unborn without
- * integrating its panels (the same result).  From 16384 atoms on, the atoms
- * are taken in an order that groups similar work in each wave (a sort by the
- * number of states that bound leaves open, then by the peak-field bound),
- * which needs stream-ordered scratch of about 16 bytes per atom
- * (hipMallocAsync / hipFreeAsync on `stream`); results do not depend on the
- * order.  EINVAL: bad
- * laser, 1 <= k_first <= k_last <= 10 violated, null pointers with
+ * integrating its panels (the same result).  One wave per atom; no device
+ * memory is allocated.  EINVAL: bad laser,
+ * 1 <= k_first <= k_last <= 10 violated, null pointers with
  * n_atoms > 0.
  * ------------------------------------------------------------------------ */
 rpdla_status rpdla_ionize(const rpdla_laser* L, uint64_t seed, uint32_t cfg_id,

@@ -2,13 +2,13 @@
 // argument validation, the per-configuration constants in normalized units,
 // kernel dispatch and launch shapes.
 #include <hip/hip_runtime.h>
-#include <hipcub/device/device_radix_sort.hpp>
 
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <string>
@@ -54,9 +54,6 @@ constexpr double kNeIpEv[10] = {21.564540, 40.96297, 63.4233, 97.1900, 126.247,
 
 // Largest slot count of one push call.
 constexpr int64_t kMaxPushSlots = (int64_t)1 << 40;
-// Below this many atoms the ionization runs in the caller's order (sorting
-// the atoms by work would cost more than it saves).
-constexpr int64_t kIonizeSortMin = 16384;
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -230,49 +227,24 @@ int persistent_blocks(K kernel, int64_t work_items, int block, int grid_factor, 
 
 constexpr int kKindPush = 0, kKindIonize = 1, kKindBatchPush = 2;
 
+// Atoms of one ionization launch: a wave each (the hardware hands the waves out
+// as others end, which levels the atoms' unequal work), and a grid holds fewer
+// than 2^32 threads.
+constexpr int64_t kIonizeAtoms = (int64_t)1 << 25;
+
 template <int FIELD>
 rpdla_status launch_ionize(const DevCfg& c, uint64_t seed, uint32_t cfg, uint64_t first,
                            int64_t n, const double* x, const double* y, const double* z, int kf,
                            int kl, double* tb, hipStream_t st)
 {
     const int bs = get_shape(kKindIonize, FIELD, 0).block;
-    if (n < kIonizeSortMin || n > (int64_t)INT32_MAX) {
-        hipLaunchKernelGGL(rpdla::ionize_kernel<FIELD>, dim3((unsigned)cdiv(n, bs)), dim3(bs), 0,
-                           st, c, seed, cfg, first, n, x, y, z, kf, kl, tb,
-                           (const uint32_t*)nullptr);
+    for (int64_t i = 0; i < n; i += kIonizeAtoms) {
+        const int64_t m = std::min(n - i, kIonizeAtoms);
+        hipLaunchKernelGGL(rpdla::ionize_kernel<FIELD>, dim3((unsigned)cdiv(m, bs / 64)), dim3(bs),
+                           0, st, c, seed, cfg, first + (uint64_t)i, m, x + i, y + i, z + i, kf,
+                           kl, tb + i * (kl - kf + 1));
         RPDLA_HIP(hipGetLastError());
-        return RPDLA_OK;
     }
-    // atoms ordered by their work key (radix sort of key/index pairs), so that
-    // each wave holds atoms of similar work; stream-ordered scratch
-    size_t sort_bytes = 0;
-    RPDLA_HIP(hipcub::DeviceRadixSort::SortPairs(nullptr, sort_bytes, (const uint32_t*)nullptr,
-                                                 (uint32_t*)nullptr, (const uint32_t*)nullptr,
-                                                 (uint32_t*)nullptr, (int)n, 0, 32, st));
-    const size_t arr = align256((size_t)n * sizeof(uint32_t));
-    char* buf = nullptr;
-    RPDLA_HIP(hipMallocAsync((void**)&buf, 4 * arr + sort_bytes, st));
-    uint32_t* key_in = (uint32_t*)buf;
-    uint32_t* key_out = (uint32_t*)(buf + arr);
-    uint32_t* idx_in = (uint32_t*)(buf + 2 * arr);
-    uint32_t* idx_out = (uint32_t*)(buf + 3 * arr);
-    rpdla_status r = RPDLA_OK;
-    hipLaunchKernelGGL(rpdla::ionize_key_kernel<FIELD>, dim3((unsigned)cdiv(n, 256)), dim3(256), 0,
-                       st, c, seed, cfg, first, n, x, y, z, kf, kl, key_in, idx_in);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess)
-        e = hipcub::DeviceRadixSort::SortPairs(buf + 4 * arr, sort_bytes, key_in, key_out, idx_in,
-                                               idx_out, (int)n, 0, 32, st);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(rpdla::ionize_kernel<FIELD>, dim3((unsigned)cdiv(n, bs)), dim3(bs), 0,
-                           st, c, seed, cfg, first, n, x, y, z, kf, kl, tb,
-                           (const uint32_t*)idx_out);
-        e = hipGetLastError();
-    }
-    if (e != hipSuccess) r = fail(RPDLA_EHIP, "ionize: %s", hipGetErrorString(e));
-    const hipError_t fe = hipFreeAsync(buf, st);
-    if (r != RPDLA_OK) return r;
-    if (fe != hipSuccess) return fail(RPDLA_EHIP, "hipFreeAsync: %s", hipGetErrorString(fe));
     return RPDLA_OK;
 }
 
@@ -734,7 +706,6 @@ constexpr size_t kMaxGraphs = 32;
 template <int FIELD, class ELEC>
 rpdla_status run_batched_impl(const rpdla::BatchArgs& A, int64_t n_chunks, hipStream_t s)
 {
-    const size_t lds_i = (size_t)A.n_cfg * sizeof(DevCfg);
     const size_t lds_p = (size_t)A.n_cfg * sizeof(unsigned long long);
     auto* kpush = rpdla::batch_push_kernel<FIELD, ELEC>;
     auto* kion = rpdla::batch_ionize_kernel<FIELD>;
@@ -742,13 +713,16 @@ rpdla_status run_batched_impl(const rpdla::BatchArgs& A, int64_t n_chunks, hipSt
     const int64_t slots = (int64_t)A.n_cfg * A.apc * A.K;
     const int64_t grid_p = persistent_blocks(kpush, slots, sh.block, sh.grid_factor, lds_p);
     const unsigned grid_a = (unsigned)cdiv((int64_t)A.n_cfg * A.apc, 256);
+    const int64_t atoms = (int64_t)A.n_cfg * A.apc;
     int64_t grid_h = cdiv(slots, 256);
     if (grid_h > 8192) grid_h = 8192;
 
     auto enqueue_chunk = [&](hipStream_t st) -> rpdla_status {
         hipLaunchKernelGGL(rpdla::batch_zero_queue_kernel, dim3(1), dim3(64), 0, st, A.ctl);
         hipLaunchKernelGGL(rpdla::batch_sample_kernel, dim3(grid_a), dim3(256), 0, st, A);
-        hipLaunchKernelGGL(kion, dim3(grid_a), dim3(256), lds_i, st, A);
+        for (int64_t i = 0; i < atoms; i += kIonizeAtoms)
+            hipLaunchKernelGGL(kion, dim3((unsigned)cdiv(std::min(atoms - i, kIonizeAtoms), 4)),
+                               dim3(256), 0, st, A, A.cfgs, i);
         hipLaunchKernelGGL(kpush, dim3((unsigned)grid_p), dim3(sh.block), lds_p, st, A, A.cfgs);
         hipLaunchKernelGGL(rpdla::batch_hist_kernel, dim3((unsigned)grid_h), dim3(256), 0, st, A);
         hipLaunchKernelGGL(rpdla::batch_advance_kernel, dim3(1), dim3(64), 0, st, A.ctl);

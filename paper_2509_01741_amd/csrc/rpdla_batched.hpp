@@ -82,26 +82,23 @@ __global__ void __launch_bounds__(256) batch_sample_kernel(BatchArgs A)
     A.z[i] = A.geo[2 * c + 1] * (2.0 * u01(r.v[2]) - 1.0);
 }
 
+// One wave per atom, as ionize_kernel, for atoms i0, i0 + 1, ... of the chunk;
+// the wave's configuration is uniform and read with scalar loads.
 template <int FIELD>
-__global__ void __launch_bounds__(256, 2) batch_ionize_kernel(BatchArgs A)
+__global__ void __launch_bounds__(256, IonizeWaves<FIELD>::value) batch_ionize_kernel(
+    BatchArgs A, const DevCfg* __restrict__ cfgs, int64_t i0)
 {
-    extern __shared__ double lds_raw[];
-    DevCfg* s_cfg = reinterpret_cast<DevCfg*>(lds_raw);
-    {
-        const int nwords = A.n_cfg * (int)(sizeof(DevCfg) / sizeof(double));
-        const double* src = reinterpret_cast<const double*>(A.cfgs);
-        for (int w = threadIdx.x; w < nwords; w += blockDim.x) lds_raw[w] = src[w];
-    }
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = i0 + wave_index();
     if (i >= (int64_t)A.n_cfg * A.apc) return;
     const int c = (int)(i / A.apc);
     const int64_t a = i - (int64_t)c * A.apc;
     const int64_t first = (int64_t)A.ctl->chunk * A.apc;
     if (first + a >= A.atoms_per_cfg) return;
-    const DevCfg& cf = s_cfg[c];
-    ionize_atom<FIELD>(cf, A.seed, A.cfg_base + (uint32_t)c, (uint64_t)(first + a), A.x[i] * cf.k,
-                       A.y[i] * cf.k, A.z[i] * cf.k, A.k_first, A.K, A.tb + i * A.K);
+    const DevCfg& cf = cfgs[c];
+    const RateRegs R(cf);
+    ionize_atom<FIELD>(cf, R, A.seed, A.cfg_base + (uint32_t)c, (uint64_t)(first + a),
+                       A.x[i] * cf.k, A.y[i] * cf.k, A.z[i] * cf.k, A.k_first, A.K,
+                       A.tb + i * A.K);
 }
 
 // One persistent launch over n_cfg * apc * K slots.  Slot j belongs to

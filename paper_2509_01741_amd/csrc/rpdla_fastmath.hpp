@@ -84,6 +84,15 @@ struct Coef {
 };
 constexpr Coef kCoef{};
 
+// The logarithm's constants beside those (the tunnelling rate takes both).
+struct LogCoef {
+    double rsqrt2 = 0.70710678118654752;
+    // atanh series, 2/19 down to 2/3
+    double at[9] = {2.0 / 19.0, 2.0 / 17.0, 2.0 / 15.0, 2.0 / 13.0, 2.0 / 11.0,
+                    2.0 / 9.0,  2.0 / 7.0,  2.0 / 5.0,  2.0 / 3.0};
+};
+constexpr LogCoef kLogCoef{};
+
 // sin r, cos r for |r| <= pi/4 (a little beyond), rotated to quadrant q.
 RPDLA_HD inline void sincos_reduced(double r, int q, double* s_out, double* c_out)
 {
@@ -219,11 +228,11 @@ RPDLA_HD inline double rcp_f64(double d);
 // (the first term left out, f^20/21, is below 2^-55 of the sum).  f comes from
 // the refined reciprocal with one residual correction, m + 1 carried exactly
 // as b + bl.  ln x = e ln2 + ln m, ln2 in two parts.  A few ulp.
-RPDLA_HD inline double log_pos_f64(double x)
+RPDLA_HD inline double log_pos_f64(double x, const Coef& k = kCoef, const LogCoef& l = kLogCoef)
 {
     int e;
     double m = frexp(x, &e);                      // m in [0.5, 1)
-    const bool lo = m < 0.70710678118654752;
+    const bool lo = m < l.rsqrt2;
     m = lo ? m + m : m;
     e = lo ? e - 1 : e;
     const double a = m - 1.0;                     // exact
@@ -237,18 +246,18 @@ RPDLA_HD inline double log_pos_f64(double x)
     // (so that it need not be held in a vector register across a loop)
     const double z = f * f;
     const double z2 = z * z, z4 = z2 * z2, z8 = z4 * z4;
-    double p = (2.0 / 19.0) * z8;
-    p = fma(2.0 / 17.0, z4 * z2 * z, p);
-    p = fma(2.0 / 15.0, z4 * z2, p);
-    p = fma(2.0 / 13.0, z4 * z, p);
-    p = fma(2.0 / 11.0, z4, p);
-    p = fma(2.0 / 9.0, z2 * z, p);
-    p = fma(2.0 / 7.0, z2, p);
-    p = fma(2.0 / 5.0, z, p);
-    p = p + 2.0 / 3.0;
+    double p = l.at[0] * z8;
+    p = fma(l.at[1], z4 * z2 * z, p);
+    p = fma(l.at[2], z4 * z2, p);
+    p = fma(l.at[3], z4 * z, p);
+    p = fma(l.at[4], z4, p);
+    p = fma(l.at[5], z2 * z, p);
+    p = fma(l.at[6], z2, p);
+    p = fma(l.at[7], z, p);
+    p = p + l.at[8];
     const double lnm = fma(f * z, p, f + f);
     const double ed = (double)e;
-    return fma(ed, kLn2_1, fma(ed, kLn2_2, lnm));
+    return fma(-ed, k.nln2_1, fma(-ed, k.nln2_2, lnm));
 }
 
 RPDLA_HD inline double rcp_f64(double d)
@@ -265,7 +274,7 @@ RPDLA_HD inline double rcp_f64(double d)
 
 // Reciprocal square root for x in [2^-960, 2^960] (no scaling of the argument):
 // the hardware estimate refined by one third-order step, as rsqrt_ge1_f64.
-RPDLA_HD inline double rsqrt_mid_f64(double x)
+RPDLA_HD inline double rsqrt_mid_f64(double x, const Coef& k = kCoef)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     double y = __builtin_amdgcn_rsq(x);
@@ -274,7 +283,7 @@ RPDLA_HD inline double rsqrt_mid_f64(double x)
     double y = (x > 1e-30 && x < 1e30) ? (double)(1.0f / sqrtf((float)x)) : 1.0 / sqrt(x);
 #endif
     const double e = fma(-x, y * y, 1.0);
-    return fma(y, e * fma(0.375, e, 0.5), y);
+    return fma(y, e * fma(k.c375, e, 0.5), y);
 }
 
 RPDLA_HD inline double rsqrt_ge1_f64(double x, const Coef& k = kCoef)

@@ -76,7 +76,7 @@ __global__ void __launch_bounds__(256) birth_phase_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Ionization.  One lane per atom.  Time axis in panels of width h from the
+// Ionization.  One wave per atom.  Time axis in panels of width h from the
 // window start; state s (charge state k_first + s) accumulates GL-4 panel
 // integrals of its rate from the previous birth; at the panel where the sum
 // reaches the Exp(1) threshold the crossing is solved by bracketed Newton.
@@ -152,69 +152,25 @@ __device__ inline AtomGeom atom_geom(const CFG& c, double X, double Y, double Z)
     return a;
 }
 
-template <int FIELD, class CFG>
-__device__ inline double emag2_atom(const CFG& c, const AtomGeom& a, double d)
+template <int FIELD, class CFG, class RCFG>
+__device__ inline double emag2_atom(const CFG& c, const RCFG& rc, const AtomGeom& a, double d,
+                                    const fm::Coef& k = fm::kCoef)
 {
     if constexpr (FIELD == 1 || FIELD == 3 || FIELD == 5) {
-        const double s = d * c.inv_T0n;
-        const double g = c.a0 * fm::exp_fin_f64(a.mrD - s * s);
+        const double s = d * rc.inv_T0n;
+        const double g = rc.a0 * fm::exp_fin_f64(a.mrD - s * s, k);
         // the sign (-1)^n of the half-angle form cancels in the squares
         double sg, kp;
-        fm::cis_half2_f64(d, a.psi_c, &sg, &kp);
+        fm::cis_half2_f64(d, a.psi_c, &sg, &kp, k);
         const double cs = fma(-sg, sg, 1.0), sn = sg * kp;
-        const double et = c.er_scale * g * (cs * a.aer - sn * a.aei);
-        const double ez = c.ez_scale * g * (sn * a.azr + cs * a.azi);
-        return et * et * a.r2 + ez * ez;
+        // one product of each sum fused, as stated: birth times then do not
+        // depend on how the kernel around this is compiled
+        const double et = rc.er_scale * g * fma(a.aer, cs, -(a.aei * sn));
+        const double ez = rc.ez_scale * g * fma(a.azr, sn, a.azi * cs);
+        return fma(ez, ez, et * et * a.r2);
     } else {
         return emag2_f64<FIELD>(c, a.X, a.Y, a.Z, d);
     }
-}
-
-template <int FIELD, class CFG>
-__device__ inline double rate_at(const CFG& c, const AdkState& st, const AtomGeom& a, double d)
-{
-    return adk_rate_n(st, emag2_atom<FIELD>(c, a, d));
-}
-
-// GL-4 estimate of the integral of the rate over [a, b]; the nodes are
-// evaluated one after another (one field evaluation live at a time).
-template <int FIELD, class CFG>
-__device__ inline double gl4_integral(const CFG& c, const AdkState& st, const AtomGeom& ag,
-                                      double a, double b)
-{
-    const double h = 0.5 * (b - a), m = 0.5 * (a + b);
-    double acc = 0.0;
-#pragma unroll 1
-    for (int i = 0; i < 4; ++i) acc += c.gl_w[i] * rate_at<FIELD>(c, st, ag, m + h * c.gl_x[i]);
-    return h * acc;
-}
-
-template <int FIELD, class CFG>
-__device__ double solve_crossing(const CFG& c, const AdkState& st, const AtomGeom& ag, double lo,
-                                 double hi, double target, double Ghi)
-{
-    if (!(target > 0.0)) return lo;
-    double tl = lo, th = hi;
-    double t = lo + (hi - lo) * (target / Ghi);
-    if (!(t > tl && t < th)) t = 0.5 * (tl + th);
-    for (int it = 0; it < 100; ++it) {
-        const double gd = gl4_integral<FIELD>(c, st, ag, lo, t) - target;
-        if (gd == 0.0) return t;
-        if (gd > 0.0) th = t; else tl = t;
-        const double tol = ldexp(fmax(fabs(t), kTwoPi), -40);
-        const double w = rate_at<FIELD>(c, st, ag, t);
-        double tn = __builtin_nan("");
-        if (w > 0.0) {
-            const double dlt = gd / w;
-            if (fabs(dlt) <= tol) return t - dlt;
-            tn = t - dlt;
-        }
-        if (!(tn > tl && tn < th)) tn = 0.5 * (tl + th);
-        const double step = fabs(tn - t);
-        t = tn;
-        if (step <= tol) break;
-    }
-    return t;
 }
 
 // Panel range [j_lo, j_hi] outside which the state's ln w lies below the skip
@@ -300,86 +256,260 @@ __device__ inline bool never_reaches(const CFG& c, const AdkState& st, double lb
     return true;
 }
 
-// Birth times of one atom (index `atom`, normalized position X, Y, Z) for
-// states k_first..k_first+K-1, written to out[0..K) in seconds.  The atom is
-// at rest, so its field depends on time only through the retarded time
-// d = tau - Z: the panels, nodes and crossings are all taken in d (the same
-// grid as in tau, shifted by Z), so the carrier phase is formed from d itself
-// and the birth time tau = d + Z is rounded once, at the output.
-template <int FIELD, class CFG>
-__device__ void ionize_atom(const CFG& c, uint64_t seed, uint32_t cfg, uint64_t atom, double X,
-                            double Y, double Z, int k_first, int K, double* __restrict__ out)
+// v of one lane (uniform index), the same in every lane.
+__device__ inline double lane_value(double v, int lane)
 {
-    for (int s = 0; s < K; ++s) out[s] = __builtin_inf();
-    const double dz = (c.window == 0) ? 0.0 : -Z;   // window start relative to arrival
+    const long long b = __builtin_bit_cast(long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, lane);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// I <- fma(h_l, acc_l, I) for l = 0..15 of each row of 16 lanes in turn (h_l,
+// acc_l the values of the row's lane l), in every lane of the row.  Two
+// instructions a term: a 64-bit row broadcast of h_l, and the multiply-add
+// that broadcasts acc_l as it reads it.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define RPDLA_ROW_TERM(L)                                                                      \
+    "v_mov_b64_dpp %1, %2 row_newbcast:" #L " row_mask:0xf bank_mask:0xf\n\t"                 \
+    "v_fmac_f64_dpp %0, %3, %1 row_newbcast:" #L " row_mask:0xf bank_mask:0xf\n\t"
+__device__ inline double row_sum(double I, double h, double acc)
+{
+    double t;
+    // two wait states between the write of a register and its read by another lane
+    asm("s_nop 1\n\t" RPDLA_ROW_TERM(0) RPDLA_ROW_TERM(1) RPDLA_ROW_TERM(2) RPDLA_ROW_TERM(3)
+        RPDLA_ROW_TERM(4) RPDLA_ROW_TERM(5) RPDLA_ROW_TERM(6) RPDLA_ROW_TERM(7)
+        RPDLA_ROW_TERM(8) RPDLA_ROW_TERM(9) RPDLA_ROW_TERM(10) RPDLA_ROW_TERM(11)
+        RPDLA_ROW_TERM(12) RPDLA_ROW_TERM(13) RPDLA_ROW_TERM(14) RPDLA_ROW_TERM(15)
+        : "+v"(I), "=&v"(t) : "v"(h), "v"(acc));
+    return I;
+}
+#undef RPDLA_ROW_TERM
+#else
+__device__ double row_sum(double I, double h, double acc);
+#endif
+
+// Constants of the rate evaluation: the configuration's, and those of the
+// functions, which stay in registers as in StepRegs (49 doubles; with the
+// compiler's own choice a node took 160 vector instructions, 22 of them moves
+// of coefficients, and its scalar loads; now 131, at 3 waves per SIMD).
+struct RateRegs {
+    double inv_T0n, a0, er_scale, ez_scale, gl_x[2], gl_w[2], lnw_zero;
+    fm::Coef k;
+    fm::LogCoef l;
+    template <class CFG>
+    __device__ inline explicit RateRegs(const CFG& c)   // nodes and weights are symmetric
+        : inv_T0n(c.inv_T0n), a0(c.a0), er_scale(c.er_scale), ez_scale(c.ez_scale),
+          gl_x{c.gl_x[2], c.gl_x[3]}, gl_w{c.gl_w[2], c.gl_w[3]}, lnw_zero(c.lnw_zero)
+    {
+        keep_in_vgpr(k.magic);
+        keep_in_sgpr(k.log2e); keep_in_sgpr(k.nln2_1); keep_in_sgpr(k.nln2_2);
+#pragma unroll
+        for (int i = 0; i < 10; ++i) if (i == 8) keep_in_vgpr(k.ex[i]); else keep_in_sgpr(k.ex[i]);
+        keep_in_sgpr(k.inv_pi); keep_in_sgpr(k.npi_1); keep_in_sgpr(k.npi_2);
+        keep_in_vgpr(k.npi_3);
+#pragma unroll
+        for (int i = 0; i < 7; ++i) keep_in_vgpr(k.sg[i]);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) if (i >= 4) keep_in_vgpr(k.kp[i]); else keep_in_sgpr(k.kp[i]);
+        keep_in_vgpr(k.ns2o8); keep_in_vgpr(k.s2);
+        keep_in_vgpr(k.c375);
+        keep_in_vgpr(l.rsqrt2);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) keep_in_vgpr(l.at[i]);
+    }
+};
+
+// Birth times of one atom (index `atom`, normalized position X, Y, Z) for
+// states k_first..k_first+K-1, written to out[0..K) in seconds; called by a
+// whole wave.  The atom is at rest, so its field depends on time only through
+// the retarded time d = tau - Z: the panels, nodes and crossings are all taken
+// in d (the same grid as in tau, shifted by Z), so the carrier phase is formed
+// from d itself and the birth time tau = d + Z is rounded once, at the output.
+//
+// The lanes take 64 consecutive panels of one state at a time and the panel
+// integrals are added up in the panels' order, so the sums are those of one
+// lane that takes panel after panel.  An atom has a few thousand panels and
+// about nine births (bound: FP64 issue; four nodes of 131 instructions a
+// panel, one in fourteen evaluated past a crossing; 200 of the 750
+// instructions for 64 panels go into the ordered sum).  With one lane per atom
+// a wave's lanes waited for one another (37 of 64 at work) and a small
+// ensemble left most of the chip idle behind one lane's serial chain: 1024
+// atoms x 10 states 19.6 -> 0.32 ms, 2e5 atoms x 1 state 11.8 -> 8.1 ms, 1e6
+// atoms x 10 states 147 -> 121 ms (and no sort of the atoms by work).
+template <int FIELD, class CFG>
+__device__ void ionize_atom(const CFG& c, const RateRegs& R, uint64_t seed, uint32_t cfg,
+                                 uint64_t atom, double X, double Y, double Z, int k_first, int K,
+                                 double* __restrict__ out)
+{
+    const int lane = __lane_id();
+    // lane s holds what belongs to state s: threshold, constants, panel window
+    // and whether its rate bound leaves it open from the window start
+    const double dz = (c.window == 0) ? 0.0 : -Z;
     const double d_s = dz - c.tb_n, d_e = dz + c.ta_n;
     const double h = c.hn;
-    // panels in the window (below 2^31: the host limits window / dt to 2e9)
     const int32_t M = (int32_t)ceil((d_e - d_s) / h);
     const double b2 = bound2_f64<FIELD>(c, X, Y, Z);
-    const double Zc = 0.0;  // the envelope peaks at d = 0 for the pulse models
+    const double lb2 = fm::log_pos_f64(b2);
+    double tbirth = __builtin_inf(), tgt_l = 0.0;
+    AdkState st_l{0.0, 0.0, 0.0, 0.0, 0.0};
+    int32_t jlo_l = 0, jhi_l = 0;
+    bool win_l = false, open_l = false;
+    if (lane < K) {
+        tgt_l = -log(uniform_j(seed, cfg, atom, k_first + lane + 2));
+        st_l = adk_state(c, k_first - 1 + lane);
+        win_l = state_window(c, st_l, b2, 0.0, d_s, h, M, jlo_l, jhi_l);
+        open_l = win_l && (FIELD == 11 || !never_reaches(c, st_l, lb2, d_s, d_e, h, M, jlo_l, jhi_l,
+                                                         d_s + (double)jlo_l * h, tgt_l));
+    }
+    const uint64_t open = __ballot(open_l), late = __ballot(tgt_l > 0.0);
 
     int s = 0;
-    double target = -log(uniform_j(seed, cfg, atom, k_first + 2));
-    // states with a zero threshold are born where they start
-    while (s < K && !(target > 0.0)) {
-        out[s] = (d_s + Z) * c.inv_omega;
+    while (s < K && !((late >> s) & 1)) {   // zero thresholds: born where they start
+        if (lane == s) tbirth = (d_s + Z) * c.inv_omega;
         ++s;
-        if (s < K) target = -log(uniform_j(seed, cfg, atom, k_first + s + 2));
     }
-    if (s >= K) return;
-    AdkState st = adk_state(c, k_first - 1 + s);
-    int32_t j_lo, j_hi;
-    if (!state_window(c, st, b2, Zc, d_s, h, M, j_lo, j_hi)) return;
-    // the envelope bound holds for the pulse models (not the static field)
-    if (FIELD != 11 &&
-        never_reaches(c, st, fm::log_pos_f64(b2), d_s, d_e, h, M, j_lo, j_hi, d_s + (double)j_lo * h, target))
-        return;
-    const AtomGeom ag = atom_geom<FIELD>(c, X, Y, Z);
-    double I = 0.0;
-    double tstart = d_s;
-    for (int32_t j = j_lo; j < M; ++j) {
-        if (j > j_hi) break;
-        const double a = d_s + (double)j * h;
-        const double b = (j == M - 1) ? d_e : d_s + (double)(j + 1) * h;
-        bool done = false;
-        while (true) {
+    if (s < K && ((open >> s) & 1)) {
+        const AtomGeom ag = atom_geom<FIELD>(c, X, Y, Z);
+        AdkState st{lane_value(st_l.c0, s), lane_value(st_l.c1h, s), lane_value(st_l.c2, s), 0.0,
+                    R.lnw_zero};
+        double target = lane_value(tgt_l, s);
+        double I = 0.0, tstart = d_s;
+        int32_t j = __builtin_amdgcn_readlane(jlo_l, s), j_hi = __builtin_amdgcn_readlane(jhi_l, s);
+        auto rate = [&](double d) {
+            return adk_rate_n(st, emag2_atom<FIELD>(c, R, ag, d, R.k), R.k, R.l);
+        };
+        while (j <= j_hi) {
+            // lane: panel j + lane, its Gauss sum over [lo, b]
+            const int32_t jl = j + lane;
+            const double a = fma((double)jl, h, d_s);
+            const double b = (jl == M - 1) ? d_e : fma((double)(jl + 1), h, d_s);
             const double lo = (tstart > a) ? tstart : a;
-            const double seg = gl4_integral<FIELD>(c, st, ag, lo, b);
-            if (I + seg < target) { I += seg; break; }
-            const double t = solve_crossing<FIELD>(c, st, ag, lo, b, target - I, seg);
-            out[s] = (t + Z) * c.inv_omega;
-            ++s;
-            if (s >= K) { done = true; break; }
-            target = -log(uniform_j(seed, cfg, atom, k_first + s + 2));
-            I = 0.0;
-            tstart = t;
-            st = adk_state(c, k_first - 1 + s);
-            int32_t nlo, nhi;
-            if (!state_window(c, st, b2, Zc, d_s, h, M, nlo, nhi)) {
-                if (!(target > 0.0)) { j_hi = M - 1; continue; }
-                done = true;
+            const double hw = 0.5 * (b - lo), m = 0.5 * (lo + b);
+            double acc = 0.0;
+            if (jl <= j_hi) {
+                acc = fma(R.gl_w[1], rate(fma(-R.gl_x[1], hw, m)), acc);
+                acc = fma(R.gl_w[0], rate(fma(-R.gl_x[0], hw, m)), acc);
+                acc = fma(R.gl_w[0], rate(fma(R.gl_x[0], hw, m)), acc);
+                acc = fma(R.gl_w[1], rate(fma(R.gl_x[1], hw, m)), acc);
+            }
+            // add them up in order, row by row of 16 lanes; a row whose every
+            // term is below a quarter of I's last place leaves I as it is
+            const uint64_t counts = __ballot(!(hw * acc <= I * 0x1.0p-56));
+            int cross = -1;
+#pragma unroll 1
+            for (int r = 0; r < 4; ++r) {
+                if (((counts >> (16 * r)) & 0xffffull) == 0) continue;
+                const double In = lane_value(row_sum(I, hw, acc), 16 * r);
+                if (In < target) { I = In; continue; }
+                // the crossing lies in this row: panel by panel
+#pragma unroll 1
+                for (cross = 16 * r; cross < 16 * r + 15; ++cross) {
+                    const double Ix = fma(lane_value(hw, cross), lane_value(acc, cross), I);
+                    if (!(Ix < target)) break;
+                    I = Ix;
+                }
                 break;
             }
-            j_hi = (target > 0.0) ? nhi : M - 1;
-            if (FIELD != 11 && target > 0.0) {
-                const int32_t j0 = nlo > j ? nlo : j;
-                const double d0 = nlo > j ? d_s + (double)nlo * h : t;
-                if (never_reaches(c, st, fm::log_pos_f64(b2), d_s, d_e, h, M, j0, j_hi, d0, target)) {
-                    done = true;
-                    break;
+            if (cross < 0) { j += 64; continue; }
+            // bracketed Newton for the crossing, as solve_crossing: lanes 0..3
+            // evaluate the Gauss nodes of [lo, t], lane 4 the rate at t
+            const double clo = lane_value(lo, cross), chi = lane_value(b, cross);
+            const double chw = lane_value(hw, cross), cacc = lane_value(acc, cross);
+            const double need = target - I;
+            double t = clo;
+            if (need > 0.0) {
+                double tl = clo, th = chi;
+                t = fma(chi - clo, need / (chw * cacc), clo);
+                if (!(t > tl && t < th)) t = 0.5 * (tl + th);
+                const double xn = (lane == 0) ? -R.gl_x[1] : (lane == 1) ? -R.gl_x[0]
+                                : (lane == 2) ? R.gl_x[0] : R.gl_x[1];
+#pragma unroll 1
+                for (int it = 0; it < 100; ++it) {
+                    const double hh = 0.5 * (t - clo), mm = 0.5 * (clo + t);
+                    const double r = rate(lane < 4 ? fma(xn, hh, mm) : t);
+                    double g = fma(R.gl_w[1], lane_value(r, 0), 0.0);
+                    g = fma(R.gl_w[0], lane_value(r, 1), g);
+                    g = fma(R.gl_w[0], lane_value(r, 2), g);
+                    g = fma(R.gl_w[1], lane_value(r, 3), g);
+                    const double gd = fma(hh, g, -need);
+                    if (gd == 0.0) break;
+                    if (gd > 0.0) th = t; else tl = t;
+                    const double tol = ldexp(fmax(fabs(t), kTwoPi), -40);
+                    const double w = lane_value(r, 4);
+                    double tn = __builtin_nan("");
+                    if (w > 0.0) {
+                        const double dlt = gd / w;
+                        if (fabs(dlt) <= tol) { t = t - dlt; break; }
+                        tn = t - dlt;
+                    }
+                    if (!(tn > tl && tn < th)) tn = 0.5 * (tl + th);
+                    const double step = fabs(tn - t);
+                    t = tn;
+                    if (step <= tol) break;
                 }
             }
-            if (target > 0.0 && nlo > j) {
-                // before its window the new state's ln w stays below the
-                // skip level at every node, the same bound that starts the
-                // first state at its window: resume at the window's first panel
-                j = nlo - 1;
-                break;
+            if (lane == s) tbirth = (t + Z) * c.inv_omega;
+            j += cross;
+            ++s;
+            // states with a zero threshold are born where the previous one is
+            while (s < K && !((late >> s) & 1)) {
+                if (lane == s) tbirth = (t + Z) * c.inv_omega;
+                ++s;
+            }
+            if (s >= K || !((open >> s) & 1)) break;
+            st.c0 = lane_value(st_l.c0, s);
+            st.c1h = lane_value(st_l.c1h, s);
+            st.c2 = lane_value(st_l.c2, s);
+            target = lane_value(tgt_l, s);
+            I = 0.0;
+            tstart = t;
+            const int32_t nlo = __builtin_amdgcn_readlane(jlo_l, s);
+            j_hi = __builtin_amdgcn_readlane(jhi_l, s);
+            const double d0 = nlo > j ? d_s + (double)nlo * h : t;
+            if (nlo > j) j = nlo;
+            if (FIELD != 11 && j <= j_hi) {
+                // the rate bound over what is left of the window, a group of
+                // panels per lane
+                const double la2pk = (st.c1h > 0.0) ? 2.0 * fm::log_pos_f64(st.c2 / (2.0 * st.c1h))
+                                                    : __builtin_inf();
+                const int32_t groups = (j_hi - j) / kBoundGroup + 1;
+                double sum = 0.0;
+                for (int32_t g = lane; g < groups; g += 64) {
+                    double da, db;
+                    bound_group(g, groups, j, j_hi, M, d_s, d_e, h, d0, da, db);
+                    sum += bound_group_rate(c, st, lb2, la2pk, da, db);
+                }
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+                if (2.0 * sum < target) break;
             }
         }
-        if (done) break;
     }
+    if (lane < K) out[lane] = tbirth;
+}
+
+template <int FIELD>
+struct IonizeWaves { static constexpr int value = (FIELD > 20) ? 2 : 3; };
+
+__device__ inline int64_t wave_index()
+{
+    return (int64_t)blockIdx.x * (blockDim.x >> 6) +
+           __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+}
+
+template <int FIELD>
+__global__ void __launch_bounds__(256, IonizeWaves<FIELD>::value) ionize_kernel(
+    DevCfg c, uint64_t seed, uint32_t cfg, uint64_t first_atom, int64_t n,
+    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
+    int k_first, int k_last, double* __restrict__ t_birth)
+{
+    const int64_t i = wave_index();
+    if (i >= n) return;
+    const int K = k_last - k_first + 1;
+    const RateRegs R(c);
+    ionize_atom<FIELD>(c, R, seed, cfg, first_atom + (uint64_t)i, x[i] * c.k, y[i] * c.k,
+                       z[i] * c.k, k_first, K, t_birth + i * K);
 }
 
 // Wave-cooperative refill: lanes with need == true get consecutive queue
@@ -395,65 +525,6 @@ __device__ inline int64_t queue_take(unsigned long long* queue, bool need)
     base = __shfl(base, leader);
     const int rank = __popcll(m & ((1ull << lane) - 1ull));
     return need ? (int64_t)(base + (unsigned long long)rank) : -1;
-}
-
-// Lane i ionizes atom order[i] (atom i without an order).  An order that
-// groups atoms of similar work in the same wave keeps the lanes of a wave
-// busy for the same number of panels; the results do not depend on it.
-template <int FIELD>
-__global__ void __launch_bounds__(256, 3) ionize_kernel(
-    DevCfg c, uint64_t seed, uint32_t cfg, uint64_t first_atom, int64_t n,
-    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
-    int k_first, int k_last, double* __restrict__ t_birth, const uint32_t* __restrict__ order)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int64_t a = order ? (int64_t)order[i] : i;
-    const int K = k_last - k_first + 1;
-    ionize_atom<FIELD>(c, seed, cfg, first_atom + (uint64_t)a, x[a] * c.k, y[a] * c.k,
-                       z[a] * c.k, k_first, K, t_birth + a * K);
-}
-
-// Work key of each atom for that order: first the number of its states that
-// the rate bound (never_reaches) does not rule out from the window start --
-// those the panel loop may integrate; the thresholds are random, so atoms of
-// one field strength differ in it -- then the bound of its peak |a|^2 (the
-// states' windows, and so the panels an atom integrates, grow with it), as
-// the top bits of a non-negative float, which order like the value.
-template <int FIELD>
-__global__ void __launch_bounds__(256) ionize_key_kernel(DevCfg c, uint64_t seed, uint32_t cfg,
-                                                         uint64_t first_atom, int64_t n,
-                                                         const double* __restrict__ x,
-                                                         const double* __restrict__ y,
-                                                         const double* __restrict__ z, int k_first,
-                                                         int k_last, uint32_t* __restrict__ key,
-                                                         uint32_t* __restrict__ idx)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double X = x[i] * c.k, Y = y[i] * c.k, Z = z[i] * c.k;
-    const double b2 = bound2_f64<FIELD>(c, X, Y, Z);
-    uint32_t open = 0;
-    if (FIELD != 11) {
-        const double dz = (c.window == 0) ? 0.0 : -Z;
-        const double d_s = dz - c.tb_n, d_e = dz + c.ta_n;
-        const double h = c.hn;
-        const int32_t M = (int32_t)ceil((d_e - d_s) / h);
-        const double lb2 = fm::log_pos_f64(b2);
-        for (int k = k_first; k <= k_last; ++k) {
-            const double target = -log(uniform_j(seed, cfg, first_atom + (uint64_t)i, k + 2));
-            if (!(target > 0.0)) { ++open; continue; }
-            const AdkState st = adk_state(c, k - 1);
-            int32_t j_lo, j_hi;
-            if (!state_window(c, st, b2, 0.0, d_s, h, M, j_lo, j_hi)) break;
-            if (never_reaches(c, st, lb2, d_s, d_e, h, M, j_lo, j_hi, d_s + (double)j_lo * h, target))
-                break;
-            ++open;
-        }
-    }
-    const float b2f = (float)b2;
-    key[i] = (open << 27) | (__float_as_uint(b2f > 0.0f ? b2f : 0.0f) >> 4);
-    idx[i] = (uint32_t)i;
 }
 
 // ---------------------------------------------------------------------------
