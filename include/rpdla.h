@@ -205,12 +205,17 @@ rpdla_status rpdla_birth_phase(const rpdla_laser* L, int64_t n_slots, const doub
  * reduced to one turn before the float sine / cosine); momentum accumulated
  * in float with Kahan compensation.
  * EINVAL: bad laser, n_slots < 0, slots_per_atom < 1, null pointers with
- * n_slots > 0.  Uses a small stream-ordered device allocation (1 KiB) for its
- * work queue (RPDLA_EHIP if that fails): the slots are split into eight
- * contiguous parts with a counter each, and a wave draws from the part of the
- * XCD it runs on (the hardware XCC_ID register) before it moves on to the
- * others, so the slots of one part pass through one XCD's L2; results do not
- * depend on it.
+ * n_slots > 0.
+ * Up to 64 slots per SIMD (65536 on 256 CUs) lanes draw their slots from a
+ * work queue, which needs a small stream-ordered device allocation (1 KiB;
+ * RPDLA_EHIP if that fails): the slots are split into eight contiguous parts
+ * with a counter each, and a wave draws from the part of the XCD it runs on
+ * (the hardware XCC_ID register) before it moves on to the others.  Above that
+ * the born slots are pushed in the order of their step counts, 64 neighbours
+ * to a wave, the last waves' worth in time slices (some 35 launches), with
+ * stream-ordered scratch of 4 bytes a slot and up to 70 MB; when that cannot
+ * be allocated, or from 2^32 - 1 slots on, the queue is used.  Results do not
+ * depend on either.
  * ------------------------------------------------------------------------ */
 rpdla_status rpdla_push(const rpdla_laser* L, int32_t precision, int64_t n_slots,
                         const double* t_birth, const double* x0, const double* y0,
@@ -253,7 +258,7 @@ rpdla_status rpdla_push_noalloc(const rpdla_laser* L, int32_t precision, int64_t
  * is Rc = alpha a0 chi, a0 = e A / (m c omega).
  * EINVAL: bad laser, radiation_reaction not 0 or 1, n_slots < 0,
  * slots_per_atom < 1, null pointers (other than chi_max) with n_slots > 0.
- * Uses a small stream-ordered device allocation for its work queue.
+ * Device scratch as rpdla_push.
  * ------------------------------------------------------------------------ */
 rpdla_status rpdla_push_rr(const rpdla_laser* L, int32_t radiation_reaction, int64_t n_slots,
                            const double* t_birth, const double* x0, const double* y0,

@@ -248,6 +248,65 @@ rpdla_status launch_ionize(const DevCfg& c, uint64_t seed, uint32_t cfg, uint64_
     return RPDLA_OK;
 }
 
+// Scratch of one ordered push, stream-ordered: the plan, the order and the
+// electrons between slices.  An ordered push needs more electrons than one
+// wave on every SIMD holds (fewer are all under way at once, and the time is one
+// electron's) and 32-bit slot numbers.
+template <int FIELD, class ELEC>
+rpdla_status launch_ordered(const DevCfg& c, const rpdla::PushIO& io, Shape sh, hipStream_t st,
+                            bool* done)
+{
+    *done = false;
+    int dev = 0, cus = 0, per_cu = 0;
+    auto* kern = rpdla::push_group_kernel<FIELD, ELEC>;
+    RPDLA_HIP(hipGetDevice(&dev));
+    RPDLA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int simds = 4 * cus;
+    if (io.n_slots <= 64ll * simds || io.n_slots >= (int64_t)UINT32_MAX) return RPDLA_OK;
+    RPDLA_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, sh.block, 0));
+    const int waves_per_block = sh.block / 64;
+    const int max_waves = per_cu * waves_per_block / 4;
+    if (max_waves < 1) return RPDLA_OK;
+    // the rest is fewer than 2 W groups
+    const int64_t groups = cdiv(io.n_slots, 64);
+    const int64_t rest = std::min<int64_t>(groups, 2ll * simds * max_waves);
+    const size_t order = align256(sizeof(rpdla::PushPlan));
+    const size_t state = order + align256((size_t)io.n_slots * sizeof(uint32_t));
+    const size_t total = state + (size_t)rest * 64 * sizeof(ELEC);
+    char* base = nullptr;
+    if (hipMallocAsync((void**)&base, total, st) != hipSuccess) {
+        (void)hipGetLastError();
+        return RPDLA_OK;                       // no room for the order: the queue needs none
+    }
+    rpdla::GroupArgs ga;
+    ga.c = c;
+    ga.io = io;
+    ga.P = rpdla::PlanArgs{(rpdla::PushPlan*)base, (uint32_t*)(base + order),
+                           (uint64_t*)(base + state), (uint32_t)simds, (uint32_t)max_waves,
+                           ceil((c.ta_n + c.tb_n) / c.hn) + 2.0};
+    constexpr int64_t words = sizeof(rpdla::PushPlan) / 8;
+    static_assert(sizeof(rpdla::PushPlan) % 8 == 0, "cleared by words");
+    hipLaunchKernelGGL(rpdla::zero_u64_kernel, dim3((unsigned)cdiv(words, 256)), dim3(256), 0, st,
+                       (unsigned long long*)base, words);
+    const unsigned blocks = (unsigned)cdiv(io.n_slots, rpdla::kPlanChunk);
+    hipLaunchKernelGGL(rpdla::plan_count_kernel<rpdla::HasExtra<ELEC>::value>, dim3(blocks),
+                       dim3(rpdla::kPlanBlock), 0, st, c, io, ga.P);
+    hipLaunchKernelGGL(rpdla::plan_scan_kernel, dim3(1), dim3(rpdla::kPlanBlock), 0, st, ga.P);
+    hipLaunchKernelGGL(rpdla::plan_order_kernel, dim3(blocks), dim3(rpdla::kPlanBlock), 0, st, c,
+                       io, ga.P);
+    const unsigned grid = (unsigned)cdiv((int64_t)simds * max_waves, waves_per_block);
+    for (int l = groups >= 2ll * simds ? -1 : 0; l < rpdla::kPlanLaunches; ++l) {
+        ga.slice = l;
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(sh.block), 0, st, ga);
+    }
+    const hipError_t e = hipGetLastError();
+    const hipError_t fe = hipFreeAsync(base, st);
+    if (e != hipSuccess) return fail(RPDLA_EHIP, "push: %s", hipGetErrorString(e));
+    if (fe != hipSuccess) return fail(RPDLA_EHIP, "hipFreeAsync: %s", hipGetErrorString(fe));
+    *done = true;
+    return RPDLA_OK;
+}
+
 template <int FIELD>
 rpdla_status launch_push(const DevCfg& c, int prec, const rpdla::PushIO& io, hipStream_t st)
 {
@@ -312,6 +371,28 @@ rpdla_status check_push_args(const rpdla_laser* L, int32_t precision, int64_t n_
         return fail(RPDLA_EINVAL, "null pointer");
     if (n_slots > kMaxPushSlots) return fail(RPDLA_ERANGE, "n_slots too large");
     return RPDLA_OK;
+}
+
+// The ordered push of slots io in the form asked for; *done false where it does
+// not apply (few slots, no room for its scratch).
+template <int FIELD>
+rpdla_status ordered_push(const DevCfg& c, int prec, const rpdla::PushIO& io, hipStream_t st,
+                          bool* done)
+{
+    const Shape sh = get_shape(kKindPush, FIELD, prec);
+    if (prec == RPDLA_FP64) return launch_ordered<FIELD, rpdla::ElecF64>(c, io, sh, st, done);
+    if constexpr (FIELD < 20) return launch_ordered<FIELD, rpdla::ElecMixed>(c, io, sh, st, done);
+    *done = false;
+    return RPDLA_OK;                           // the queue reports what is not supported
+}
+
+template <int FIELD>
+rpdla_status ordered_push_rr(const DevCfg& c, bool rr, const rpdla::PushIO& io, hipStream_t st,
+                             bool* done)
+{
+    const Shape sh = get_shape(kKindPush, FIELD, RPDLA_FP64);
+    return rr ? launch_ordered<FIELD, rpdla::ElecRR<true>>(c, io, sh, st, done)
+              : launch_ordered<FIELD, rpdla::ElecRR<false>>(c, io, sh, st, done);
 }
 
 // Clear the work counters q[kQueueWords] (a fill kernel, no memset node) and
@@ -519,6 +600,23 @@ rpdla_status rpdla_push(const rpdla_laser* L, int32_t precision, int64_t n_slots
                                       ux, uy, uz, xf, yf, zf);
     if (st != RPDLA_OK || n_slots == 0) return st;
     hipStream_t s = (hipStream_t)stream;
+    {
+        const DevCfg c = make_cfg(L);
+        const rpdla::PushIO io{t_birth, x0, y0, z0, slots_per_atom, n_slots, ux, uy, uz, xf, yf,
+                               zf, nullptr};
+        bool done = false;
+        switch (L->field) {
+        case 1: st = ordered_push<1>(c, precision, io, s, &done); break;
+        case 3: st = ordered_push<3>(c, precision, io, s, &done); break;
+        case 5: st = ordered_push<5>(c, precision, io, s, &done); break;
+        case 10: st = ordered_push<10>(c, precision, io, s, &done); break;
+        case 21: st = ordered_push<21>(c, precision, io, s, &done); break;
+        case 23: st = ordered_push<23>(c, precision, io, s, &done); break;
+        case 25: st = ordered_push<25>(c, precision, io, s, &done); break;
+        default: st = ordered_push<11>(c, precision, io, s, &done); break;
+        }
+        if (st != RPDLA_OK || done) return st;
+    }
     unsigned long long* q = nullptr;
     RPDLA_HIP(hipMallocAsync((void**)&q, rpdla::kQueueWords * sizeof(unsigned long long), s));
     st = enqueue_push(L, precision, n_slots, t_birth, x0, y0, z0, slots_per_atom, ux, uy, uz, xf,
@@ -562,13 +660,26 @@ rpdla_status rpdla_push_rr(const rpdla_laser* L, int32_t radiation_reaction, int
     if (n_slots > ((int64_t)1 << 40)) return fail(RPDLA_ERANGE, "n_slots too large");
     const DevCfg c = make_cfg(L);
     hipStream_t s = (hipStream_t)stream;
+    rpdla::PushIO io{t_birth, x0, y0, z0, slots_per_atom, n_slots, ux, uy, uz, xf, yf, zf, nullptr,
+                     chi_max};
+    const bool rr = radiation_reaction == 1;
+    bool done = false;
+    switch (L->field) {
+    case 1: st = ordered_push_rr<1>(c, rr, io, s, &done); break;
+    case 3: st = ordered_push_rr<3>(c, rr, io, s, &done); break;
+    case 5: st = ordered_push_rr<5>(c, rr, io, s, &done); break;
+    case 10: st = ordered_push_rr<10>(c, rr, io, s, &done); break;
+    case 21: st = ordered_push_rr<21>(c, rr, io, s, &done); break;
+    case 23: st = ordered_push_rr<23>(c, rr, io, s, &done); break;
+    case 25: st = ordered_push_rr<25>(c, rr, io, s, &done); break;
+    default: st = ordered_push_rr<11>(c, rr, io, s, &done); break;
+    }
+    if (st != RPDLA_OK || done) return st;
     unsigned long long* q = nullptr;
     RPDLA_HIP(hipMallocAsync((void**)&q, rpdla::kQueueWords * sizeof(unsigned long long), s));
     hipLaunchKernelGGL(rpdla::zero_u64_kernel, dim3(1), dim3(rpdla::kQueueWords), 0, s, q,
                        (int64_t)rpdla::kQueueWords);
-    rpdla::PushIO io{t_birth, x0, y0, z0, slots_per_atom, n_slots, ux, uy, uz, xf, yf, zf, q,
-                     chi_max};
-    const bool rr = radiation_reaction == 1;
+    io.queue = q;
     switch (L->field) {
     case 1: st = launch_push_rr<1>(c, rr, io, s); break;
     case 3: st = launch_push_rr<3>(c, rr, io, s); break;
