@@ -350,12 +350,11 @@ rpdla_status rpdla_histogram2d(int64_t n, const double* a, const double* b, cons
  * with atoms_per_cfg atoms sampled uniformly in r < r_factor * w0,
  * |z| < z_r, RNG key (seed, cfg_base + c) for configuration c, charge states
  * k_first..k_last.  Atoms are processed in chunks of atoms_per_chunk per
- * configuration; each chunk runs sample -> ionize -> push -> histogram, the
- * push as ONE persistent launch over every configuration's electrons: every
- * configuration has its own work counter, each wave serves one configuration
- * at a time (its constants read with scalar loads from the configuration
- * table) and moves to another with work left when its own runs dry; lanes are
- * refilled as their electron finishes.
+ * configuration; each chunk runs sample -> ionize -> push -> histogram.  The
+ * push takes every configuration's born slots in the order of their step
+ * counts, in groups of 64 of one configuration (its constants read with scalar
+ * loads), and deals the groups to the waves in whole rounds and, for the last
+ * ones, in time slices; some 40 launches a chunk.
  * On a non-null stream that is not being captured, the chunk's launch
  * sequence is captured once in a hipGraph (the chunk index advances in device
  * memory) and replayed per chunk, one chunk included; graphs are cached per
@@ -369,7 +368,10 @@ rpdla_status rpdla_histogram2d(int64_t n, const double* a, const double* b, cons
  * workspace: device memory of at least
  * rpdla_batched_workspace_bytes(n_cfg, atoms_per_chunk, k_first, k_last)
  * bytes, 256-byte aligned, owned by the caller, not touched by other work
- * until the stream reaches the end of this call.
+ * until the stream reaches the end of this call.  A smaller one that holds the
+ * chunk's arrays (through the end of uz, see the layout below) is accepted: the
+ * push then is one persistent launch with a work counter per configuration,
+ * with the same results.
  * EINVAL on bad configurations or sizes; RPDLA_ENOMEM when ws_bytes is too
  * small; RPDLA_EUNSUPPORTED for n_cfg > 64.
  * ------------------------------------------------------------------------ */

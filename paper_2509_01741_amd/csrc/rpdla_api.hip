@@ -798,8 +798,15 @@ namespace {
 
 
 struct WsLayout {
-    size_t cfg, geo, ctl, x, y, z, tb, ux, uy, uz, total;
+    size_t cfg, geo, ctl, x, y, z, tb, ux, uy, uz;
+    size_t queued;                       // bytes a chunk needs with the queue push
+    size_t plan, order, groups, state;   // and what its ordered push needs
+    size_t total;
 };
+
+// Waves of an ordered batched push: 1024 SIMDs, 7 waves at most.  The size of
+// its workspace does not depend on the device it will run on.
+constexpr int64_t kBatchWaves = 1024 * 7;
 
 WsLayout ws_layout(int n_cfg, int64_t apc, int K)
 {
@@ -816,6 +823,13 @@ WsLayout ws_layout(int n_cfg, int64_t apc, int K)
     w.ux = off; off += align256(na * (size_t)K * sizeof(double));
     w.uy = off; off += align256(na * (size_t)K * sizeof(double));
     w.uz = off; off += align256(na * (size_t)K * sizeof(double));
+    w.queued = off;
+    const size_t slots = na * (size_t)K, groups = slots / 64 + (size_t)n_cfg;
+    w.plan = off; off += align256(sizeof(rpdla::BatchPlan));
+    w.order = off; off += align256(slots * sizeof(uint32_t));
+    w.groups = off; off += align256(groups * sizeof(rpdla::BatchGroup));
+    w.state = off;
+    off += align256(std::min<size_t>(groups, 2 * kBatchWaves) * 64 * sizeof(rpdla::ElecF64));
     w.total = off;
     return w;
 }
@@ -828,7 +842,8 @@ std::vector<std::pair<std::string, hipGraphExec_t>> g_graphs;  // small cache, p
 constexpr size_t kMaxGraphs = 32;
 
 template <int FIELD, class ELEC>
-rpdla_status run_batched_impl(const rpdla::BatchArgs& A, int64_t n_chunks, hipStream_t s)
+rpdla_status run_batched_impl(const rpdla::BatchArgs& A, rpdla::BatchPlanArgs P, int64_t n_chunks,
+                              hipStream_t s)
 {
     const size_t lds_p = (size_t)A.n_cfg * sizeof(unsigned long long);
     auto* kpush = rpdla::batch_push_kernel<FIELD, ELEC>;
@@ -841,13 +856,48 @@ rpdla_status run_batched_impl(const rpdla::BatchArgs& A, int64_t n_chunks, hipSt
     int64_t grid_h = cdiv(slots, 256);
     if (grid_h > 8192) grid_h = 8192;
 
+    // the ordered push, where the workspace has room for it
+    auto* kgroup = rpdla::batch_group_kernel<FIELD, ELEC>;
+    unsigned grid_g = 0;
+    if (P.plan) {
+        int dev = 0, cus = 0, per_cu = 0;
+        RPDLA_HIP(hipGetDevice(&dev));
+        RPDLA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        RPDLA_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kgroup, sh.block, 0));
+        const int wpb = sh.block / 64;
+        P.simds = (uint32_t)(4 * cus);
+        P.max_waves = (uint32_t)std::min<int64_t>(per_cu * wpb / 4, kBatchWaves / (4 * cus));
+        if (P.max_waves < 1) P.plan = nullptr;
+        else grid_g = (unsigned)cdiv((int64_t)P.simds * P.max_waves, wpb);
+    }
+    const int64_t per_cfg = A.apc * A.K;
+    const dim3 grid_plan((unsigned)cdiv(per_cfg, rpdla::kPlanChunk), (unsigned)A.n_cfg);
+    constexpr int64_t plan_words = sizeof(rpdla::BatchPlan) / 8;
+    static_assert(sizeof(rpdla::BatchPlan) % 8 == 0 && sizeof(ELEC) <= sizeof(rpdla::ElecF64),
+                  "cleared by words; the workspace is sized for the larger electron");
+    auto enqueue_ordered = [&](hipStream_t st) {
+        hipLaunchKernelGGL(rpdla::zero_u64_kernel, dim3((unsigned)cdiv(plan_words, 256)), dim3(256),
+                           0, st, (unsigned long long*)P.plan, plan_words);
+        hipLaunchKernelGGL(rpdla::batch_plan_kernel<false>, grid_plan, dim3(rpdla::kPlanBlock), 0,
+                           st, A, A.cfgs, P);
+        hipLaunchKernelGGL(rpdla::batch_plan_scan_kernel, dim3(1), dim3(rpdla::kPlanBlock), 0, st,
+                           A.n_cfg, P);
+        hipLaunchKernelGGL(rpdla::batch_plan_kernel<true>, grid_plan, dim3(rpdla::kPlanBlock), 0,
+                           st, A, A.cfgs, P);
+        const int64_t groups = slots / 64 + A.n_cfg;
+        const int last = groups <= (int64_t)P.simds ? 1 : rpdla::kPlanLaunches;
+        for (int l = groups >= 2ll * P.simds ? -1 : 0; l < last; ++l)
+            hipLaunchKernelGGL(kgroup, dim3(grid_g), dim3(sh.block), 0, st, A, A.cfgs, P, l);
+    };
+
     auto enqueue_chunk = [&](hipStream_t st) -> rpdla_status {
         hipLaunchKernelGGL(rpdla::batch_zero_queue_kernel, dim3(1), dim3(64), 0, st, A.ctl);
         hipLaunchKernelGGL(rpdla::batch_sample_kernel, dim3(grid_a), dim3(256), 0, st, A);
         for (int64_t i = 0; i < atoms; i += kIonizeAtoms)
             hipLaunchKernelGGL(kion, dim3((unsigned)cdiv(std::min(atoms - i, kIonizeAtoms), 4)),
                                dim3(256), 0, st, A, A.cfgs, i);
-        hipLaunchKernelGGL(kpush, dim3((unsigned)grid_p), dim3(sh.block), lds_p, st, A, A.cfgs);
+        if (P.plan) enqueue_ordered(st);
+        else hipLaunchKernelGGL(kpush, dim3((unsigned)grid_p), dim3(sh.block), lds_p, st, A, A.cfgs);
         hipLaunchKernelGGL(rpdla::batch_hist_kernel, dim3((unsigned)grid_h), dim3(256), 0, st, A);
         hipLaunchKernelGGL(rpdla::batch_advance_kernel, dim3(1), dim3(64), 0, st, A.ctl);
         RPDLA_HIP(hipGetLastError());
@@ -871,6 +921,7 @@ rpdla_status run_batched_impl(const rpdla::BatchArgs& A, int64_t n_chunks, hipSt
     key.append(reinterpret_cast<const char*>(&s), sizeof s);
     key.append(reinterpret_cast<const char*>(&grid_p), sizeof grid_p);
     key.append(reinterpret_cast<const char*>(&sh), sizeof sh);
+    key.append(reinterpret_cast<const char*>(&P), sizeof P);
     hipGraphExec_t exec = nullptr;
     bool full = false;
     {
@@ -990,7 +1041,7 @@ rpdla_status rpdla_run_batched_range(const rpdla_laser* cfgs, int32_t n_cfg, uin
     if ((double)n_cfg * (double)atoms_per_chunk * K > 1.0e12)
         return fail(RPDLA_ERANGE, "chunk too large");
     const WsLayout w = ws_layout(n_cfg, atoms_per_chunk, K);
-    if (ws_bytes < w.total)
+    if (ws_bytes < w.queued)
         return fail(RPDLA_ENOMEM, "workspace %zu bytes < required %zu", ws_bytes, w.total);
     hipStream_t s = (hipStream_t)stream;
     char* base = (char*)workspace;
@@ -1028,21 +1079,33 @@ rpdla_status rpdla_run_batched_range(const rpdla_laser* cfgs, int32_t n_cfg, uin
                        (unsigned long long)first_chunk);
     RPDLA_HIP(hipGetLastError());
     if (n_chunks == 0) return RPDLA_OK;
+    // the ordered push needs the whole workspace and 32-bit places; a smaller
+    // workspace that holds the chunk runs the queue push
+    rpdla::BatchPlanArgs P;
+    memset(&P, 0, sizeof P);
+    if (ws_bytes >= w.total && (int64_t)n_cfg * atoms_per_chunk * K < (int64_t)UINT32_MAX) {
+        P.plan = (rpdla::BatchPlan*)(base + w.plan);
+        P.order = (uint32_t*)(base + w.order);
+        P.groups = (rpdla::BatchGroup*)(base + w.groups);
+        P.state = (uint64_t*)(base + w.state);
+        for (int c = 0; c < n_cfg; ++c)
+            P.n_max = std::max(P.n_max, ceil((cfgs[c].t_before + cfgs[c].t_after) / cfgs[c].dt) + 2.0);
+    }
     const bool mixed = precision == RPDLA_MIXED;
     switch (cfgs[0].field) {
-    case 1: return mixed ? run_batched_impl<1, rpdla::ElecMixed>(A, n_chunks, s)
-                         : run_batched_impl<1, rpdla::ElecF64>(A, n_chunks, s);
-    case 3: return mixed ? run_batched_impl<3, rpdla::ElecMixed>(A, n_chunks, s)
-                         : run_batched_impl<3, rpdla::ElecF64>(A, n_chunks, s);
-    case 5: return mixed ? run_batched_impl<5, rpdla::ElecMixed>(A, n_chunks, s)
-                         : run_batched_impl<5, rpdla::ElecF64>(A, n_chunks, s);
-    case 10: return mixed ? run_batched_impl<10, rpdla::ElecMixed>(A, n_chunks, s)
-                          : run_batched_impl<10, rpdla::ElecF64>(A, n_chunks, s);
-    case 21: return run_batched_impl<21, rpdla::ElecF64>(A, n_chunks, s);
-    case 23: return run_batched_impl<23, rpdla::ElecF64>(A, n_chunks, s);
-    case 25: return run_batched_impl<25, rpdla::ElecF64>(A, n_chunks, s);
-    default: return mixed ? run_batched_impl<11, rpdla::ElecMixed>(A, n_chunks, s)
-                          : run_batched_impl<11, rpdla::ElecF64>(A, n_chunks, s);
+    case 1: return mixed ? run_batched_impl<1, rpdla::ElecMixed>(A, P, n_chunks, s)
+                         : run_batched_impl<1, rpdla::ElecF64>(A, P, n_chunks, s);
+    case 3: return mixed ? run_batched_impl<3, rpdla::ElecMixed>(A, P, n_chunks, s)
+                         : run_batched_impl<3, rpdla::ElecF64>(A, P, n_chunks, s);
+    case 5: return mixed ? run_batched_impl<5, rpdla::ElecMixed>(A, P, n_chunks, s)
+                         : run_batched_impl<5, rpdla::ElecF64>(A, P, n_chunks, s);
+    case 10: return mixed ? run_batched_impl<10, rpdla::ElecMixed>(A, P, n_chunks, s)
+                          : run_batched_impl<10, rpdla::ElecF64>(A, P, n_chunks, s);
+    case 21: return run_batched_impl<21, rpdla::ElecF64>(A, P, n_chunks, s);
+    case 23: return run_batched_impl<23, rpdla::ElecF64>(A, P, n_chunks, s);
+    case 25: return run_batched_impl<25, rpdla::ElecF64>(A, P, n_chunks, s);
+    default: return mixed ? run_batched_impl<11, rpdla::ElecMixed>(A, P, n_chunks, s)
+                          : run_batched_impl<11, rpdla::ElecF64>(A, P, n_chunks, s);
     }
 }
 

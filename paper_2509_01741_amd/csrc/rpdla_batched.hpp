@@ -1,10 +1,9 @@
 // rpdla_batched.hpp -- parameter sweeps in one pass per atom chunk: sampling
-// and ionization over every configuration's atoms, then ONE persistent push
-// launch over every configuration's electrons (per-configuration work
-// counters, each wave serving one configuration at a time from an LDS table,
-// lanes refilled as their electron finishes, so uneven step counts across
-// wavelengths and powers balance themselves), then one binning pass over the
-// chunk's final momenta into per-configuration energy-angle histograms.
+// and ionization over every configuration's atoms, then the push of every
+// configuration's electrons together (in the order of their step counts, or,
+// where the workspace has no room for that, in one persistent launch with a
+// work counter per configuration), then one binning pass over the chunk's
+// final momenta into per-configuration energy-angle histograms.
 #pragma once
 
 #include "rpdla_kernels.hpp"
@@ -101,7 +100,7 @@ __global__ void __launch_bounds__(256, IonizeWaves<FIELD>::value) batch_ionize_k
                        A.tb + i * A.K);
 }
 
-// One persistent launch over n_cfg * apc * K slots.  Slot j belongs to
+// The queue push: one persistent launch over n_cfg * apc * K slots.  Slot j belongs to
 // configuration j / (apc K) and atom (j / K) % apc of the chunk.  Every
 // configuration has its own work counter, and a wave works on ONE
 // configuration at a time: it starts on configuration (wave id mod n_cfg),
@@ -199,6 +198,234 @@ __global__ void __launch_bounds__(256, BatchWaves<ELEC>::value) batch_push_kerne
         __syncthreads();
         for (int w = threadIdx.x; w < ncfg; w += blockDim.x)
             if (s_steps[w]) atomicAdd(&A.steps[w], s_steps[w]);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Ordered push of a chunk (see push_group_kernel): each configuration's born
+// slots in the order of their step counts, in groups of 64 of one configuration
+// (the last one of each part empty), and the groups of all configurations in
+// the order of theirs, dealt to the waves in whole rounds and time slices.  A
+// wave's configuration is uniform for a group and read with scalar loads.
+// With the queues above a wave serves one configuration until that runs dry,
+// every time down to its last electron: a sweep of 64 configurations of 10,240
+// slots took 13.6% longer (both timed against a third form on two chips, 0.889
+// and 0.782 of its time).
+// ---------------------------------------------------------------------------
+constexpr int kBatchBins = 512;
+
+struct BatchPlan {
+    uint32_t waves, whole, rest, slices, slice_steps;
+    uint32_t pad;
+    uint32_t born[kMaxCfg], base[kMaxCfg];   // born slots; first place in the order
+    uint32_t cursor[kMaxCfg * kBatchBins];   // counts, then the next free place
+};
+
+struct BatchGroup { uint32_t cfg, first; };  // first: place in its configuration's order
+
+struct BatchPlanArgs {
+    BatchPlan* plan;
+    uint32_t* order;             // slot of its configuration
+    BatchGroup* groups;
+    uint64_t* state;
+    uint32_t simds, max_waves;
+    double n_max;                // bound of the step counts of all configurations
+};
+
+__device__ inline uint32_t batch_bin(const DevCfg& c, const BatchPlanArgs& P, double t0, double z)
+{
+    const double taue = (c.window == 0 ? z * c.k : 0.0) + c.ta_n;
+    const double f = (taue - t0 * c.omega) / c.hn * ((double)kBatchBins / P.n_max);
+    const double g = fmin(fmax(f, 0.0), (double)(kBatchBins - 1));
+    return (uint32_t)(kBatchBins - 1) - (uint32_t)g;
+}
+
+// One configuration per blockIdx.y, kPlanChunk of its slots per block.
+template <bool PLACE>
+__global__ void __launch_bounds__(kPlanBlock) batch_plan_kernel(BatchArgs A,
+                                                                const DevCfg* __restrict__ cfgs,
+                                                                BatchPlanArgs P)
+{
+    __shared__ uint32_t bins[kBatchBins], base[kBatchBins];
+    constexpr int kPer = kPlanChunk / kPlanBlock;
+    const int c = blockIdx.y;
+    const int64_t per_cfg = A.apc * A.K;
+    const int64_t first = (int64_t)A.ctl->chunk * A.apc;
+    for (int b = threadIdx.x; b < kBatchBins; b += kPlanBlock) bins[b] = 0;
+    __syncthreads();
+    const int64_t lo = (int64_t)blockIdx.x * kPlanChunk;
+    uint32_t bin[kPer], rank[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int64_t j = lo + i * kPlanBlock + threadIdx.x;
+        bin[i] = kBatchBins;
+        if (j < per_cfg) {
+            const int64_t a = j / A.K;
+            const double t0 = A.tb[(int64_t)c * per_cfg + j];
+            if (first + a < A.atoms_per_cfg && t0 < __builtin_inf()) {
+                bin[i] = batch_bin(cfgs[c], P, t0, A.z[(int64_t)c * A.apc + a]);
+                rank[i] = atomicAdd(&bins[bin[i]], 1u);
+            }
+        }
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < kBatchBins; b += kPlanBlock)
+        if (bins[b]) base[b] = atomicAdd(&P.plan->cursor[c * kBatchBins + b], bins[b]);
+    if constexpr (PLACE) {
+        __syncthreads();
+        uint32_t* order = P.order + P.plan->base[c];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+            if (bin[i] < kBatchBins)
+                order[base[bin[i]] + rank[i]] = (uint32_t)(lo + i * kPlanBlock + threadIdx.x);
+    }
+}
+
+// Inclusive sum over the block's threads.
+__device__ inline uint32_t block_scan(uint32_t v, uint32_t* part)
+{
+    part[threadIdx.x] = v;
+    __syncthreads();
+    for (int d = 1; d < kPlanBlock; d *= 2) {
+        const uint32_t add = (int)threadIdx.x >= d ? part[threadIdx.x - d] : 0;
+        __syncthreads();
+        part[threadIdx.x] += add;
+        __syncthreads();
+    }
+    const uint32_t r = part[threadIdx.x];
+    __syncthreads();
+    return r;
+}
+
+// Places of the bins, the groups in order, and the plan (one block).
+__global__ void __launch_bounds__(kPlanBlock) batch_plan_scan_kernel(int n_cfg, BatchPlanArgs P)
+{
+    __shared__ uint32_t part[kPlanBlock], born[kMaxCfg], first_bin;
+    // each configuration's bins, one after another; threads past kBatchBins add nothing
+    for (int c = 0; c < n_cfg; ++c) {
+        const bool mine = threadIdx.x < kBatchBins;
+        const uint32_t n = mine ? P.plan->cursor[c * kBatchBins + threadIdx.x] : 0;
+        const uint32_t up = block_scan(n, part);
+        if (mine) P.plan->cursor[c * kBatchBins + threadIdx.x] = up - n;
+        if (threadIdx.x == kPlanBlock - 1) born[c] = up;
+    }
+    if (threadIdx.x == 0) first_bin = 0;
+    __syncthreads();
+    const int tc = (int)threadIdx.x;
+    const uint32_t total = block_scan(tc < n_cfg ? born[tc] : 0, part);
+    if (tc < n_cfg) {
+        P.plan->born[tc] = born[tc];
+        P.plan->base[tc] = total - born[tc];
+    }
+    // a group starts in each place that is a multiple of 64: groups in the
+    // order of (bin, configuration)
+    const int cells = n_cfg * kBatchBins, per = (cells + kPlanBlock - 1) / kPlanBlock;
+    auto starts = [&](int cell, uint32_t& lo) {
+        const int b = cell / n_cfg, c = cell - b * n_cfg;
+        const uint32_t* off = P.plan->cursor + c * kBatchBins;
+        lo = (off[b] + 63u) / 64u;
+        const uint32_t hi = ((b + 1 < kBatchBins ? off[b + 1] : born[c]) + 63u) / 64u;
+        return hi - lo;
+    };
+    uint32_t sum = 0, lo;
+    for (int i = 0; i < per; ++i) {
+        const int cell = tc * per + i;
+        if (cell < cells) sum += starts(cell, lo);
+    }
+    const uint32_t up = block_scan(sum, part);
+    if (tc == kPlanBlock - 1) part[0] = up;
+    __syncthreads();
+    const uint32_t groups = part[0];
+    const uint32_t per_simd = groups / P.simds < P.max_waves ? groups / P.simds : P.max_waves;
+    const uint32_t W = P.simds * (per_simd > 0 ? per_simd : 1);
+    const uint32_t whole = groups / W >= 2 ? (groups / W - 1) * W : 0;
+    const uint32_t rest = groups - whole;
+    uint32_t at = up - sum;
+    for (int i = 0; i < per; ++i) {
+        const int cell = tc * per + i;
+        if (cell >= cells) break;
+        const uint32_t n = starts(cell, lo);
+        const int b = cell / n_cfg, c = cell - b * n_cfg;
+        if (n && at <= whole && whole < at + n) first_bin = (uint32_t)b;
+        for (uint32_t g = 0; g < n; ++g) P.groups[at + g] = BatchGroup{(uint32_t)c, (lo + g) * 64u};
+        at += n;
+    }
+    __syncthreads();
+    if (tc == 0) {
+        BatchPlan& p = *P.plan;
+        p.waves = W;
+        p.whole = whole;
+        p.rest = rest;
+        p.slices = rest <= W ? 1u : (uint32_t)((uint64_t)kPlanLaunches * W / rest);
+        const double top = (double)(kBatchBins - first_bin) * (P.n_max / (double)kBatchBins);
+        p.slice_steps = (uint32_t)(top / (double)p.slices) + 1u;
+    }
+}
+
+template <int FIELD, class ELEC>
+__global__ void __launch_bounds__(256, BatchWaves<ELEC>::value) batch_group_kernel(
+    BatchArgs A, const DevCfg* __restrict__ cfgs, BatchPlanArgs P, int32_t slice)
+{
+    const BatchPlan* plan = P.plan;
+    const uint32_t W = plan->waves, whole = plan->whole, rest = plan->rest;
+    const uint32_t wave = (uint32_t)wave_index();
+    if (wave >= W) return;
+    uint32_t group = wave, end = whole;
+    int32_t steps = 0x7fffffff;
+    bool first = true;
+    if (slice >= 0) {
+        const uint32_t slices = plan->slices;
+        const uint64_t p = (uint64_t)slice * W + wave;
+        if (rest == 0 || p >= (uint64_t)rest * slices) return;
+        const uint32_t turn = (uint32_t)(p / rest);
+        group = whole + (uint32_t)(p - (uint64_t)turn * rest);
+        end = group + 1;
+        first = turn == 0;
+        if (turn + 1 < slices) steps = (int32_t)plan->slice_steps;
+    }
+    StepRegs<FIELD, ELEC> R;
+    const int64_t per_cfg = A.apc * A.K;
+    for (; group < end; group += W) {
+        const uint32_t c = P.groups[group].cfg;
+        const uint32_t lane = (uint32_t)__lane_id();
+        const uint32_t at = P.groups[group].first + lane;
+        const bool used = at < plan->born[c];
+        const size_t stride = (size_t)rest * 64;
+        uint64_t* const state = P.state + (size_t)(group - whole) * 64 + lane;
+        int64_t js = 0;
+        if (used) js = (int64_t)c * per_cfg + (int64_t)P.order[plan->base[c] + at];
+        ELEC e;
+        e.left = 0;
+        if (!first) {
+            get_state(state, stride, e);
+        } else {
+            if (used) {
+                const int64_t ia = (int64_t)c * A.apc + (js - (int64_t)c * per_cfg) / A.K;
+                if (!elec_init(cfgs[c], e, A.tb[js], A.x[ia], A.y[ia], A.z[ia])) {
+                    const double q = __builtin_nan("");
+                    A.ux[js] = q; A.uy[js] = q; A.uz[js] = q;
+                } else if (e.left <= 0) {
+                    double ux, uy, uz, xf, yf, zf;
+                    elec_final(cfgs[c], e, ux, uy, uz, xf, yf, zf);
+                    A.ux[js] = ux; A.uy[js] = uy; A.uz[js] = uz;
+                }
+            }
+            if (A.steps) {
+                unsigned long long n = e.left > 0 ? (unsigned long long)e.left : 0ull;
+                for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+                if (lane == 0 && n) atomicAdd(&A.steps[c], n);
+            }
+        }
+        const bool runs = e.left > 0;
+        R.set(cfgs[c]);
+        for (int32_t n = steps; n > 0 && __ballot(e.left > 0) != 0; --n)
+            if (e.left > 0) elec_step<FIELD, true>(R.c, e, R.k);
+        if (runs && e.left == 0) {
+            double ux, uy, uz, xf, yf, zf;
+            elec_final(cfgs[c], e, ux, uy, uz, xf, yf, zf);
+            A.ux[js] = ux; A.uy[js] = uy; A.uz[js] = uz;
+        }
+        if (steps != 0x7fffffff) put_state(state, stride, e);
     }
 }
 

@@ -1227,12 +1227,18 @@ struct StepRegs {
     using Cfg = typename std::conditional<kHold, RadialCfg, DevCfg>::type;
     Cfg c;
     fm::Coef k;
-    __device__ inline explicit StepRegs(const DevCfg& d)
+    __device__ inline void set(const DevCfg& d)
     {
-        if constexpr (kHold) {
+        if constexpr (kHold)
             c = RadialCfg{d.hn, d.inv_zrn, d.inv_w0n2, d.e2, d.phi0, d.inv_T0n, d.a0_w, d.er_scale,
                           d.ez_2, d.rr_kappa, d.ad_rtol, d.ad_atol, d.ad_hmax, d.ad_ktol,
                           d.ad_max_steps};
+        else
+            c = d;
+    }
+    __device__ inline StepRegs()
+    {
+        if constexpr (kHold) {
             constexpr bool kWide = std::is_same<ELEC, ElecDP>::value;
             auto keep = [](double& v) {
                 if constexpr (kWide) keep_in_vgpr(v); else keep_in_sgpr(v);
@@ -1250,8 +1256,6 @@ struct StepRegs {
             keep_in_vgpr(k.ns2o8); keep_in_vgpr(k.s2);
             keep_in_vgpr(k.c375); keep_in_vgpr(k.c1_0625); keep_in_vgpr(k.c1875);
             keep_in_vgpr(k.c5);
-        } else {
-            c = d;
         }
     }
 };
@@ -1280,7 +1284,8 @@ template <int FIELD, class ELEC>
 __global__ void __launch_bounds__(256, ElecWaves<ELEC>::value) push_kernel(PushArgs args)
 {
     constexpr bool X = HasExtra<ELEC>::value;
-    const StepRegs<FIELD, ELEC> R(args.c);
+    StepRegs<FIELD, ELEC> R;
+    R.set(args.c);
     int64_t idx = -1;
     bool exhausted = false;
     ELEC e;
@@ -1533,7 +1538,8 @@ __global__ void __launch_bounds__(256, ElecWaves<ELEC>::value) push_group_kernel
         first = turn == 0;
         if (turn + 1 < slices) steps = (int32_t)plan->slice_steps;
     }
-    const StepRegs<FIELD, ELEC> R(args.c);
+    StepRegs<FIELD, ELEC> R;
+    R.set(args.c);
     for (; group < end; group += W) {
         ELEC e;
         e.left = 0;
