@@ -420,17 +420,18 @@ rpdla_status enqueue_push(const rpdla_laser* L, int32_t precision, int64_t n_slo
     }
 }
 
-// Launch a histogram kernel over n slots: with its bins in LDS where they fit.
-// 512 blocks of 16 waves keep every CU's wave slots full; more would only add
-// atomics on the tallies.
+// Launch a histogram kernel over n slots: all bins in LDS where they fit, two
+// blocks of 16 waves on a CU, else the table, one block on a CU.
 template <class F>
 void launch_hist(int64_t nbins, int tallies, int64_t n, F launch)
 {
-    const unsigned blocks = (unsigned)std::min<int64_t>(cdiv(n, rpdla::kHistBlock), 512);
+    const int64_t blocks = cdiv(n, rpdla::kHistBlock);
     if (nbins <= rpdla::kHistLdsBins)
-        launch(std::true_type{}, blocks, (size_t)(nbins + tallies) * sizeof(unsigned));
+        launch(std::true_type{}, (unsigned)std::min<int64_t>(blocks, 512),
+               (size_t)(nbins + tallies) * sizeof(unsigned));
     else
-        launch(std::false_type{}, blocks, (size_t)tallies * sizeof(unsigned));
+        launch(std::false_type{}, (unsigned)std::min<int64_t>(blocks, 256),
+               (size_t)(2 * rpdla::kHistPlaces + tallies) * sizeof(unsigned));
 }
 
 // Device address of this device's copy of `scratch`, looked up once per
@@ -780,8 +781,8 @@ rpdla_status rpdla_histogram(int64_t n, const double* t_birth, const double* ux,
     H.lo = spec->logE_min_MeV;
     H.width = (spec->logE_max_MeV - spec->logE_min_MeV) / (double)spec->nE;
     H.mec2 = kMeC2MeV;
-    launch_hist(2ll * H.nE * H.nA, 6, n, [&](auto lds, unsigned blocks, size_t bytes) {
-        hipLaunchKernelGGL(rpdla::histogram_kernel<decltype(lds)::value>, dim3(blocks),
+    launch_hist(2ll * H.nE * H.nA, 6, n, [&](auto all, unsigned blocks, size_t bytes) {
+        hipLaunchKernelGGL(rpdla::histogram_kernel<decltype(all)::value>, dim3(blocks),
                            dim3(rpdla::kHistBlock), bytes, (hipStream_t)stream, H, n, t_birth, ux,
                            uy, uz, (unsigned long long*)counts, (unsigned long long*)tallies);
     });
@@ -1300,8 +1301,8 @@ rpdla_status rpdla_histogram2d(int64_t n, const double* a, const double* b, cons
     H.wb = (spec->b_hi - spec->b_lo) / (double)spec->nb;
     H.na = spec->na;
     H.nb = spec->nb;
-    launch_hist(2ll * H.na * H.nb, 2, n, [&](auto lds, unsigned blocks, size_t bytes) {
-        hipLaunchKernelGGL(rpdla::histogram2d_kernel<decltype(lds)::value>, dim3(blocks),
+    launch_hist(2ll * H.na * H.nb, 2, n, [&](auto all, unsigned blocks, size_t bytes) {
+        hipLaunchKernelGGL(rpdla::histogram2d_kernel<decltype(all)::value>, dim3(blocks),
                            dim3(rpdla::kHistBlock), bytes, (hipStream_t)stream, H, n, a, b, uz,
                            (unsigned long long*)counts, (unsigned long long*)tallies);
     });

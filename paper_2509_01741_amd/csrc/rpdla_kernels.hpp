@@ -1637,33 +1637,55 @@ __device__ inline void wave_merge_add(int64_t key, unsigned long long* __restric
     }
 }
 
-// Counters of one block: the bins in LDS where they fit (LDS), else in global
-// memory, and NT tallies, counted per wave by ballot while it runs and added
-// to global memory once, at the end.  A tally is one address for the whole
-// grid, and the two or three atomics on them for every 64 slots were what
-// bounded the histograms (1e7 slots, 4.5e5 atomics, 5.6 ms whatever the bins).
-// Now 1e7 slots take 0.14 ms with bins in LDS (energies and angles; the
-// logarithm and the arctangent bound it) or 0.04 ms (pairs, 5.7 TB/s), and 1.3 ms
-// with 92,160 bins in global memory, bound by its atomics.
-template <bool LDS, int NT>
+// Counters of one block.  All bins in the block's LDS where they fit
+// (kHistLdsBins); beyond that a direct-mapped table in LDS, where the first bin
+// that comes to a place owns it and the others of that place go to global
+// memory: a block's 4e4 slots fall into some 8e3 bins, so 9e6 slots leave 2.4e6
+// global atomics, spread over all bins alike.  NT tallies are counted per wave
+// by ballot while it runs and added to global memory once, at the end: a tally
+// is one address for the whole grid, and the two or three atomics on them for
+// every 64 slots were what bounded the histograms (1e7 slots, 4.5e5 atomics,
+// 5.6 ms whatever the bins).  Now 1e7 slots take 0.14 ms with the bins in LDS
+// (energies and angles; the logarithm and the arctangent bound it) or 0.04 ms
+// (pairs, 5.7 TB/s), and with 92,160 bins 0.20 ms with the table (1.18 ms with
+// an atomic a slot on the crowded bins in global memory; from 2e4 slots on the
+// table is no slower).
+constexpr int64_t kHistLdsBins = 8192;     // 32 KiB of 32-bit counters
+constexpr int kHistPlaces = 16384;         // 128 KiB of bin numbers and counters
+constexpr int kHistBlock = 1024;
+
+template <bool ALL, int NT>
 struct BlockCounts {
     unsigned* bins;
+    unsigned* owner;
     unsigned* tally;
     unsigned long long* counts;
     unsigned t[NT];
     __device__ inline BlockCounts(unsigned* lds, int64_t nbins, unsigned long long* c)
-        : bins(lds + NT), tally(lds), counts(c)
+        : bins(lds + NT), owner(lds + NT + kHistPlaces), tally(lds), counts(c)
     {
         for (int k = 0; k < NT; ++k) t[k] = 0;
-        const int words = NT + (LDS ? (int)nbins : 0);
+        const int words = NT + (ALL ? (int)nbins : kHistPlaces);
         for (int w = threadIdx.x; w < words; w += blockDim.x) lds[w] = 0;
+        if constexpr (!ALL)
+            for (int w = threadIdx.x; w < kHistPlaces; w += blockDim.x) owner[w] = ~0u;
         __syncthreads();
     }
     __device__ inline void add(int64_t key)
     {
         if (key < 0) return;
-        if constexpr (LDS) atomicAdd(&bins[key], 1u);
-        else atomicAdd(&counts[key], 1ull);
+        if constexpr (ALL) {
+            atomicAdd(&bins[key], 1u);
+        } else {
+            const unsigned k = (unsigned)key, h = k & (kHistPlaces - 1);   // bins < 2^30
+            unsigned o = __hip_atomic_load(&owner[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (o == ~0u) {
+                o = atomicCAS(&owner[h], ~0u, k);
+                if (o == ~0u) o = k;
+            }
+            if (o == k) atomicAdd(&bins[h], 1u);
+            else atomicAdd(&counts[key], 1ull);
+        }
     }
     __device__ inline void tallied(int k, bool hit) { t[k] += (unsigned)__popcll(__ballot(hit)); }
     __device__ inline void finish(int64_t nbins, unsigned long long* tallies)
@@ -1673,17 +1695,14 @@ struct BlockCounts {
         __syncthreads();
         if (threadIdx.x < NT && tally[threadIdx.x])
             atomicAdd(&tallies[threadIdx.x], (unsigned long long)tally[threadIdx.x]);
-        if constexpr (LDS)
-            for (int w = threadIdx.x; w < (int)nbins; w += blockDim.x)
-                if (bins[w]) atomicAdd(&counts[w], (unsigned long long)bins[w]);
+        const int n = ALL ? (int)nbins : kHistPlaces;
+        for (int w = threadIdx.x; w < n; w += blockDim.x)
+            if (bins[w])
+                atomicAdd(&counts[ALL ? (unsigned)w : owner[w]], (unsigned long long)bins[w]);
     }
 };
 
-// Bins a block holds in LDS (32 KiB of 32-bit counters, two blocks on a CU).
-constexpr int64_t kHistLdsBins = 8192;
-constexpr int kHistBlock = 1024;
-
-template <bool LDS>
+template <bool ALL>
 __global__ void __launch_bounds__(kHistBlock) histogram_kernel(
     HistArgs H, int64_t n, const double* __restrict__ tb, const double* __restrict__ ux,
     const double* __restrict__ uy, const double* __restrict__ uz,
@@ -1691,7 +1710,7 @@ __global__ void __launch_bounds__(kHistBlock) histogram_kernel(
 {
     extern __shared__ unsigned hist_lds[];
     const int64_t nbins = 2ll * H.nE * H.nA;
-    BlockCounts<LDS, 6> B(hist_lds, nbins, counts);
+    BlockCounts<ALL, 6> B(hist_lds, nbins, counts);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     // wave-uniform trip count so every lane takes part in the ballots
     const int64_t base0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63);
@@ -1718,7 +1737,7 @@ struct Hist2dArgs {
     int32_t na, nb;
 };
 
-template <bool LDS>
+template <bool ALL>
 __global__ void __launch_bounds__(kHistBlock) histogram2d_kernel(
     Hist2dArgs H, int64_t n, const double* __restrict__ a, const double* __restrict__ b,
     const double* __restrict__ uz, unsigned long long* __restrict__ counts,
@@ -1727,7 +1746,7 @@ __global__ void __launch_bounds__(kHistBlock) histogram2d_kernel(
 #pragma clang fp contract(off)
     extern __shared__ unsigned hist_lds[];
     const int64_t nbins = 2ll * H.na * H.nb;
-    BlockCounts<LDS, 2> B(hist_lds, nbins, counts);
+    BlockCounts<ALL, 2> B(hist_lds, nbins, counts);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t base0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63);
     for (int64_t w = base0; w < n; w += stride) {

@@ -1,5 +1,5 @@
 """The histograms on both sides of their rule (bins in a block's LDS up to 8192,
-in global memory beyond), for slot counts around a wave and a block and past
+a table of 16,384 places in LDS beyond), for slot counts around a wave and a block and past
 one pass of the whole grid, with bins that many slots share, against the
 oracle's binning of the same numbers: counts and tallies exact."""
 import numpy as np
@@ -9,7 +9,8 @@ from gpu_common import require_gpu
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(1, 1), (64, 64), (4097, 1), (64, 65), (256, 180)]   # 2, 8192, 8194, 8320, 92160 bins
+SHAPES = [(1, 1), (64, 64), (4097, 1), (64, 65), (256, 180),
+          (16385, 2)]     # 2, 8192, 8194, 8320, 92160 and 65540 bins
 SIZES = [1, 63, 64, 65, 1023, 1024, 1025, 3000]
 
 
