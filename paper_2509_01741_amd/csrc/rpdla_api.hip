@@ -119,12 +119,15 @@ double adk_threshold_a2(double c0, double c1h, double c2, double level)
     if (f(lo) >= level) return 0.0;
     for (int it = 0; it < 200; ++it) {
         const double mid = 0.5 * (lo + hi);
+        if (mid <= lo || mid >= hi) break;     // neighbours: further halvings change nothing
         if (f(mid) < level) lo = mid; else hi = mid;
     }
     return exp(lo);
 }
 
-DevCfg make_cfg(const rpdla_laser* L)
+// Constants of one laser.  The tunnelling rates' (ten gamma functions and
+// bisections, 25 us of host time) are filled in for the ionization only.
+DevCfg make_cfg(const rpdla_laser* L, bool rates = false)
 {
     DevCfg c;
     memset(&c, 0, sizeof c);
@@ -157,7 +160,7 @@ DevCfg make_cfg(const rpdla_laser* L)
     // tunnelling constants: F [a.u.] = |a| fconv
     const double fconv = (kMe * kC * om / kQe) / kEa;
     c.lnw_zero = -700.0 - log(om);
-    for (int s = 0; s < rpdla::kMaxStates; ++s) {
+    for (int s = 0; rates && s < rpdla::kMaxStates; ++s) {
         const double Ip = kNeIpEv[s] / kEhEv;
         const double Z = (double)(s + 1);
         const double ns = Z / sqrt(2.0 * Ip);
@@ -578,7 +581,7 @@ rpdla_status rpdla_ionize(const rpdla_laser* L, uint64_t seed, uint32_t cfg_id, 
     if (n == 0) return RPDLA_OK;
     if (!x || !y || !z || !t_birth) return fail(RPDLA_EINVAL, "null pointer");
     if (n > ((int64_t)1 << 36)) return fail(RPDLA_ERANGE, "n_atoms too large");
-    const DevCfg c = make_cfg(L);
+    const DevCfg c = make_cfg(L, true);
     hipStream_t s = (hipStream_t)stream;
     switch (L->field) {
     case 1: return launch_ionize<1>(c, seed, cfg_id, first_atom, n, x, y, z, k_first, k_last, t_birth, s);
@@ -1070,7 +1073,7 @@ rpdla_status rpdla_run_batched_range(const rpdla_laser* cfgs, int32_t n_cfg, uin
     A.steps = (unsigned long long*)electron_steps;
     // configuration table: written by tiny kernels (arguments copied at launch)
     for (int c = 0; c < n_cfg; ++c) {
-        const DevCfg dc = make_cfg(&cfgs[c]);
+        const DevCfg dc = make_cfg(&cfgs[c], true);
         const double rmax = r_factor * cfgs[c].w0;
         const double zh = rpdla_rayleigh(&cfgs[c]);
         hipLaunchKernelGGL(rpdla::batch_set_cfg_kernel, dim3(1), dim3(64), 0, s, dc, rmax, zh,
