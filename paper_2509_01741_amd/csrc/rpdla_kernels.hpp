@@ -747,6 +747,22 @@ __device__ inline void elec_step(const CFG& c, ElecRR<RR>& e, const fm::Coef& k)
 }
 
 
+// The configuration where it lies among the kernel's arguments (of the push
+// kernels, whose arguments begin with it), read anew at each call: what is
+// needed once a step or less does not stay in scalar registers.
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef const __attribute__((address_space(4))) DevCfg* ColdCfgPtr;
+__device__ inline ColdCfgPtr cold_cfg()
+{
+    ColdCfgPtr p = (ColdCfgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+#else
+typedef const DevCfg* ColdCfgPtr;   // host pass: declaration only
+__device__ ColdCfgPtr cold_cfg();
+#endif
+
 // ---------------------------------------------------------------------------
 // Controlled-step push (Sec. 1, Sec. 2.1: fifth-order Runge-Kutta with a
 // controlled step, run until the kinetic energy is constant).  Dormand-Prince
@@ -820,16 +836,17 @@ template <int FIELD, bool BATCH = false, class CFG>
 __device__ inline void elec_step(const CFG& c, ElecDP& e, const fm::Coef& co)
 {
     using namespace dp;
+    const ColdCfgPtr cold = cold_cfg();
     if (e.fresh) {
         dp_rhs<FIELD, 1>(c, e.tau, e.y, e.k1, co);
         e.fresh = false;
     }
-    if (e.acc + e.rej >= c.ad_max_steps) {
+    if (e.acc + e.rej >= cold->ad_max_steps) {
         e.failed = true;
         e.left = 0;
         return;
     }
-    double hs = e.h < c.ad_hmax ? e.h : c.ad_hmax;
+    double hs = e.h < cold->ad_hmax ? e.h : cold->ad_hmax;
     bool last = false;
     if (hs >= e.taue - e.tau) { hs = e.taue - e.tau; last = true; }
     double k2[6], k3[6], k4[6], k5[6], k6[6], k7[6], yt[6];
@@ -862,7 +879,7 @@ __device__ inline void elec_step(const CFG& c, ElecDP& e, const fm::Coef& co)
         const double d = fabs(hs * (e1 * e.k1[i] + e3 * k3[i] + e4 * k4[i] + e5 * k5[i] +
                                     e6 * k6[i] + e7 * k7[i]));
         const double ya = fabs(e.y[i]), yb = fabs(y5[i]);
-        const double r = d / (c.ad_atol + c.ad_rtol * (ya > yb ? ya : yb));
+        const double r = d / (cold->ad_atol + cold->ad_rtol * (ya > yb ? ya : yb));
         err = (r > err || r != r) ? r : err;
     }
     if (err != err) {            // the step produced no number: give up on this electron
@@ -878,7 +895,7 @@ __device__ inline void elec_step(const CFG& c, ElecDP& e, const fm::Coef& co)
         if (last) { e.left = 0; return; }
         if (e.tau - e.t_ref >= 0.999 * (2.0 * 3.14159265358979323846)) {
             const double g = sqrt(1.0 + e.y[3] * e.y[3] + e.y[4] * e.y[4] + e.y[5] * e.y[5]);
-            if (fabs(g - e.g_ref) <= c.ad_ktol * g) { e.left = 0; return; }
+            if (fabs(g - e.g_ref) <= cold->ad_ktol * g) { e.left = 0; return; }
             e.g_ref = g;
             e.t_ref = e.tau;
         }
@@ -1201,8 +1218,6 @@ template <> struct ElecWaves<ElecDP> { static constexpr int value = 1; };
 // that it reads, under the same names).
 struct RadialCfg {
     double hn, inv_zrn, inv_w0n2, e2, phi0, inv_T0n, a0_w, er_scale, ez_2, rr_kappa;
-    double ad_rtol, ad_atol, ad_hmax, ad_ktol;
-    int64_t ad_max_steps;
 };
 
 // What a step reads besides its electron, in registers for the whole kernel.
@@ -1231,8 +1246,7 @@ struct StepRegs {
     {
         if constexpr (kHold)
             c = RadialCfg{d.hn, d.inv_zrn, d.inv_w0n2, d.e2, d.phi0, d.inv_T0n, d.a0_w, d.er_scale,
-                          d.ez_2, d.rr_kappa, d.ad_rtol, d.ad_atol, d.ad_hmax, d.ad_ktol,
-                          d.ad_max_steps};
+                          d.ez_2, d.rr_kappa};
         else
             c = d;
     }
