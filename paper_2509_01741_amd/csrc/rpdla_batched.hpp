@@ -115,11 +115,12 @@ __global__ void __launch_bounds__(256, IonizeWaves<FIELD>::value) batch_ionize_k
 // inactive slots are not written).
 // Register budgets: as the single push, except that the mixed form keeps 6
 // waves (its queue switching needs a few more registers than 7 waves leave).
-template <class E> struct BatchWaves { static constexpr int value = ElecWaves<E>::value; };
-template <> struct BatchWaves<ElecMixed> { static constexpr int value = 6; };
+template <class E, int FIELD>
+struct BatchWaves { static constexpr int value = ElecWaves<E, FIELD>::value; };
+template <int FIELD> struct BatchWaves<ElecMixed, FIELD> { static constexpr int value = 6; };
 
 template <int FIELD, class ELEC>
-__global__ void __launch_bounds__(256, BatchWaves<ELEC>::value) batch_push_kernel(
+__global__ void __launch_bounds__(256, (BatchWaves<ELEC, FIELD>::value)) batch_push_kernel(
     BatchArgs A, const DevCfg* __restrict__ cfgs)
 {
     extern __shared__ unsigned long long s_steps[];   // [n_cfg] steps taken in this block
@@ -363,7 +364,7 @@ __global__ void __launch_bounds__(kPlanBlock) batch_plan_scan_kernel(int n_cfg, 
 }
 
 template <int FIELD, class ELEC>
-__global__ void __launch_bounds__(256, BatchWaves<ELEC>::value) batch_group_kernel(
+__global__ void __launch_bounds__(256, (BatchWaves<ELEC, FIELD>::value)) batch_group_kernel(
     BatchArgs A, const DevCfg* __restrict__ cfgs, BatchPlanArgs P, int32_t slice)
 {
     const BatchPlan* plan = P.plan;

@@ -1209,10 +1209,13 @@ __device__ inline int64_t queue_take_xcd(unsigned long long* queue, int64_t n, b
 // Waves per SIMD each electron form is compiled for (its register budget):
 // FP64 RK4 4 (5 needs a few spills and measured no faster), mixed 6 (lands
 // at 7 without spills, 1-5% faster than 5), controlled-step unbounded (six
-// stored stages, 2 waves).
-template <class E> struct ElecWaves { static constexpr int value = 4; };
-template <> struct ElecWaves<ElecMixed> { static constexpr int value = 7; };
-template <> struct ElecWaves<ElecDP> { static constexpr int value = 1; };
+// stored stages, 2 waves).  The linear focus at order 5 needs more: at 4 waves it
+// kept 63 doubles in scratch inside the step (3e5 slots 436 ms, now 301).
+template <class E, int FIELD>
+struct ElecWaves { static constexpr int value = FIELD == 25 ? 3 : 4; };
+template <int FIELD> struct ElecWaves<ElecMixed, FIELD> { static constexpr int value = 7; };
+template <int FIELD> struct ElecWaves<ElecDP, FIELD> { static constexpr int value = 1; };
+template <bool RR> struct ElecWaves<ElecRR<RR>, 25> { static constexpr int value = 2; };
 
 // Configuration constants of the radial field's step (the members of DevCfg
 // that it reads, under the same names).
@@ -1295,7 +1298,7 @@ __device__ PushArgsPtr push_args();
 #endif
 
 template <int FIELD, class ELEC>
-__global__ void __launch_bounds__(256, ElecWaves<ELEC>::value) push_kernel(PushArgs args)
+__global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_kernel(PushArgs args)
 {
     constexpr bool X = HasExtra<ELEC>::value;
     StepRegs<FIELD, ELEC> R;
@@ -1531,7 +1534,7 @@ __device__ GroupArgsPtr group_args();
 #endif
 
 template <int FIELD, class ELEC>
-__global__ void __launch_bounds__(256, ElecWaves<ELEC>::value) push_group_kernel(GroupArgs args)
+__global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_group_kernel(GroupArgs args)
 {
     constexpr bool X = HasExtra<ELEC>::value;
     const PushPlan* plan = args.P.plan;
