@@ -206,16 +206,15 @@ rpdla_status rpdla_birth_phase(const rpdla_laser* L, int64_t n_slots, const doub
  * in float with Kahan compensation.
  * EINVAL: bad laser, n_slots < 0, slots_per_atom < 1, null pointers with
  * n_slots > 0.
- * Up to 64 slots per SIMD (65536 on 256 CUs) lanes draw their slots from a
- * work queue, which needs a small stream-ordered device allocation (1 KiB;
- * RPDLA_EHIP if that fails): the slots are split into eight contiguous parts
- * with a counter each, and a wave draws from the part of the XCD it runs on
- * (the hardware XCC_ID register) before it moves on to the others.  Above that
- * the born slots are pushed in the order of their step counts, 64 neighbours
- * to a wave, the last waves' worth in time slices (some 35 launches), with
- * stream-ordered scratch of 4 bytes a slot and up to 70 MB; when that cannot
- * be allocated, or from 2^32 - 1 slots on, the queue is used.  Results do not
- * depend on either.
+ * The born slots are pushed in the order of their step counts, 64 neighbours
+ * to a wave; beyond one wave per SIMD (65536 slots on 256 CUs) the last waves'
+ * worth runs in time slices (some 35 launches).  Stream-ordered device scratch:
+ * 20 KB and 4 bytes a slot, with slices up to 70 MB more.  When that cannot be
+ * allocated, or from 2^32 - 1 slots on, lanes draw their slots from a work
+ * queue instead, which needs 1 KiB (RPDLA_EHIP if that fails too): the slots are
+ * split into eight contiguous parts with a counter each, and a wave draws from
+ * the part of the XCD it runs on (the hardware XCC_ID register) before it moves
+ * on to the others.  Results do not depend on either.
  * ------------------------------------------------------------------------ */
 rpdla_status rpdla_push(const rpdla_laser* L, int32_t precision, int64_t n_slots,
                         const double* t_birth, const double* x0, const double* y0,
@@ -225,7 +224,7 @@ rpdla_status rpdla_push(const rpdla_laser* L, int32_t precision, int64_t n_slots
 /* ------------------------------------------------------------------------
  * Allocation-free push, for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc).  Same arguments, validation, kernels and results as rpdla_push;
+ * hipMalloc).  Same arguments, validation and results as rpdla_push, by its queue;
  * it calls no hipMalloc / hipFree and no allocating library routine.  Its
  * work-queue counters live in a 1 KiB library-owned device array (one per
  * GPU, held until the process ends, its address looked up on the first call

@@ -251,10 +251,9 @@ rpdla_status launch_ionize(const DevCfg& c, uint64_t seed, uint32_t cfg, uint64_
     return RPDLA_OK;
 }
 
-// Scratch of one ordered push, stream-ordered: the plan, the order and the
-// electrons between slices.  An ordered push needs more electrons than one
-// wave on every SIMD holds (fewer are all under way at once, and the time is one
-// electron's) and 32-bit slot numbers.
+// The ordered push, with its scratch (the plan, the order and the electrons
+// between slices) allocated in stream order; *done false, and nothing
+// enqueued, where there is no room for it or slot numbers do not fit 32 bits.
 template <int FIELD, class ELEC>
 rpdla_status launch_ordered(const DevCfg& c, const rpdla::PushIO& io, Shape sh, hipStream_t st,
                             bool* done)
@@ -265,14 +264,14 @@ rpdla_status launch_ordered(const DevCfg& c, const rpdla::PushIO& io, Shape sh, 
     RPDLA_HIP(hipGetDevice(&dev));
     RPDLA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     const int simds = 4 * cus;
-    if (io.n_slots <= 64ll * simds || io.n_slots >= (int64_t)UINT32_MAX) return RPDLA_OK;
+    if (io.n_slots >= (int64_t)UINT32_MAX) return RPDLA_OK;
     RPDLA_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, sh.block, 0));
     const int waves_per_block = sh.block / 64;
     const int max_waves = per_cu * waves_per_block / 4;
     if (max_waves < 1) return RPDLA_OK;
-    // the rest is fewer than 2 W groups
+    // the rest is fewer than 2 W groups, and all at once up to a wave per SIMD
     const int64_t groups = cdiv(io.n_slots, 64);
-    const int64_t rest = std::min<int64_t>(groups, 2ll * simds * max_waves);
+    const int64_t rest = groups <= simds ? 0 : std::min<int64_t>(groups, 2ll * simds * max_waves);
     const size_t order = align256(sizeof(rpdla::PushPlan));
     const size_t state = order + align256((size_t)io.n_slots * sizeof(uint32_t));
     const size_t total = state + (size_t)rest * 64 * sizeof(ELEC);
@@ -297,8 +296,10 @@ rpdla_status launch_ordered(const DevCfg& c, const rpdla::PushIO& io, Shape sh, 
     hipLaunchKernelGGL(rpdla::plan_scan_kernel, dim3(1), dim3(rpdla::kPlanBlock), 0, st, ga.P);
     hipLaunchKernelGGL(rpdla::plan_order_kernel, dim3(blocks), dim3(rpdla::kPlanBlock), 0, st, c,
                        io, ga.P);
-    const unsigned grid = (unsigned)cdiv((int64_t)simds * max_waves, waves_per_block);
-    for (int l = groups >= 2ll * simds ? -1 : 0; l < rpdla::kPlanLaunches; ++l) {
+    const unsigned grid =
+        (unsigned)cdiv(std::min<int64_t>(groups, (int64_t)simds * max_waves), waves_per_block);
+    const int last = groups <= simds ? 1 : rpdla::kPlanLaunches;
+    for (int l = groups >= 2ll * simds ? -1 : 0; l < last; ++l) {
         ga.slice = l;
         hipLaunchKernelGGL(kern, dim3(grid), dim3(sh.block), 0, st, ga);
     }

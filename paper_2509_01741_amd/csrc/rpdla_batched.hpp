@@ -186,7 +186,7 @@ __global__ void __launch_bounds__(256, (BatchWaves<ELEC, FIELD>::value)) batch_p
             continue;
         }
         if (idx >= 0) {
-            elec_step<FIELD, true>(cfgs[cw], e, fm::kCoef);
+            elec_step<FIELD, false, true>(cfgs[cw], e, fm::kCoef);
             if (e.left == 0) {
                 double ux, uy, uz, xf, yf, zf;
                 elec_final(cfgs[cw], e, ux, uy, uz, xf, yf, zf);
@@ -364,7 +364,7 @@ __global__ void __launch_bounds__(kPlanBlock) batch_plan_scan_kernel(int n_cfg, 
 }
 
 template <int FIELD, class ELEC>
-__global__ void __launch_bounds__(256, (BatchWaves<ELEC, FIELD>::value)) batch_group_kernel(
+__global__ void __launch_bounds__(256, (GroupWaves<ELEC, FIELD>::value)) batch_group_kernel(
     BatchArgs A, const DevCfg* __restrict__ cfgs, BatchPlanArgs P, int32_t slice)
 {
     const BatchPlan* plan = P.plan;
@@ -419,8 +419,7 @@ __global__ void __launch_bounds__(256, (BatchWaves<ELEC, FIELD>::value)) batch_g
         }
         const bool runs = e.left > 0;
         R.set(cfgs[c]);
-        for (int32_t n = steps; n > 0 && __ballot(e.left > 0) != 0; --n)
-            if (e.left > 0) elec_step<FIELD, true>(R.c, e, R.k);
+        run_steps<FIELD, true>(R.c, e, R.k, steps);
         if (runs && e.left == 0) {
             double ux, uy, uz, xf, yf, zf;
             elec_final(cfgs[c], e, ux, uy, uz, xf, yf, zf);

@@ -621,10 +621,12 @@ __device__ inline bool elec_init(const CFG& c, ElecF64& e, double t0, double x, 
     return true;
 }
 
-template <int FIELD, bool BATCH = false, class CFG>
+// One step.  FULL: a step of the full length, which leaves the count of steps
+// to the caller; else the one that is due, the last one of its own length.
+template <int FIELD, bool FULL = false, bool BATCH = false, class CFG>
 __device__ inline void elec_step(const CFG& c, ElecF64& e, const fm::Coef& k)
 {
-    const double hs = (e.left == 1) ? e.h_last : c.hn;
+    const double hs = (!FULL && e.left == 1) ? e.h_last : c.hn;
     const double hh = 0.5 * hs;
     double kX, kY, kZ, kx, ky, kz, aX, aY, aZ, ax, ay, az;
     rhs_f64<FIELD, 1>(c, e.D, -e.cD, e.X, e.Y, e.Z, e.ux, e.uy, e.uz, kX, kY, kZ, kx, ky, kz, k);
@@ -652,7 +654,7 @@ __device__ inline void elec_step(const CFG& c, ElecF64& e, const fm::Coef& k)
     kahan_add_f64(e.uz, e.cuz, w6 * (az + kz));
     // the weighted slopes of D sum to 6 - sZ
     kahan_add_f64(e.D, e.cD, w6 * (6.0 - sZ));
-    --e.left;
+    if (!FULL) --e.left;
 }
 
 template <class CFG>
@@ -711,10 +713,10 @@ __device__ inline bool elec_init(const CFG& c, ElecRR<RR>& e, double t0, double 
     return elec_init(c, static_cast<ElecF64&>(e), t0, x, y, z);
 }
 
-template <int FIELD, bool BATCH = false, class CFG, bool RR>
+template <int FIELD, bool FULL = false, bool BATCH = false, class CFG, bool RR>
 __device__ inline void elec_step(const CFG& c, ElecRR<RR>& e, const fm::Coef& k)
 {
-    const double hs = (e.left == 1) ? e.h_last : c.hn;
+    const double hs = (!FULL && e.left == 1) ? e.h_last : c.hn;
     const double hh = 0.5 * hs;
     double kX, kY, kZ, kx, ky, kz, aX, aY, aZ, ax, ay, az;
     const double g2q = rhs_rr_f64<FIELD, RR, 1>(c, e.D, -e.cD, e.X, e.Y, e.Z, e.ux, e.uy, e.uz, kX,
@@ -743,7 +745,7 @@ __device__ inline void elec_step(const CFG& c, ElecRR<RR>& e, const fm::Coef& k)
     kahan_add_f64(e.uy, e.cuy, w6 * (ay + ky));
     kahan_add_f64(e.uz, e.cuz, w6 * (az + kz));
     kahan_add_f64(e.D, e.cD, w6 * (6.0 - sZ));
-    --e.left;
+    if (!FULL) --e.left;
 }
 
 
@@ -832,7 +834,7 @@ __device__ inline void dp_rhs(const CFG& c, double tau, const double* y, double*
                    k[4], k[5], co);
 }
 
-template <int FIELD, bool BATCH = false, class CFG>
+template <int FIELD, bool FULL = false, bool BATCH = false, class CFG>
 __device__ inline void elec_step(const CFG& c, ElecDP& e, const fm::Coef& co)
 {
     using namespace dp;
@@ -1074,12 +1076,12 @@ __device__ inline bool elec_init(const CFG& c, ElecMixed& e, double t0, double x
     return true;
 }
 
-template <int FIELD, bool BATCH = false, class CFG>
+template <int FIELD, bool FULL = false, bool BATCH = false, class CFG>
 __device__ inline void elec_step(const CFG& c, ElecMixed& e, const fm::Coef&)
 {
     const double h = c.hn;
     const double ta = fma((double)e.n, h, e.tau0);
-    const double hsd = (e.left == 1) ? e.h_last : h;
+    const double hsd = (!FULL && e.left == 1) ? e.h_last : h;
     const float hs = (float)hsd, hh = 0.5f * hs;
     const MixedBase b = mixed_base(c, ta, e.X, e.Y, e.Z);
     float kX, kY, kZ, kx, ky, kz, aX, aY, aZ, ax, ay, az;
@@ -1102,7 +1104,7 @@ __device__ inline void elec_step(const CFG& c, ElecMixed& e, const fm::Coef&)
     kahan_add(e.uy, e.cy, w6 * (ay + ky));
     kahan_add(e.uz, e.cz, w6 * (az + kz));
     ++e.n;
-    --e.left;
+    if (!FULL) --e.left;
 }
 
 template <class CFG>
@@ -1114,7 +1116,9 @@ __device__ inline void elec_final(const CFG& c, const ElecMixed& e, double& ux, 
 }
 
 // ---------------------------------------------------------------------------
-// Persistent push over one configuration.  A lane whose electron has reached
+// Persistent push over one configuration, for the controlled-step form, whose
+// step counts are not known beforehand, and where the ordered push below has no
+// scratch.  A lane whose electron has reached
 // its window end writes it out and takes the next slot from a global counter
 // (one atomic per wave per refill, ranks from the ballot), so lanes stay busy
 // however uneven the step counts are.  Unborn slots are written as NaN when
@@ -1354,22 +1358,22 @@ __global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_ker
 }
 
 // ---------------------------------------------------------------------------
-// Ordered push, for more electrons than one wave on every SIMD holds.  The
-// queue above refills single lanes, so when it runs dry every wave is left
-// with a few electrons at any point of their way, and the last 1.5 rounds of
-// waves issue for half-empty lanes; and with few electrons, some SIMDs hold one
-// wave more than others, which then take that much longer.  Here the born
-// slots are first put in the order of their step counts (a counting sort on
-// kPlanBins bins of N, most steps first), and a wave takes 64 neighbours of
-// that order, which end together.  Groups of 64 are dealt to W waves, a whole
-// number per SIMD: all but the last R < 2 W in whole rounds, one launch; those R
-// in time slices, a launch per slice, where the waves go round the groups
-// (slice p of the sequence is a step range of group p mod R), so that no SIMD has
-// more to do than another.  Between slices the electrons rest in memory (128
-// bytes each, against some 1500 steps).  It waits on nothing but the stream's
-// order.  Measured against the queue: 1e5 slots 111.9 -> 90.9 ms, 2e6 slots in
-// mixed precision 480 -> 450 ms, in double 889 -> 884 ms (there the chip lowers
-// its clock with the work in flight, and half-empty waves cost little).
+// Ordered push.  The queue above refills single lanes, so when it runs dry
+// every wave is left with a few electrons at any point of their way, and the
+// last 1.5 rounds of waves issue for half-empty lanes; and with few electrons,
+// some SIMDs hold one wave more than others, which then take that much longer.
+// Here the born slots are first put in the order of their step counts (a
+// counting sort on kPlanBins bins of N, most steps first), and a wave takes 64
+// neighbours of that order, which end together.  Groups of 64 are dealt to W
+// waves, a whole number per SIMD: all but the last R < 2 W in whole rounds, one
+// launch; those R in time slices, a launch per slice, where the waves go round
+// the groups (slice p of the sequence is a step range of group p mod R), so that
+// no SIMD has more to do than another.  Between slices the electrons rest in
+// memory (128 bytes each, against some 1500 steps).  It waits on nothing but the
+// stream's order.  Measured against the queue, with the same step: 1e5 slots
+// 111.9 -> 90.9 ms, 2e6 slots in mixed precision 480 -> 450 ms, in double 889 ->
+// 884 ms (there the chip lowers its clock with the work in flight, and half-empty
+// waves cost little).  The step loop below is what small launches gain by.
 // ---------------------------------------------------------------------------
 constexpr int kPlanBins = 4096;
 constexpr int kPlanLaunches = 32;         // slice launches
@@ -1514,6 +1518,49 @@ __device__ inline void get_state(const uint64_t* at, size_t stride, ELEC& e)
     __builtin_memcpy(&e, w, sizeof(ELEC));
 }
 
+// Up to `steps` steps of a wave's electrons.  Neighbours in the order have
+// nearly the same number of steps left, so all but a few go through a loop with
+// no test on any lane, one step length and two steps a turn (the new state then
+// need not be copied over the old one); lanes without an electron come along,
+// their values are not used.  In double precision a step is 593 instructions
+// there instead of 607 and its branches, and one wave on a SIMD issues one every 4.3 cycles
+// instead of 5.1 (8192 slots 36.0 -> 29.4 ms, 2e4 slots with radiation reaction
+// 76.9 -> 65.5 ms, 2e6 slots 4% faster).  The mixed form, several waves to a
+// SIMD, is slower with it (455 against 435 ms for 2e6 slots): there the other
+// waves fill the gaps, and the larger loop only takes registers.
+template <int FIELD, bool BATCH, class CFG, class ELEC>
+__device__ inline void run_steps(const CFG& c, ELEC& e, const fm::Coef& k, int32_t steps)
+{
+    if constexpr (!std::is_same<ELEC, ElecMixed>::value) {
+        int32_t least = e.left > 0 ? e.left : 0x7fffffff;
+        for (int o = 32; o > 0; o >>= 1) {
+            const int32_t other = __shfl_xor(least, o);
+            least = other < least ? other : least;
+        }
+        least = __builtin_amdgcn_readfirstlane(least);
+        if (least == 0x7fffffff) return;
+        const int32_t full = least - 1 < steps ? least - 1 : steps;
+        int32_t n = full;
+#pragma unroll 1
+        for (; n > 1; n -= 2) {
+            elec_step<FIELD, true, BATCH>(c, e, k);
+            elec_step<FIELD, true, BATCH>(c, e, k);
+        }
+        if (n > 0) elec_step<FIELD, true, BATCH>(c, e, k);
+        if (e.left > 0) e.left -= full;
+        steps -= full;
+    }
+#pragma unroll 1
+    for (; steps > 0 && __ballot(e.left > 0) != 0; --steps)
+        if (e.left > 0) elec_step<FIELD, false, BATCH>(c, e, k);
+}
+
+// Waves per SIMD of the ordered push: as the queue's, except the mixed form,
+// whose loop is fastest at 5 (2e6 slots at 4, 5, 6, 7: 409, 404, 446, 449 ms).
+template <class E, int FIELD>
+struct GroupWaves { static constexpr int value = ElecWaves<E, FIELD>::value; };
+template <int FIELD> struct GroupWaves<ElecMixed, FIELD> { static constexpr int value = 5; };
+
 struct GroupArgs {
     DevCfg c;
     PushIO io;
@@ -1534,7 +1581,7 @@ __device__ GroupArgsPtr group_args();
 #endif
 
 template <int FIELD, class ELEC>
-__global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_group_kernel(GroupArgs args)
+__global__ void __launch_bounds__(256, (GroupWaves<ELEC, FIELD>::value)) push_group_kernel(GroupArgs args)
 {
     constexpr bool X = HasExtra<ELEC>::value;
     const PushPlan* plan = args.P.plan;
@@ -1581,8 +1628,7 @@ __global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_gro
             }
         }
         const bool runs = e.left > 0;
-        for (int32_t n = steps; n > 0 && __ballot(e.left > 0) != 0; --n)
-            if (e.left > 0) elec_step<FIELD>(R.c, e, R.k);
+        run_steps<FIELD, false>(R.c, e, R.k, steps);
         {
             const GroupArgsPtr ga = group_args();
             if (runs && e.left == 0) {
