@@ -424,16 +424,15 @@ rpdla_status enqueue_push(const rpdla_laser* L, int32_t precision, int64_t n_slo
     }
 }
 
-rpdla::HistArgs hist_args(const rpdla_hist_spec& spec)
+// Field by field: the bytes between them, part of a graph's key, stay as they are.
+void set_hist(rpdla::HistArgs& H, const rpdla_hist_spec& spec)
 {
-    rpdla::HistArgs H;
     H.nE = spec.nE; H.nA = spec.nA; H.angle = spec.angle;
     H.lo = spec.logE_min_MeV;
     H.width = (spec.logE_max_MeV - spec.logE_min_MeV) / (double)spec.nE;
     H.mec2 = kMeC2MeV;
     H.log_mec2 = std::log10(kMeC2MeV);
     H.inv_width = 1.0 / H.width;
-    return H;
 }
 
 // Launch a histogram kernel over n slots: all bins in LDS where they fit, two
@@ -792,7 +791,8 @@ rpdla_status rpdla_histogram(int64_t n, const double* t_birth, const double* ux,
     if (!counts || !tallies) return fail(RPDLA_EINVAL, "null output pointer");
     if (n == 0) return RPDLA_OK;
     if (!t_birth || !ux || !uy || !uz) return fail(RPDLA_EINVAL, "null input pointer");
-    const rpdla::HistArgs H = hist_args(*spec);
+    rpdla::HistArgs H;
+    set_hist(H, *spec);
     launch_hist(2ll * H.nE * H.nA, 6, n, [&](auto all, unsigned blocks, size_t bytes) {
         hipLaunchKernelGGL(rpdla::histogram_kernel<decltype(all)::value>, dim3(blocks),
                            dim3(rpdla::kHistBlock), bytes, (hipStream_t)stream, H, n, t_birth, ux,
@@ -1073,7 +1073,7 @@ rpdla_status rpdla_run_batched_range(const rpdla_laser* cfgs, int32_t n_cfg, uin
     A.tb = (double*)(base + w.tb);
     A.ux = (double*)(base + w.ux); A.uy = (double*)(base + w.uy); A.uz = (double*)(base + w.uz);
     A.ctl = (rpdla::BatchCtl*)(base + w.ctl);
-    A.H = hist_args(*spec);
+    set_hist(A.H, *spec);
     A.counts = (unsigned long long*)counts;
     A.tallies = (unsigned long long*)tallies;
     A.steps = (unsigned long long*)electron_steps;
