@@ -58,6 +58,17 @@ COUNTERS2_CMD = COUNTERS_RUN.format(ctrs=" ".join(COUNTERS2), d="pmcC")
 COUNTER_KERNELS = (("fp64", "push_kernel<5, rpdla::ElecF64>"),
                    ("mixed", "push_kernel<5, rpdla::ElecMixed>"),
                    ("ionize", "ionize_kernel<5>"))
+# A push in the order of step counts is one launch of whole rounds and 32 time
+# slices at the bench ensemble's size (push_group_kernel), by its queue one launch.
+ORDERED_LAUNCHES = 33
+
+
+def _plain_name(kernel):
+    """(kernel name with both forms of the push under one name, launches of a call)"""
+    ordered = "push_group_kernel<" in kernel
+    return kernel.replace("push_group_kernel<", "push_kernel<"), ORDERED_LAUNCHES if ordered else 1
+
+
 PROFILE_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "push_fp64_rp_ne_fp64_1m_traffic.json")
 # sources that define the FP64 push kernel (its traffic figure is tied to them)
 KERNEL_SOURCES = ["rpdla_device.hpp", "rpdla_kernels.hpp", "rpdla_fastmath.hpp",
@@ -374,12 +385,12 @@ def write_traffic_summary(fetch_dir, write_dir, atoms=1_000_000, copy_mib=512, s
     for counter, d in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
         rows = _counter_rows(d, counter)
         copy = [v for k, v in rows if "copyBuffer" in k or "copy" in k.lower()]
-        push = [v for k, v in rows if PUSH_KERNEL_NAME in k]
+        push = [(v, _plain_name(k)[1]) for k, v in rows if PUSH_KERNEL_NAME in _plain_name(k)[0]]
         ion = [v for k, v in rows if "ionize_kernel<5>" in k]
-        if not copy or len(push) != 1:
-            raise SystemExit(f"{counter}: need one copy and one push dispatch, got {len(copy)}, "
-                             f"{len(push)}")
-        out[counter] = dict(copy_kib=max(copy), push_kib=push[0], ionize_kib=ion[0] if ion else None)
+        if not copy or not push or len(push) != push[0][1]:
+            raise SystemExit(f"{counter}: need one copy and one push call, got {len(copy)} and "
+                             f"{len(push)} dispatches")
+        out[counter] = dict(copy_kib=max(copy), push_kib=sum(v for v, _ in push), ionize_kib=ion[0] if ion else None)
     ref_kib = copy_mib * 1024.0
     f_scale = out["FETCH_SIZE"]["copy_kib"] / ref_kib
     w_scale = out["WRITE_SIZE"]["copy_kib"] / ref_kib
@@ -421,13 +432,13 @@ def write_traffic_summary(fetch_dir, write_dir, atoms=1_000_000, copy_mib=512, s
         "",
         f"Calibration on the copy of {ref_kib:.0f} KiB: FETCH_SIZE scale {f_scale:.3f}, "
         f"WRITE_SIZE scale {w_scale:.3f}.",
-        f"Scaled push traffic per launch: read {rd / 1e6:.1f} MB + write {wr / 1e6:.1f} MB = "
+        f"Scaled push traffic per call: read {rd / 1e6:.1f} MB + write {wr / 1e6:.1f} MB = "
         f"{(rd + wr) / 1e6:.1f} MB (algorithmic: {atoms * slots_per_atom:.0e} slots x (8 B birth "
         f"time + 48 B outputs) + {atoms:.0e} atoms x 24 B = {algo / 1e6:.1f} MB).",
-        "Spread over the multi-second launch this is well under 1 GB/s against 8 TB/s: the kernel",
-        "is bound by FP64 arithmetic.  The excess over the algorithmic bytes comes from the",
-        "scattered 8-byte output stores (each lane finishes its electron at its own time, so the",
-        "six stores of one electron land in six partly written sectors).",
+        "Spread over the multi-second call this is a few GB/s at most against 8 TB/s: the kernel",
+        "is bound by FP64 arithmetic.  The excess over the algorithmic bytes comes from the order",
+        "by step count (8-byte loads and stores scattered over the slots' arrays) and from the",
+        "electrons that rest in memory between time slices.",
         "",
         f"Kernel source hash {kernel_source_hash()} (bench.py reports this traffic only for",
         "that build of the push kernel).",
@@ -439,18 +450,21 @@ def write_traffic_summary(fetch_dir, write_dir, atoms=1_000_000, copy_mib=512, s
 
 
 def _per_dispatch(counter_dir):
-    """{form: {dispatch id: {counter: value summed over its dimensions}}}."""
+    """{form: {dispatch id: {counter: value summed over its dimensions}}} of each
+    kernel's last call."""
     import csv
     import glob
-    per = {}
+    per, launches = {}, {}
     for f in glob.glob(os.path.join(counter_dir, "**", "*counter_collection.csv"), recursive=True):
         with open(f) as fh:
             for r in csv.DictReader(fh):
+                plain, n = _plain_name(r["Kernel_Name"])
                 for form, name in COUNTER_KERNELS:
-                    if name in r["Kernel_Name"] and "batch" not in r["Kernel_Name"]:
+                    if name in plain and "batch" not in plain:
+                        launches[form] = n
                         d = per.setdefault(form, {}).setdefault(int(r["Dispatch_Id"]), {})
                         d[r["Counter_Name"]] = d.get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
-    return per
+    return {form: {i: disp[i] for i in sorted(disp)[-launches[form]:]} for form, disp in per.items()}
 
 
 def write_counter_summary(counter_dir, bench_json, counter_dir2=None, out_json=PROFILE_COUNTERS_FILE):
@@ -458,12 +472,18 @@ def write_counter_summary(counter_dir, bench_json, counter_dir2=None, out_json=P
     and the first run's bench line into per-unit FLOPs, issue rates, clock and
     lane activity of the FP64 and mixed pushes and the ionization kernel, and
     write out_json and the .md beside it."""
-    # one launch per form: bench.py calls the mixed push twice (untimed, then
-    # timed), so take the last dispatch of each kernel, the timed one
-    vals = {form: disp[max(disp)] for form, disp in _per_dispatch(counter_dir).items()}
-    vals2 = {}
-    if counter_dir2:
-        vals2 = {form: disp[max(disp)] for form, disp in _per_dispatch(counter_dir2).items()}
+    # one call per form: bench.py calls the mixed push twice (untimed, then
+    # timed), so take the last call of each kernel, the timed one
+    def last_call(d):
+        out = {}
+        for form, disp in _per_dispatch(d).items():
+            out[form] = {}
+            for counters in disp.values():
+                for ctr, v in counters.items():
+                    out[form][ctr] = out[form].get(ctr, 0.0) + v
+        return out
+    vals = last_call(counter_dir)
+    vals2 = last_call(counter_dir2) if counter_dir2 else {}
     line = [l for l in open(bench_json) if l.startswith("{")][-1]
     b = json.loads(line)
     steps = b["config"]["electron_steps"]
@@ -537,7 +557,8 @@ def write_counter_summary(counter_dir, bench_json, counter_dir2=None, out_json=P
            "set against the published peaks (157.3 TFLOP/s FP32, counted with packed FMAs, which the",
            "kernels do not use).  FLOPs per unit count every lane of a wave instruction (SQ counts",
            "are per wave); the active-lane figure gives the share of lanes doing work.  The counters",
-           "are taken from one launch per kernel: the timed one, the last of each kernel in the run.",
+           "are those of one call per kernel: the timed one, the last of each kernel in the run (a push",
+           "in the order of step counts is 33 launches, added up).",
            "",
            f"Kernel source hash {kernel_source_hash()} (bench.py uses these figures only for",
            "that build of the kernels)."]
@@ -599,18 +620,21 @@ def write_kernel_stats_summary(trace_dir, bench_json, out_md=PROFILE_KSTATS_FILE
             continue
         md.append(f"| `{_short_kernel_name(r['Name'])}` | {r['Calls']} | "
                   f"{float(r['TotalDurationNs']) / 1e6:.2f} | {float(r['AverageNs']) / 1e6:.2f} | {pct:.2f} |")
-    # the benchmark step is the first ionization and the first FP64 push dispatch
+    # the benchmark step is the first ionization and the first FP64 push call
     # (one timed step, no warm-up); later ones belong to the mixed workload
-    first = {}
+    first, seen = {}, {}
     for r in sorted(trace, key=lambda r: int(r["Dispatch_Id"])):
+        plain, n = _plain_name(r["Kernel_Name"])
         for key, pat in (("ionize", "rpdla::ionize_kernel<5>("),
                          ("push", "rpdla::push_kernel<5, rpdla::ElecF64>(")):
-            if pat in r["Kernel_Name"] and key not in first:
-                first[key] = (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e6
+            if pat in plain and seen.get(key, 0) < n:
+                seen[key] = seen.get(key, 0) + 1
+                first[key] = first.get(key, 0.0) + (int(r["End_Timestamp"])
+                                                    - int(r["Start_Timestamp"])) / 1e6
     md += ["", "The benchmark step's dispatches in `run_kernel_trace.csv` against bench.py's own "
            "HIP-event times of the same profiled run:", "",
            "| kernel | trace ms | bench.py ms |", "|---|---|---|",
-           f"| `push_kernel<5, ElecF64>` (1e7 slots) | {first.get('push', float('nan')):.2f} | "
+           f"| `push_group_kernel<5, ElecF64>` (1e7 slots, all launches) | {first.get('push', float('nan')):.2f} | "
            f"{b['roofline']['push_ms']:.2f} (`push_ms`) |",
            f"| `ionize_kernel<5>` (1e6 atoms) | {first.get('ionize', float('nan')):.2f} | "
            f"{b['ionize_ms']:.2f} (`ionize_ms`) |", "",
@@ -892,7 +916,7 @@ def main():
             "window": "[z/c - 5 tau, z/c + 10 tau]",
         },
         "roofline": {
-            "bound": "alu", "kernel": "push_kernel<5, ElecF64>",
+            "bound": "alu", "kernel": "push_group_kernel<5, ElecF64>",
             "achieved": achieved_tflops, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved_tflops / FP64_VECTOR_PEAK_TFLOPS, "traffic": traffic,
             "flop_per_electron_step": ALGO_FLOP_PER_STEP, "push_ms": round(push_avg, 2),
