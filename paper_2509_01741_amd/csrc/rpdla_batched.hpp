@@ -364,7 +364,7 @@ __global__ void __launch_bounds__(kPlanBlock) batch_plan_scan_kernel(int n_cfg, 
 }
 
 template <int FIELD, class ELEC>
-__global__ void __launch_bounds__(256, (GroupWaves<ELEC, FIELD>::value)) batch_group_kernel(
+__global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) batch_group_kernel(
     BatchArgs A, const DevCfg* __restrict__ cfgs, BatchPlanArgs P, int32_t slice)
 {
     const BatchPlan* plan = P.plan;

@@ -1526,8 +1526,12 @@ __device__ inline void get_state(const uint64_t* at, size_t stride, ELEC& e)
 // there instead of 607 and its branches, and one wave on a SIMD issues one every 4.3 cycles
 // instead of 5.1 (8192 slots 36.0 -> 29.4 ms, 2e4 slots with radiation reaction
 // 76.9 -> 65.5 ms, 2e6 slots 4% faster).  The mixed form, several waves to a
-// SIMD, is slower with it (455 against 435 ms for 2e6 slots): there the other
-// waves fill the gaps, and the larger loop only takes registers.
+// SIMD, is no faster with it, in twice the code.  It issues its float
+// instructions faster than one in four cycles, and then what bounds its loop
+// (435 instructions, 2.4 KB) is their fetch: with where the loop begins in a
+// window of 32 bytes, 6e5 slots take 122 to 141 ms and a sweep of 64 small
+// configurations 162 to 173 ms (8 places; the double-precision loops do not care),
+// so its place is stated (with that, 4 to 7 waves are within 1% of each other).
 template <int FIELD, bool BATCH, class CFG, class ELEC>
 __device__ inline void run_steps(const CFG& c, ELEC& e, const fm::Coef& k, int32_t steps)
 {
@@ -1550,16 +1554,16 @@ __device__ inline void run_steps(const CFG& c, ELEC& e, const fm::Coef& k, int32
         if (e.left > 0) e.left -= full;
         steps -= full;
     }
+    if constexpr (std::is_same<ELEC, ElecMixed>::value) {
+        if constexpr (BATCH)
+            asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
+        else
+            asm volatile(".p2align 5");
+    }
 #pragma unroll 1
     for (; steps > 0 && __ballot(e.left > 0) != 0; --steps)
         if (e.left > 0) elec_step<FIELD, false, BATCH>(c, e, k);
 }
-
-// Waves per SIMD of the ordered push: as the queue's, except the mixed form,
-// whose loop is fastest at 5 (2e6 slots at 4, 5, 6, 7: 409, 404, 446, 449 ms).
-template <class E, int FIELD>
-struct GroupWaves { static constexpr int value = ElecWaves<E, FIELD>::value; };
-template <int FIELD> struct GroupWaves<ElecMixed, FIELD> { static constexpr int value = 5; };
 
 struct GroupArgs {
     DevCfg c;
@@ -1581,7 +1585,7 @@ __device__ GroupArgsPtr group_args();
 #endif
 
 template <int FIELD, class ELEC>
-__global__ void __launch_bounds__(256, (GroupWaves<ELEC, FIELD>::value)) push_group_kernel(GroupArgs args)
+__global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_group_kernel(GroupArgs args)
 {
     constexpr bool X = HasExtra<ELEC>::value;
     const PushPlan* plan = args.P.plan;
