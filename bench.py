@@ -71,7 +71,7 @@ def _plain_name(kernel):
 
 PROFILE_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "push_fp64_rp_ne_fp64_1m_traffic.json")
 # sources that define the FP64 push kernel (its traffic figure is tied to them)
-KERNEL_SOURCES = ["rpdla_device.hpp", "rpdla_kernels.hpp", "rpdla_fastmath.hpp",
+KERNEL_SOURCES = ["rpdla_device.hpp", "rpdla_kernels.hpp", "rpdla_plan.hpp", "rpdla_fastmath.hpp",
                   "rpdla_fastmath_coeffs.hpp"]
 
 

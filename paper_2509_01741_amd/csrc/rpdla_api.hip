@@ -269,9 +269,8 @@ rpdla_status launch_ordered(const DevCfg& c, const rpdla::PushIO& io, Shape sh, 
     const int waves_per_block = sh.block / 64;
     const int max_waves = per_cu * waves_per_block / 4;
     if (max_waves < 1) return RPDLA_OK;
-    // the rest is fewer than 2 W groups, and all at once up to a wave per SIMD
     const int64_t groups = cdiv(io.n_slots, 64);
-    const int64_t rest = groups <= simds ? 0 : std::min<int64_t>(groups, 2ll * simds * max_waves);
+    const int64_t rest = rpdla::plan_rest_bound(groups, simds, max_waves);
     const size_t order = align256(sizeof(rpdla::PushPlan));
     const size_t state = order + align256((size_t)io.n_slots * sizeof(uint32_t));
     const size_t total = state + (size_t)rest * 64 * sizeof(ELEC);

@@ -216,8 +216,8 @@ __global__ void __launch_bounds__(256, (BatchWaves<ELEC, FIELD>::value)) batch_p
 constexpr int kBatchBins = 512;
 
 struct BatchPlan {
-    uint32_t waves, whole, rest, slices, slice_steps;
-    uint32_t pad;
+    PlanSplit split;
+    uint32_t slice_steps, pad;
     uint32_t born[kMaxCfg], base[kMaxCfg];   // born slots; first place in the order
     uint32_t cursor[kMaxCfg * kBatchBins];   // counts, then the next free place
 };
@@ -324,8 +324,8 @@ __global__ void __launch_bounds__(kPlanBlock) batch_plan_scan_kernel(int n_cfg, 
     auto starts = [&](int cell, uint32_t& lo) {
         const int b = cell / n_cfg, c = cell - b * n_cfg;
         const uint32_t* off = P.plan->cursor + c * kBatchBins;
-        lo = (off[b] + 63u) / 64u;
-        const uint32_t hi = ((b + 1 < kBatchBins ? off[b + 1] : born[c]) + 63u) / 64u;
+        lo = groups_of(off[b]);
+        const uint32_t hi = groups_of(b + 1 < kBatchBins ? off[b + 1] : born[c]);
         return hi - lo;
     };
     uint32_t sum = 0, lo;
@@ -336,11 +336,8 @@ __global__ void __launch_bounds__(kPlanBlock) batch_plan_scan_kernel(int n_cfg, 
     const uint32_t up = block_scan(sum, part);
     if (tc == kPlanBlock - 1) part[0] = up;
     __syncthreads();
-    const uint32_t groups = part[0];
-    const uint32_t per_simd = groups / P.simds < P.max_waves ? groups / P.simds : P.max_waves;
-    const uint32_t W = P.simds * (per_simd > 0 ? per_simd : 1);
-    const uint32_t whole = groups / W >= 2 ? (groups / W - 1) * W : 0;
-    const uint32_t rest = groups - whole;
+    const PlanSplit split = plan_split(part[0], P.simds, P.max_waves);
+    const uint32_t whole = split.whole;
     uint32_t at = up - sum;
     for (int i = 0; i < per; ++i) {
         const int cell = tc * per + i;
@@ -354,12 +351,9 @@ __global__ void __launch_bounds__(kPlanBlock) batch_plan_scan_kernel(int n_cfg, 
     __syncthreads();
     if (tc == 0) {
         BatchPlan& p = *P.plan;
-        p.waves = W;
-        p.whole = whole;
-        p.rest = rest;
-        p.slices = rest <= W ? 1u : (uint32_t)((uint64_t)kPlanLaunches * W / rest);
-        const double top = (double)(kBatchBins - first_bin) * (P.n_max / (double)kBatchBins);
-        p.slice_steps = (uint32_t)(top / (double)p.slices) + 1u;
+        p.split = split;
+        p.slice_steps = plan_slice_steps(
+            (double)(kBatchBins - first_bin) * (P.n_max / (double)kBatchBins), split.slices);
     }
 }
 
@@ -368,21 +362,20 @@ __global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) batch_gr
     BatchArgs A, const DevCfg* __restrict__ cfgs, BatchPlanArgs P, int32_t slice)
 {
     const BatchPlan* plan = P.plan;
-    const uint32_t W = plan->waves, whole = plan->whole, rest = plan->rest;
+    const uint32_t W = plan->split.waves, whole = plan->split.whole, rest = plan->split.rest;
     const uint32_t wave = (uint32_t)wave_index();
     if (wave >= W) return;
     uint32_t group = wave, end = whole;
     int32_t steps = 0x7fffffff;
     bool first = true;
     if (slice >= 0) {
-        const uint32_t slices = plan->slices;
-        const uint64_t p = (uint64_t)slice * W + wave;
-        if (rest == 0 || p >= (uint64_t)rest * slices) return;
-        const uint32_t turn = (uint32_t)(p / rest);
-        group = whole + (uint32_t)(p - (uint64_t)turn * rest);
+        const uint32_t slices = plan->split.slices;
+        const PlanTurn t = plan_turn((uint32_t)slice, wave, W, rest, slices);
+        if (!t.any) return;
+        group = whole + t.index;
         end = group + 1;
-        first = turn == 0;
-        if (turn + 1 < slices) steps = (int32_t)plan->slice_steps;
+        first = t.turn == 0;
+        if (t.turn + 1 < slices) steps = (int32_t)plan->slice_steps;
     }
     StepRegs<FIELD, ELEC> R;
     const int64_t per_cfg = A.apc * A.K;

@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "rpdla_device.hpp"
+#include "rpdla_plan.hpp"
 
 namespace rpdla {
 
@@ -1376,16 +1377,13 @@ __global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_ker
 // waves cost little).  The step loop below is what small launches gain by.
 // ---------------------------------------------------------------------------
 constexpr int kPlanBins = 4096;
-constexpr int kPlanLaunches = 32;         // slice launches
 constexpr int kPlanBlock = 1024;
 constexpr int kPlanChunk = 16 * kPlanBlock;   // slots of one block
 
 struct PushPlan {
     uint32_t born;               // slots in the order
-    uint32_t waves;              // W
-    uint32_t whole;              // groups pushed in whole rounds (a multiple of W)
-    uint32_t rest;               // R, groups pushed in slices
-    uint32_t slices, slice_steps;
+    PlanSplit split;             // waves W, groups in whole rounds, the rest R in slices
+    uint32_t slice_steps;
     uint32_t cursor[kPlanBins];  // counts, then the next free place of each bin
 };
 
@@ -1442,11 +1440,8 @@ __global__ void __launch_bounds__(kPlanBlock) plan_scan_kernel(PlanArgs P)
         __syncthreads();
     }
     const uint32_t born = part[kPlanBlock - 1];
-    const uint32_t groups = (born + 63) / 64;
-    const uint32_t per_simd = groups / P.simds < P.max_waves ? groups / P.simds : P.max_waves;
-    const uint32_t W = P.simds * (per_simd > 0 ? per_simd : 1);
-    const uint32_t whole = groups / W >= 2 ? (groups / W - 1) * W : 0;
-    const uint32_t rest = groups - whole;
+    const PlanSplit split = plan_split(groups_of(born), P.simds, P.max_waves);
+    const uint32_t whole = split.whole;
     if (threadIdx.x == 0) first = 0;
     __syncthreads();
     uint32_t at = part[threadIdx.x] - sum;
@@ -1461,12 +1456,9 @@ __global__ void __launch_bounds__(kPlanBlock) plan_scan_kernel(PlanArgs P)
     if (threadIdx.x == 0) {
         PushPlan& p = *P.plan;
         p.born = born;
-        p.waves = W;
-        p.whole = whole;
-        p.rest = rest;
-        p.slices = rest <= W ? 1u : (uint32_t)((uint64_t)kPlanLaunches * W / rest);
-        const double top = (double)(kPlanBins - first) * (P.n_max / (double)kPlanBins);
-        p.slice_steps = (uint32_t)(top / (double)p.slices) + 1u;
+        p.split = split;
+        p.slice_steps = plan_slice_steps((double)(kPlanBins - first) * (P.n_max / (double)kPlanBins),
+                                         split.slices);
     }
 }
 
@@ -1589,7 +1581,7 @@ __global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_gro
 {
     constexpr bool X = HasExtra<ELEC>::value;
     const PushPlan* plan = args.P.plan;
-    const uint32_t W = plan->waves, whole = plan->whole, rest = plan->rest;
+    const uint32_t W = plan->split.waves, whole = plan->split.whole, rest = plan->split.rest;
     const uint32_t wave = (uint32_t)wave_index();
     if (wave >= W) return;
     // whole rounds: groups wave, wave + W, ...; a slice: one group's next steps
@@ -1597,14 +1589,13 @@ __global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_gro
     int32_t steps = 0x7fffffff;
     bool first = true;
     if (args.slice >= 0) {
-        const uint32_t slices = plan->slices;
-        const uint64_t p = (uint64_t)args.slice * W + wave;
-        if (rest == 0 || p >= (uint64_t)rest * slices) return;
-        const uint32_t turn = (uint32_t)(p / rest);
-        group = whole + (uint32_t)(p - (uint64_t)turn * rest);
+        const uint32_t slices = plan->split.slices;
+        const PlanTurn t = plan_turn((uint32_t)args.slice, wave, W, rest, slices);
+        if (!t.any) return;
+        group = whole + t.index;
         end = group + 1;
-        first = turn == 0;
-        if (turn + 1 < slices) steps = (int32_t)plan->slice_steps;
+        first = t.turn == 0;
+        if (t.turn + 1 < slices) steps = (int32_t)plan->slice_steps;
     }
     StepRegs<FIELD, ELEC> R;
     R.set(args.c);

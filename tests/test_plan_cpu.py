@@ -1,0 +1,88 @@
+"""How an ordered push deals its groups to the waves (csrc/rpdla_plan.hpp),
+compiled for the host: the group count up to the largest slot count the ordered
+push takes, and, for group counts around whole rounds of waves, that the rounds
+and slice launches together give every group each of its turns once, a later
+turn always in a later launch, within the scratch the host allots."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2509_01741_amd", "csrc")
+
+HARNESS = r'''
+#include "rpdla_plan.hpp"
+using namespace rpdla;
+extern "C" {
+unsigned t_groups(unsigned n) { return groups_of(n); }
+void t_split(unsigned g, unsigned simds, unsigned waves, unsigned* o)
+{
+    const PlanSplit s = plan_split(g, simds, waves);
+    o[0] = s.waves; o[1] = s.whole; o[2] = s.rest; o[3] = s.slices;
+}
+long long t_bound(long long g, long long simds, long long waves) { return plan_rest_bound(g, simds, waves); }
+int t_turn(unsigned l, unsigned w, unsigned W, unsigned rest, unsigned slices, unsigned* o)
+{
+    const PlanTurn t = plan_turn(l, w, W, rest, slices);
+    o[0] = t.index; o[1] = t.turn;
+    return t.any;
+}
+unsigned t_steps(double most, unsigned slices) { return plan_slice_steps(most, slices); }
+int t_launches() { return kPlanLaunches; }
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "h.cpp").write_text(HARNESS)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + CSRC, "-o",
+                    str(d / "libplan.so"), str(d / "h.cpp")], check=True)
+    lib = C.CDLL(str(d / "libplan.so"))
+    lib.t_groups.restype = C.c_uint
+    lib.t_bound.restype = C.c_longlong
+    lib.t_bound.argtypes = [C.c_longlong] * 3
+    lib.t_steps.restype = C.c_uint
+    lib.t_steps.argtypes = [C.c_double, C.c_uint]
+    return lib
+
+
+@pytest.mark.parametrize("n", [0, 1, 63, 64, 65, 128, 2**31, 2**32 - 129, 2**32 - 65, 2**32 - 64,
+                               2**32 - 63, 2**32 - 2])
+def test_group_count(plan, n):
+    assert plan.t_groups(C.c_uint(n)) == (n + 63) // 64
+
+
+@pytest.mark.parametrize("simds,waves", [(1, 1), (4, 4), (12, 7)])
+def test_every_group_gets_its_turns(plan, simds, waves):
+    u = C.c_uint
+    most = simds * waves
+    counts = {0, 1, simds - 1, simds, simds + 1, 2 * simds - 1, 2 * simds, 2 * simds + 1, 3 * most}
+    counts |= {k * most + d for k in (1, 2, 3) for d in (-1, 0, 1)} | set(range(0, 2 * most, 3))
+    launches = plan.t_launches()
+    for g in sorted(c for c in counts if c >= 0):
+        o = (u * 4)()
+        plan.t_split(u(g), u(simds), u(waves), o)
+        W, whole, rest, slices = o
+        assert W % simds == 0 and simds <= W <= most and whole % W == 0 and whole + rest == g
+        assert slices >= 1 and rest * slices <= launches * W
+        # room for the electrons that rest between slices
+        if slices > 1:
+            assert rest <= plan.t_bound(g, simds, waves)
+        turns = [[] for _ in range(rest)]
+        for launch in range(launches):
+            for w in range(W):
+                t = (u * 2)()
+                if plan.t_turn(u(launch), u(w), u(W), u(rest), u(slices), t):
+                    turns[t[0]].append((launch, t[1]))
+        for seen in turns:
+            assert [t for _, t in seen] == list(range(slices))
+            assert all(a < b for (a, _), (b, _) in zip(seen, seen[1:]))
+        # up to a group per SIMD the host makes one slice launch
+        if g <= simds:
+            assert all(seen == [(0, 0)] for seen in turns)
+        for steps in (0.0, 1.0, 31.0, 22500.0, 2.0e9):
+            assert plan.t_steps(steps, slices) * slices >= steps
