@@ -431,7 +431,11 @@ void set_hist(rpdla::HistArgs& H, const rpdla_hist_spec& spec)
     H.width = (spec.logE_max_MeV - spec.logE_min_MeV) / (double)spec.nE;
     H.mec2 = kMeC2MeV;
     H.log_mec2 = std::log10(kMeC2MeV);
-    H.inv_width = 1.0 / H.width;
+    // Beyond 1e6 the subtraction of lo and the product with 1/width round by more
+    // than the estimate's margins allow for: not a number, so that no estimate
+    // passes its test and the definition takes every electron.
+    H.inv_width = std::max(fabs(spec.logE_min_MeV), fabs(spec.logE_max_MeV)) <= 1e6
+                      ? 1.0 / H.width : NAN;
 }
 
 // Launch a histogram kernel over n slots: all bins in LDS where they fit, two

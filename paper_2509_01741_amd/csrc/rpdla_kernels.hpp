@@ -1648,7 +1648,7 @@ struct HistArgs {
     int32_t nE, nA, angle;
     double lo, width;
     double mec2;  // electron rest energy [MeV]
-    double log_mec2, inv_width;   // of the estimate
+    double log_mec2, inv_width;   // of the estimate; inv_width NaN: no estimates
 };
 
 // atan2 in float, |error| < 1e-6: polynomial 4.4.49 of Abramowitz and Stegun
