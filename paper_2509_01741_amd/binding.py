@@ -430,7 +430,8 @@ def rpdla_run_batched(lasers, seed, cfg_base, atoms_per_cfg, atoms_per_chunk, r_
     """Returns (counts [n_cfg, 2, nE, nA], tallies [n_cfg, 6]); electron_steps,
     if given, is an int64 tensor [n_cfg] that accumulates the RK4 steps.
     chunks=(first, count) runs only those chunks of the stream
-    (rpdla_run_batched_range)."""
+    (rpdla_run_batched_range).  A workspace of the caller's own holds at least
+    the chunk's arrays (through the end of uz in rpdla_batched_workspace_layout)."""
     n_cfg = len(lasers)
     arr = (rpdla_laser * n_cfg)(*lasers)
     nb = 2 * spec.nE * spec.nA
@@ -442,6 +443,10 @@ def rpdla_run_batched(lasers, seed, cfg_base, atoms_per_cfg, atoms_per_chunk, r_
     need = rpdla_batched_workspace_bytes(n_cfg, atoms_per_chunk, k_first, k_last)
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=counts.device)
+    elif workspace.numel() < need:       # the chunk's arrays alone will do
+        lay = rpdla_batched_workspace_layout(n_cfg, atoms_per_chunk, k_first, k_last)
+        slots = n_cfg * atoms_per_chunk * (k_last - k_first + 1)
+        need = lay["uz"] + (8 * slots + 255) // 256 * 256
     first, count = (0, -1) if chunks is None else chunks
     _check(lib.rpdla_run_batched_range(arr, n_cfg, seed, cfg_base, atoms_per_cfg, atoms_per_chunk,
                                        first, count, r_factor, k_first, k_last, precision,

@@ -1058,7 +1058,7 @@ rpdla_status rpdla_run_batched_range(const rpdla_laser* cfgs, int32_t n_cfg, uin
         return fail(RPDLA_ERANGE, "chunk too large");
     const WsLayout w = ws_layout(n_cfg, atoms_per_chunk, K);
     if (ws_bytes < w.queued)
-        return fail(RPDLA_ENOMEM, "workspace %zu bytes < required %zu", ws_bytes, w.total);
+        return fail(RPDLA_ENOMEM, "workspace %zu bytes < required %zu", ws_bytes, w.queued);
     hipStream_t s = (hipStream_t)stream;
     char* base = (char*)workspace;
     rpdla::BatchArgs A;
