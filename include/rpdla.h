@@ -419,14 +419,17 @@ rpdla_status rpdla_run_batched_range(const rpdla_laser* cfgs, int32_t n_cfg, uin
  * Launch-shape autotuning.  Kernel kinds: 0 push, 1 ionize, 2 batched push.
  * A launch shape is the number of threads per block (64, 128, 192, 256) and,
  * for the persistent push kernels, a factor on the resident-block count of
- * the grid (1..8).  Shapes live in a process-wide table keyed by (kind,
+ * the grid (1..8).  The push kinds are the queue forms: rpdla_push_noalloc,
+ * rpdla_push_adaptive, and the calls that fall back to them; the ordered form
+ * has no shape to choose.  Shapes live in a process-wide table keyed by (kind,
  * field model, precision; ionize ignores precision), default 256 x 1, and
  * are read by every later launch.  Results never depend on the shape.
  *
  * rpdla_autotune samples a probe ensemble of n_atoms (64..2^24) for laser L
- * and states k_first..k_last, times ionize for each block size and the push
- * and the one-configuration batched push for each block size x grid factor
- * 1, 2 (one untimed call before each timed one, HIP events on `stream`),
+ * and states k_first..k_last, times ionize for each block size and the queue
+ * forms of the push and of the one-configuration batched push for each block
+ * size x grid factor 1, 2 (one untimed call before each timed one, HIP events
+ * on `stream`),
  * stores the fastest shapes, and writes a JSON report of all timings to
  * `report` (host buffer of report_len bytes, NUL-terminated, may be NULL).
  * It allocates and frees its own probe buffers (hipMalloc) and synchronizes

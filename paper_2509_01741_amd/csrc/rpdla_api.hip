@@ -201,7 +201,9 @@ int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Launch shapes, per (kernel kind, field model, precision): threads per block
 // and, for persistent kernels, resident blocks per CU times grid_factor.
-// Filled by rpdla_autotune / rpdla_set_launch_shape; default 256 x 1.
+// Filled by rpdla_autotune / rpdla_set_launch_shape; default 256 x 1.  The push
+// kinds are the queue forms: a wave of an ordered push works for itself on what
+// the plan deals it, so its block is only the unit of its dispatch, kOrderedBlock.
 struct Shape { int block = 256; int grid_factor = 1; };
 std::mutex g_shape_mu;
 std::map<int, Shape> g_shapes;
@@ -227,6 +229,12 @@ int persistent_blocks(K kernel, int64_t work_items, int block, int grid_factor, 
     if (need < blocks) blocks = need;
     return (int)(blocks < 1 ? 1 : blocks);
 }
+
+// Blocks of 256 threads put a wave on each of a CU's SIMDs, so that the plan's
+// whole number of waves per SIMD comes out as such; blocks of 128 and 192 do not
+// (1e5 slots, two waves for some SIMDs and none for others: 80 ms against 44,
+// in mixed precision 48 against 30; 64 is as good as 256).
+constexpr int kOrderedBlock = 256;
 
 constexpr int kKindPush = 0, kKindIonize = 1, kKindBatchPush = 2;
 
@@ -255,8 +263,7 @@ rpdla_status launch_ionize(const DevCfg& c, uint64_t seed, uint32_t cfg, uint64_
 // between slices) allocated in stream order; *done false, and nothing
 // enqueued, where there is no room for it or slot numbers do not fit 32 bits.
 template <int FIELD, class ELEC>
-rpdla_status launch_ordered(const DevCfg& c, const rpdla::PushIO& io, Shape sh, hipStream_t st,
-                            bool* done)
+rpdla_status launch_ordered(const DevCfg& c, const rpdla::PushIO& io, hipStream_t st, bool* done)
 {
     *done = false;
     int dev = 0, cus = 0, per_cu = 0;
@@ -265,8 +272,8 @@ rpdla_status launch_ordered(const DevCfg& c, const rpdla::PushIO& io, Shape sh, 
     RPDLA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     const int simds = 4 * cus;
     if (io.n_slots >= (int64_t)UINT32_MAX) return RPDLA_OK;
-    RPDLA_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, sh.block, 0));
-    const int waves_per_block = sh.block / 64;
+    RPDLA_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kOrderedBlock, 0));
+    constexpr int waves_per_block = kOrderedBlock / 64;
     const int max_waves = per_cu * waves_per_block / 4;
     if (max_waves < 1) return RPDLA_OK;
     const int64_t groups = cdiv(io.n_slots, 64);
@@ -300,7 +307,7 @@ rpdla_status launch_ordered(const DevCfg& c, const rpdla::PushIO& io, Shape sh, 
     const int last = groups <= simds ? 1 : rpdla::kPlanLaunches;
     for (int l = groups >= 2ll * simds ? -1 : 0; l < last; ++l) {
         ga.slice = l;
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(sh.block), 0, st, ga);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kOrderedBlock), 0, st, ga);
     }
     const hipError_t e = hipGetLastError();
     const hipError_t fe = hipFreeAsync(base, st);
@@ -377,14 +384,13 @@ rpdla_status check_push_args(const rpdla_laser* L, int32_t precision, int64_t n_
 }
 
 // The ordered push of slots io in the form asked for; *done false where it does
-// not apply (few slots, no room for its scratch).
+// not apply (no room for its scratch, slot numbers beyond 32 bits).
 template <int FIELD>
 rpdla_status ordered_push(const DevCfg& c, int prec, const rpdla::PushIO& io, hipStream_t st,
                           bool* done)
 {
-    const Shape sh = get_shape(kKindPush, FIELD, prec);
-    if (prec == RPDLA_FP64) return launch_ordered<FIELD, rpdla::ElecF64>(c, io, sh, st, done);
-    if constexpr (FIELD < 20) return launch_ordered<FIELD, rpdla::ElecMixed>(c, io, sh, st, done);
+    if (prec == RPDLA_FP64) return launch_ordered<FIELD, rpdla::ElecF64>(c, io, st, done);
+    if constexpr (FIELD < 20) return launch_ordered<FIELD, rpdla::ElecMixed>(c, io, st, done);
     *done = false;
     return RPDLA_OK;                           // the queue reports what is not supported
 }
@@ -393,9 +399,8 @@ template <int FIELD>
 rpdla_status ordered_push_rr(const DevCfg& c, bool rr, const rpdla::PushIO& io, hipStream_t st,
                              bool* done)
 {
-    const Shape sh = get_shape(kKindPush, FIELD, RPDLA_FP64);
-    return rr ? launch_ordered<FIELD, rpdla::ElecRR<true>>(c, io, sh, st, done)
-              : launch_ordered<FIELD, rpdla::ElecRR<false>>(c, io, sh, st, done);
+    return rr ? launch_ordered<FIELD, rpdla::ElecRR<true>>(c, io, st, done)
+              : launch_ordered<FIELD, rpdla::ElecRR<false>>(c, io, st, done);
 }
 
 // Clear the work counters q[kQueueWords] (a fill kernel, no memset node) and
@@ -879,8 +884,8 @@ rpdla_status run_batched_impl(const rpdla::BatchArgs& A, rpdla::BatchPlanArgs P,
         int dev = 0, cus = 0, per_cu = 0;
         RPDLA_HIP(hipGetDevice(&dev));
         RPDLA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        RPDLA_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kgroup, sh.block, 0));
-        const int wpb = sh.block / 64;
+        RPDLA_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kgroup, kOrderedBlock, 0));
+        constexpr int wpb = kOrderedBlock / 64;
         P.simds = (uint32_t)(4 * cus);
         P.max_waves = (uint32_t)std::min<int64_t>(per_cu * wpb / 4, kBatchWaves / (4 * cus));
         if (P.max_waves < 1) P.plan = nullptr;
@@ -903,7 +908,7 @@ rpdla_status run_batched_impl(const rpdla::BatchArgs& A, rpdla::BatchPlanArgs P,
         const int64_t groups = slots / 64 + A.n_cfg;
         const int last = groups <= (int64_t)P.simds ? 1 : rpdla::kPlanLaunches;
         for (int l = groups >= 2ll * P.simds ? -1 : 0; l < last; ++l)
-            hipLaunchKernelGGL(kgroup, dim3(grid_g), dim3(sh.block), 0, st, A, A.cfgs, P, l);
+            hipLaunchKernelGGL(kgroup, dim3(grid_g), dim3(kOrderedBlock), 0, st, A, A.cfgs, P, l);
     };
 
     auto enqueue_chunk = [&](hipStream_t st) -> rpdla_status {
@@ -1199,7 +1204,7 @@ rpdla_status rpdla_autotune(const rpdla_laser* L, int32_t precision, int64_t n_a
     hipStream_t s = (hipStream_t)stream;
     const int K = k_last - k_first + 1;
     const int64_t ns = n_atoms * K;
-    DevBuf bx, by, bz, btb, bo[6], bcnt, btal, bws;
+    DevBuf bx, by, bz, btb, bo[6], bq, bcnt, btal, bws;
     RPDLA_HIP(hipMalloc(&bx.p, n_atoms * 8)); RPDLA_HIP(hipMalloc(&by.p, n_atoms * 8));
     RPDLA_HIP(hipMalloc(&bz.p, n_atoms * 8)); RPDLA_HIP(hipMalloc(&btb.p, ns * 8));
     for (auto& b : bo) RPDLA_HIP(hipMalloc(&b.p, ns * 8));
@@ -1230,8 +1235,9 @@ rpdla_status rpdla_autotune(const rpdla_laser* L, int32_t precision, int64_t n_a
         set_shape(kKindIonize, field, 0, bsh);
         js += "}, \"ionize_best\": \"" + std::to_string(bsh.block) + "x1\"";
     }
-    // push: threads per block x persistent grid factor
+    // push by its queue: threads per block x persistent grid factor
     {
+        RPDLA_HIP(hipMalloc(&bq.p, rpdla::kQueueWords * sizeof(unsigned long long)));
         const Shape keep = get_shape(kKindPush, field, precision);
         float best = 1e30f; Shape bsh = keep;
         js += ", \"push_ms\": {";
@@ -1240,8 +1246,9 @@ rpdla_status rpdla_autotune(const rpdla_laser* L, int32_t precision, int64_t n_a
             for (int gf = 1; gf <= 2; ++gf) {
                 set_shape(kKindPush, field, precision, Shape{blocks[bi], gf});
                 float ms = 0;
-                st = time_ms(s, [&] { return rpdla_push(L, precision, ns, tb, x, y, z, K, o[0], o[1], o[2],
-                                                        o[3], o[4], o[5], stream); }, &ms);
+                st = time_ms(s, [&] { return enqueue_push(L, precision, ns, tb, x, y, z, K, o[0], o[1],
+                                                          o[2], o[3], o[4], o[5],
+                                                          (unsigned long long*)bq.p, s); }, &ms);
                 if (st != RPDLA_OK) { set_shape(kKindPush, field, precision, keep); return st; }
                 js += (firstc ? "\"" : ", \"") + std::to_string(blocks[bi]) + "x" + std::to_string(gf) +
                       "\": " + std::to_string(ms);
@@ -1252,10 +1259,11 @@ rpdla_status rpdla_autotune(const rpdla_laser* L, int32_t precision, int64_t n_a
         set_shape(kKindPush, field, precision, bsh);
         js += "}, \"push_best\": \"" + std::to_string(bsh.block) + "x" + std::to_string(bsh.grid_factor) + "\"";
     }
-    // batched push (one configuration through the batched path)
+    // batched push by its queue (one configuration through the batched path, with a
+    // workspace of the chunk's arrays alone)
     {
         rpdla_hist_spec sp{64, 36, -3.0, 4.0, RPDLA_ANG_POLAR};
-        const size_t wsb = rpdla_batched_workspace_bytes(1, n_atoms, k_first, k_last);
+        const size_t wsb = ws_layout(1, n_atoms, K).queued;
         RPDLA_HIP(hipMalloc(&bws.p, wsb));
         RPDLA_HIP(hipMalloc(&bcnt.p, 2 * 64 * 36 * 8));
         RPDLA_HIP(hipMalloc(&btal.p, 6 * 8));
