@@ -446,13 +446,12 @@ rpdla_status rpdla_get_launch_shape(int32_t kernel, int32_t field, int32_t preci
 
 /* Resources and occupancy of one kernel (kinds as above; field 1, 3, 5, 10 or
  * 11; precision RPDLA_FP64 or RPDLA_MIXED, ignored for ionize) on the current
- * device (the push kinds in their queue form), at its current launch shape:
- * vector registers per lane (*vgprs), private scratch bytes per lane
- * (*scratch_bytes, nonzero only when registers spill) and resident waves per SIMD (*waves_per_simd, from the runtime's
- * occupancy query; a CU has four SIMDs).  The batched push is sized with the
- * per-configuration step counters of 64 configurations in LDS.  Field 21, 23
- * or 25 (linear focus) is accepted for the FP64 forms.  Host pointers, all
- * non-NULL; RPDLA_EINVAL
+ * device: the ordered kernels that rpdla_push and rpdla_run_batched run, and the
+ * ionization at its current launch shape.  Vector registers per lane (*vgprs),
+ * private scratch bytes per lane (*scratch_bytes, nonzero only when registers
+ * spill) and resident waves per SIMD (*waves_per_simd, from the runtime's
+ * occupancy query; a CU has four SIMDs).  Field 21, 23 or 25 (linear focus) is
+ * accepted for the FP64 forms.  Host pointers, all non-NULL; RPDLA_EINVAL
  * otherwise, RPDLA_EHIP when the runtime query fails. */
 rpdla_status rpdla_kernel_occupancy(int32_t kernel, int32_t field, int32_t precision,
                                     int32_t* vgprs, int32_t* scratch_bytes,

@@ -1338,13 +1338,12 @@ rpdla_status rpdla_histogram2d(int64_t n, const double* a, const double* b, cons
 namespace {
 
 template <typename K>
-rpdla_status kernel_info(K kern, int block, size_t lds, int32_t* vgprs, int32_t* scratch,
-                         double* waves)
+rpdla_status kernel_info(K kern, int block, int32_t* vgprs, int32_t* scratch, double* waves)
 {
     hipFuncAttributes fa;
     RPDLA_HIP(hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(kern)));
     int per_cu = 0;
-    RPDLA_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, block, lds));
+    RPDLA_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, block, 0));
     *vgprs = fa.numRegs;
     *scratch = (int32_t)fa.localSizeBytes;
     *waves = (double)per_cu * (double)(block / 64) / 4.0;   // four SIMDs per CU
@@ -1354,23 +1353,18 @@ rpdla_status kernel_info(K kern, int block, size_t lds, int32_t* vgprs, int32_t*
 template <int FIELD>
 rpdla_status field_kernel_info(int kind, bool mixed, int32_t* v, int32_t* s, double* w)
 {
-    const Shape sh = get_shape(kind, FIELD, kind == kKindIonize ? 0 : (mixed ? 1 : 0));
     if (kind == kKindIonize)
-        return kernel_info(rpdla::ionize_kernel<FIELD>, sh.block, 0, v, s, w);
+        return kernel_info(rpdla::ionize_kernel<FIELD>, get_shape(kind, FIELD, 0).block, v, s, w);
     if constexpr (FIELD > 20) {
         if (mixed) return fail(RPDLA_EUNSUPPORTED, "the linearly polarized focus has no mixed form");
-        const size_t lds = (size_t)rpdla::kMaxCfg * sizeof(unsigned long long);
+    } else if (mixed) {
         return kind == kKindPush
-                   ? kernel_info(rpdla::push_kernel<FIELD, rpdla::ElecF64>, sh.block, 0, v, s, w)
-                   : kernel_info(rpdla::batch_push_kernel<FIELD, rpdla::ElecF64>, sh.block, lds, v, s, w);
-    } else {
-    if (kind == kKindPush)
-        return mixed ? kernel_info(rpdla::push_kernel<FIELD, rpdla::ElecMixed>, sh.block, 0, v, s, w)
-                     : kernel_info(rpdla::push_kernel<FIELD, rpdla::ElecF64>, sh.block, 0, v, s, w);
-    const size_t lds = (size_t)rpdla::kMaxCfg * sizeof(unsigned long long);
-    return mixed ? kernel_info(rpdla::batch_push_kernel<FIELD, rpdla::ElecMixed>, sh.block, lds, v, s, w)
-                 : kernel_info(rpdla::batch_push_kernel<FIELD, rpdla::ElecF64>, sh.block, lds, v, s, w);
+                   ? kernel_info(rpdla::push_group_kernel<FIELD, rpdla::ElecMixed>, kOrderedBlock, v, s, w)
+                   : kernel_info(rpdla::batch_group_kernel<FIELD, rpdla::ElecMixed>, kOrderedBlock, v, s, w);
     }
+    return kind == kKindPush
+               ? kernel_info(rpdla::push_group_kernel<FIELD, rpdla::ElecF64>, kOrderedBlock, v, s, w)
+               : kernel_info(rpdla::batch_group_kernel<FIELD, rpdla::ElecF64>, kOrderedBlock, v, s, w);
 }
 
 }  // namespace

@@ -113,8 +113,9 @@ __global__ void __launch_bounds__(256, IonizeWaves<FIELD>::value) batch_ionize_k
 // spilling them.  The step's vector registers hold electron state only.  Final
 // momenta go to the chunk's u arrays (NaN for invalid births; unborn and
 // inactive slots are not written).
-// Register budgets: as the single push, except that the mixed form keeps 6
-// waves (its queue switching needs a few more registers than 7 waves leave).
+// Register budgets of the queue push: as the single push, except that the mixed
+// form keeps 6 waves (its queue switching needs a few more registers than 7 waves
+// leave).  The ordered push below has the single push's.
 template <class E, int FIELD>
 struct BatchWaves { static constexpr int value = ElecWaves<E, FIELD>::value; };
 template <int FIELD> struct BatchWaves<ElecMixed, FIELD> { static constexpr int value = 6; };
@@ -380,20 +381,22 @@ __global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) batch_gr
     StepRegs<FIELD, ELEC> R;
     const int64_t per_cfg = A.apc * A.K;
     for (; group < end; group += W) {
+        // what each lane needs before the step loop and after it, formed anew
         const uint32_t c = P.groups[group].cfg;
-        const uint32_t lane = (uint32_t)__lane_id();
-        const uint32_t at = P.groups[group].first + lane;
-        const bool used = at < plan->born[c];
         const size_t stride = (size_t)rest * 64;
-        uint64_t* const state = P.state + (size_t)(group - whole) * 64 + lane;
-        int64_t js = 0;
-        if (used) js = (int64_t)c * per_cfg + (int64_t)P.order[plan->base[c] + at];
+        auto state = [&]() { return P.state + (size_t)(group - whole) * 64 + fresh_lane(); };
+        auto slot = [&]() -> int64_t {       // -1 for a lane without one
+            const uint32_t at = P.groups[group].first + fresh_lane();
+            return at < plan->born[c] ? (int64_t)c * per_cfg + (int64_t)P.order[plan->base[c] + at]
+                                      : -1;
+        };
         ELEC e;
         e.left = 0;
         if (!first) {
-            get_state(state, stride, e);
+            get_state(state(), stride, e);
         } else {
-            if (used) {
+            const int64_t js = slot();
+            if (js >= 0) {
                 const int64_t ia = (int64_t)c * A.apc + (js - (int64_t)c * per_cfg) / A.K;
                 if (!elec_init(cfgs[c], e, A.tb[js], A.x[ia], A.y[ia], A.z[ia])) {
                     const double q = __builtin_nan("");
@@ -407,18 +410,19 @@ __global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) batch_gr
             if (A.steps) {
                 unsigned long long n = e.left > 0 ? (unsigned long long)e.left : 0ull;
                 for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
-                if (lane == 0 && n) atomicAdd(&A.steps[c], n);
+                if (fresh_lane() == 0 && n) atomicAdd(&A.steps[c], n);
             }
         }
         const bool runs = e.left > 0;
         R.set(cfgs[c]);
         run_steps<FIELD, true>(R.c, e, R.k, steps);
         if (runs && e.left == 0) {
+            const int64_t js = slot();
             double ux, uy, uz, xf, yf, zf;
             elec_final(cfgs[c], e, ux, uy, uz, xf, yf, zf);
             A.ux[js] = ux; A.uy[js] = uy; A.uz[js] = uz;
         }
-        if (steps != 0x7fffffff) put_state(state, stride, e);
+        if (steps != 0x7fffffff) put_state(state(), stride, e);
     }
 }
 

@@ -1212,12 +1212,14 @@ __device__ inline int64_t queue_take_xcd(unsigned long long* queue, int64_t n, b
 }
 
 // Waves per SIMD each electron form is compiled for (its register budget):
-// FP64 RK4 4 (5 needs a few spills and measured no faster), mixed 6 (lands
-// at 7 without spills, 1-5% faster than 5), controlled-step unbounded (six
-// stored stages, 2 waves).  The linear focus at order 5 needs more: at 4 waves it
-// kept 63 doubles in scratch inside the step (3e5 slots 436 ms, now 301).
+// FP64 RK4 4 (5 needs a few spills and measured no faster), mixed 7 (4 to 7
+// within 1%), controlled-step unbounded (six stored stages, 2 waves).  The linear
+// focus needs more: order 5 at 4 waves kept 63 doubles in scratch inside the step
+// (3e5 slots 436 ms, now 301), order 3 up to 27 registers, some inside it (at 3
+// waves, none: the queue form of 6e5 slots of 1000 steps 22.6 -> 21.6 ms, the
+// ordered one 19.0 -> 18.8).
 template <class E, int FIELD>
-struct ElecWaves { static constexpr int value = FIELD == 25 ? 3 : 4; };
+struct ElecWaves { static constexpr int value = FIELD == 23 || FIELD == 25 ? 3 : 4; };
 template <int FIELD> struct ElecWaves<ElecMixed, FIELD> { static constexpr int value = 7; };
 template <int FIELD> struct ElecWaves<ElecDP, FIELD> { static constexpr int value = 1; };
 template <bool RR> struct ElecWaves<ElecRR<RR>, 25> { static constexpr int value = 2; };
@@ -1510,6 +1512,14 @@ __device__ inline void get_state(const uint64_t* at, size_t stride, ELEC& e)
     __builtin_memcpy(&e, w, sizeof(ELEC));
 }
 
+// The number of this lane, computed anew: nothing holds it over a step loop.
+__device__ inline uint32_t fresh_lane()
+{
+    uint32_t lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+    return lane;
+}
+
 // Up to `steps` steps of a wave's electrons.  Neighbours in the order have
 // nearly the same number of steps left, so all but a few go through a loop with
 // no test on any lane, one step length and two steps a turn (the new state then
@@ -1518,16 +1528,29 @@ __device__ inline void get_state(const uint64_t* at, size_t stride, ELEC& e)
 // there instead of 607 and its branches, and one wave on a SIMD issues one every 4.3 cycles
 // instead of 5.1 (8192 slots 36.0 -> 29.4 ms, 2e4 slots with radiation reaction
 // 76.9 -> 65.5 ms, 2e6 slots 4% faster).  The mixed form, several waves to a
-// SIMD, is no faster with it, in twice the code.  It issues its float
-// instructions faster than one in four cycles, and then what bounds its loop
-// (435 instructions, 2.4 KB) is their fetch: with where the loop begins in a
-// window of 32 bytes, 6e5 slots take 122 to 141 ms and a sweep of 64 small
-// configurations 162 to 173 ms (8 places; the double-precision loops do not care),
-// so its place is stated (with that, 4 to 7 waves are within 1% of each other).
+// SIMD, is no faster with it, in twice the code.  Its time depends on where its
+// loop (435 instructions, 2.4 KB) lies: with the eight word offsets in a window
+// of 32 bytes 6e5 slots took 122 to 141 ms and a sweep of 64 configurations of
+// 10,240 slots 149 to 170 ms (150, 149 with one and three words, 161 to 170 with
+// the others; order 3 135 to 141, order 1 107 to 109; the double-precision loops
+// do not care).  Instruction fetch is the likely reason; no counter was read for
+// it.  The alignment and the words below move the loop to the best of the eight.
+// The compiler puts the loop's first instructions between, so the number holds
+// for the kernels as they stand: after a change to them it is measured again.
+// What only the last step of an electron needs waits in LDS during the loop
+// without tests, and what a lane needs before and after its steps (its number,
+// its slot) is formed anew: held in registers, these put 28 to 52 bytes a lane
+// into scratch (at order 5, 4 and 7 waves).  ElecRR's loop came out with spills
+// inside it that way and without any when the last step stays in registers.
 template <int FIELD, bool BATCH, class CFG, class ELEC>
 __device__ inline void run_steps(const CFG& c, ELEC& e, const fm::Coef& k, int32_t steps)
 {
     if constexpr (!std::is_same<ELEC, ElecMixed>::value) {
+        // what the loop without tests does not read waits in LDS
+        constexpr bool kPark = std::is_same<ELEC, ElecF64>::value;
+        __shared__ double park_last[256];
+        __shared__ int32_t park_left[256];
+        const uint32_t park = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
         int32_t least = e.left > 0 ? e.left : 0x7fffffff;
         for (int o = 32; o > 0; o >>= 1) {
             const int32_t other = __shfl_xor(least, o);
@@ -1537,18 +1560,28 @@ __device__ inline void run_steps(const CFG& c, ELEC& e, const fm::Coef& k, int32
         if (least == 0x7fffffff) return;
         const int32_t full = least - 1 < steps ? least - 1 : steps;
         int32_t n = full;
+        if (e.left > 0) e.left -= full;
+        if constexpr (kPark) {
+            const uint32_t at = park + fresh_lane();
+            park_last[at] = e.h_last;
+            park_left[at] = e.left;
+        }
 #pragma unroll 1
         for (; n > 1; n -= 2) {
             elec_step<FIELD, true, BATCH>(c, e, k);
             elec_step<FIELD, true, BATCH>(c, e, k);
         }
         if (n > 0) elec_step<FIELD, true, BATCH>(c, e, k);
-        if (e.left > 0) e.left -= full;
+        if constexpr (kPark) {
+            const uint32_t at = park + fresh_lane();
+            e.h_last = park_last[at];
+            e.left = park_left[at];
+        }
         steps -= full;
     }
     if constexpr (std::is_same<ELEC, ElecMixed>::value) {
         if constexpr (BATCH)
-            asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
+            asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
         else
             asm volatile(".p2align 5");
     }
@@ -1602,9 +1635,8 @@ __global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_gro
     for (; group < end; group += W) {
         ELEC e;
         e.left = 0;
-        const uint32_t lane = (uint32_t)__lane_id();
-        const uint32_t at = group * 64u + lane;
         {
+            const uint32_t lane = fresh_lane(), at = group * 64u + lane;
             const GroupArgsPtr ga = group_args();
             const size_t stride = (size_t)rest * 64;
             if (!first) {
@@ -1625,6 +1657,7 @@ __global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_gro
         const bool runs = e.left > 0;
         run_steps<FIELD, false>(R.c, e, R.k, steps);
         {
+            const uint32_t lane = fresh_lane(), at = group * 64u + lane;
             const GroupArgsPtr ga = group_args();
             if (runs && e.left == 0) {
                 const PushIO io = ga->io;
