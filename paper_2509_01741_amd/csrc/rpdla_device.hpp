@@ -304,6 +304,49 @@ __device__ inline Cx<double> lp_sum(const lp::Term (&T)[N], const double* sp, co
     return u;
 }
 
+// The same with what is fused stated, as in radius2.  An electron's steps run in
+// three copies of the field (two to a turn, the odd one, the last one), and which
+// copy a step takes depends on the electron's neighbours in the order.  Left to
+// the compiler the copies of order 5 rounded differently in the plain push, so
+// that an electron's result changed in its last digits with the slots around it
+// and from run to run.  That push takes this form (and 3e5 slots of 1000 steps
+// 14.1 -> 12.3 ms with it); the copies of the others agree as they are, which is
+// tested, and keep their bits.
+__device__ inline Cx<double> lp_cmul(Cx<double> a, Cx<double> b)
+{
+#pragma clang fp contract(off)
+    return {fma(a.re, b.re, -(a.im * b.im)), fma(a.re, b.im, a.im * b.re)};
+}
+
+// u + the coefficient of f power n.
+template <int N>
+__device__ inline Cx<double> lp_add_coef(Cx<double> u, const lp::Term (&T)[N], int n,
+                                         const double* sp, const double* ep)
+{
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+        if (T[t].n == n) {
+            const double w = ep[T[t].j] * sp[T[t].m];
+            if (T[t].re != 0.0) u.re = fma(T[t].re, w, u.re);
+            if (T[t].im != 0.0) u.im = fma(T[t].im, w, u.im);
+        }
+    }
+    return u;
+}
+
+template <int N, int NMIN, int NMAX>
+__device__ inline Cx<double> lp_sum_stated(const lp::Term (&T)[N], const double* sp, const double* ep,
+                                    Cx<double> q)
+{
+    Cx<double> u = lp_add_coef(Cx<double>{0.0, 0.0}, T, NMAX, sp, ep);
+#pragma unroll
+    for (int n = NMAX - 1; n >= NMIN; --n) u = lp_add_coef(lp_cmul(u, q), T, n, sp, ep);
+#pragma unroll
+    for (int n = 0; n < NMIN; ++n) u = lp_cmul(u, q);
+    return u;
+}
+
 // Upper bound of |sum_n c_n Q_n| / (g): sum of the coefficient magnitudes
 // times |q|^n.
 template <int N>
@@ -323,6 +366,10 @@ __device__ inline double lp_bound_sum(const lp::Term (&T)[N], const double* sp, 
 #define RPDLA_LP_SUM(ORD, NAME, sp, ep, q)                                                   \
     lp_sum<lp::k##NAME##_O##ORD##_N, lp::k##NAME##_O##ORD##_NMIN,                            \
            lp::k##NAME##_O##ORD##_NMAX>(lp::k##NAME##_O##ORD, sp, ep, q)
+
+#define RPDLA_LP_STATED(NAME, sp, ep, q)                                                     \
+    lp_sum_stated<lp::k##NAME##_O5_N, lp::k##NAME##_O5_NMIN, lp::k##NAME##_O5_NMAX>(         \
+        lp::k##NAME##_O5, sp, ep, q)
 
 template <int ORDER>
 __device__ inline void lp_sums(const double* sp, const double* ep, Cx<double> q, Cx<double>& ux0,
@@ -385,6 +432,37 @@ __device__ inline void lp_field_f64(const CFG& c, double X, double Y, double Z, 
     }
 }
 
+// The order-5 field with its magnetic part, what is fused stated.
+template <class CFG>
+__device__ inline void lp_field_stated(const CFG& c, double X, double Y, double Z, double d,
+                                       double& ax, double& ay, double& az, double& bx, double& by,
+                                       double& bz)
+{
+#pragma clang fp contract(off)
+    const double rx = X * c.inv_w0n, ry = Y * c.inv_w0n, rx2 = rx * rx;
+    const double s = fma(ry, ry, rx2);
+    const double zeta = Z * c.inv_zrn;
+    const double iD = fm::rcp_f64(fma(zeta, zeta, 1.0));
+    const double Psi = fma(-(s * zeta), iD, c.phi0 + d);
+    const double sg = d * c.inv_T0n;
+    const double g = c.a0 * fm::exp_fin_f64(fma(-s, iD, -(sg * sg)));
+    double sn, cs;
+    fm::sincos_f64(Psi, &sn, &cs);
+    const Cx<double> base{g * cs, g * sn}, q{iD, zeta * iD};
+    double sp[6], ep[8];
+    lp_powers(c, s, sp, ep);
+    const Cx<double> ux0 = RPDLA_LP_STATED(AX0, sp, ep, q), uxr = RPDLA_LP_STATED(AXR, sp, ep, q);
+    const Cx<double> uz = RPDLA_LP_STATED(AZ, sp, ep, q), uby = RPDLA_LP_STATED(BY, sp, ep, q);
+    const Cx<double> us = RPDLA_LP_STATED(S, sp, ep, q);
+    const double wxr = lp_cmul(base, uxr).re;
+    ax = c.er_scale * fma(rx2, wxr, lp_cmul(base, ux0).re);
+    ay = c.er_scale * rx * ry * wxr;
+    az = c.ez_scale * rx * lp_cmul(base, uz).re;
+    bx = 0.0;
+    by = lp_cmul(base, uby).re;
+    bz = c.eps * ry * lp_cmul(base, us).im;
+}
+
 // Spatial bound M with |a(X, tau)|^2 <= M^2 exp(-2 s^2) for the linear focus.
 template <int ORDER, class CFG>
 __device__ inline double lp_bound2(const CFG& c, double X, double Y, double Z)
@@ -417,7 +495,7 @@ __device__ inline double lp_bound2(const CFG& c, double X, double Y, double Z)
 // Field of any model in double precision (test models included) at position
 // (X, Y, Z) and retarded time d = tau - Z; with LO the retarded time is the
 // unevaluated sum d + dl (the radial focus keeps the pair, the others add it).
-template <int FIELD, bool WANT_B, class CFG, bool LO = false, int AXIS = 0>
+template <int FIELD, bool WANT_B, class CFG, bool LO = false, int AXIS = 0, bool STATED = false>
 __device__ inline void field_f64(const CFG& c, double X, double Y, double Z, double d,
                                  double& ax, double& ay, double& az, double& bx, double& by,
                                  double& bz, double dl = 0.0, const fm::Coef& k = fm::kCoef)
@@ -435,6 +513,8 @@ __device__ inline void field_f64(const CFG& c, double X, double Y, double Z, dou
         const double e = c.a0 * fm::exp_fin_f64(-s * s) * cs;
         ax = e; ay = 0.0; az = 0.0;
         bx = 0.0; by = e; bz = 0.0;
+    } else if constexpr (FIELD == 25 && WANT_B && STATED) {
+        lp_field_stated(c, X, Y, Z, d, ax, ay, az, bx, by, bz);
     } else if constexpr (FIELD == 21 || FIELD == 23 || FIELD == 25) {
         lp_field_f64<FIELD - 20, WANT_B, CFG>(c, X, Y, Z, d, ax, ay, az, bx, by, bz);
     } else {

@@ -539,7 +539,7 @@ __device__ inline int64_t queue_take(unsigned long long* queue, bool need)
 // rounding of D itself rather than that of tau and Z separately (each up to
 // ~1e3 over the window).
 // ---------------------------------------------------------------------------
-template <int FIELD, int AXIS, class CFG>
+template <int FIELD, int AXIS, bool STATED = false, class CFG>
 __device__ inline void rhs_f64(const CFG& c, double d, double dl, double X, double Y, double Z,
                                double ux, double uy, double uz, double& dX, double& dY,
                                double& dZ, double& dux, double& duy, double& duz,
@@ -559,7 +559,7 @@ __device__ inline void rhs_f64(const CFG& c, double d, double dl, double X, doub
         duz = -fma(pb, fma(dY, Y, dX * X), az);
     } else {
         double ax, ay, az, bx, by, bz;
-        field_f64<FIELD, true, CFG>(c, X, Y, Z, d + dl, ax, ay, az, bx, by, bz);
+        field_f64<FIELD, true, CFG, false, 0, STATED>(c, X, Y, Z, d + dl, ax, ay, az, bx, by, bz);
         dux = -(ax + dY * bz - dZ * by);
         duy = -(ay + dZ * bx - dX * bz);
         duz = -(az + dX * by - dY * bx);
@@ -630,19 +630,19 @@ __device__ inline void elec_step(const CFG& c, ElecF64& e, const fm::Coef& k)
     const double hs = (!FULL && e.left == 1) ? e.h_last : c.hn;
     const double hh = 0.5 * hs;
     double kX, kY, kZ, kx, ky, kz, aX, aY, aZ, ax, ay, az;
-    rhs_f64<FIELD, 1>(c, e.D, -e.cD, e.X, e.Y, e.Z, e.ux, e.uy, e.uz, kX, kY, kZ, kx, ky, kz, k);
+    rhs_f64<FIELD, 1, true>(c, e.D, -e.cD, e.X, e.Y, e.Z, e.ux, e.uy, e.uz, kX, kY, kZ, kx, ky, kz, k);
     aX = kX; aY = kY; aZ = kZ; ax = kx; ay = ky; az = kz;
-    rhs_f64<FIELD, 0>(c, e.D, fma(hh, 1.0 - kZ, -e.cD), e.X + hh * kX, e.Y + hh * kY,
+    rhs_f64<FIELD, 0, true>(c, e.D, fma(hh, 1.0 - kZ, -e.cD), e.X + hh * kX, e.Y + hh * kY,
                    e.Z + hh * kZ, e.ux + hh * kx, e.uy + hh * ky, e.uz + hh * kz, kX, kY, kZ, kx,
                    ky, kz, k);
     aX += 2.0 * kX; aY += 2.0 * kY; aZ += 2.0 * kZ;
     ax += 2.0 * kx; ay += 2.0 * ky; az += 2.0 * kz;
-    rhs_f64<FIELD, 0>(c, e.D, fma(hh, 1.0 - kZ, -e.cD), e.X + hh * kX, e.Y + hh * kY,
+    rhs_f64<FIELD, 0, true>(c, e.D, fma(hh, 1.0 - kZ, -e.cD), e.X + hh * kX, e.Y + hh * kY,
                    e.Z + hh * kZ, e.ux + hh * kx, e.uy + hh * ky, e.uz + hh * kz, kX, kY, kZ, kx,
                    ky, kz, k);
     aX += 2.0 * kX; aY += 2.0 * kY; aZ += 2.0 * kZ;
     ax += 2.0 * kx; ay += 2.0 * ky; az += 2.0 * kz;
-    rhs_f64<FIELD, 0>(c, e.D, fma(hs, 1.0 - kZ, -e.cD), e.X + hs * kX, e.Y + hs * kY,
+    rhs_f64<FIELD, 0, true>(c, e.D, fma(hs, 1.0 - kZ, -e.cD), e.X + hs * kX, e.Y + hs * kY,
                    e.Z + hs * kZ, e.ux + hs * kx, e.uy + hs * ky, e.uz + hs * kz, kX, kY, kZ, kx,
                    ky, kz, k);
     const double w6 = hs * (1.0 / 6.0);
