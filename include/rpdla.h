@@ -209,8 +209,11 @@ rpdla_status rpdla_birth_phase(const rpdla_laser* L, int64_t n_slots, const doub
  * The born slots are pushed in the order of their step counts, 64 neighbours
  * to a wave; beyond one wave per SIMD (65536 slots on 256 CUs) the last waves'
  * worth runs in time slices (some 35 launches).  Stream-ordered device scratch:
- * 20 KB and 4 bytes a slot, with slices up to 70 MB more.  When that cannot be
- * allocated, or from 2^32 - 1 slots on, lanes draw their slots from a work
+ * 20 KB and 4 bytes a slot; with slices, what two rounds of resident waves
+ * hold in electrons of 72 (mixed), 128 or 136 bytes (radiation reaction): 64 to
+ * 90 MB on 256 CUs, or less for fewer slots.  When that cannot be allocated, for
+ * 2^18 slots and more of a window of at most 3 to 16 steps (more with more
+ * slots), or from 2^32 - 1 slots on, lanes draw their slots from a work
  * queue instead, which needs 1 KiB (RPDLA_EHIP if that fails too): the slots are
  * split into eight contiguous parts with a counter each, and a wave draws from
  * the part of the XCD it runs on (the hardware XCC_ID register) before it moves
@@ -370,7 +373,9 @@ rpdla_status rpdla_histogram2d(int64_t n, const double* a, const double* b, cons
  * until the stream reaches the end of this call.  A smaller one that holds the
  * chunk's arrays (through the end of uz, see the layout below) is accepted: the
  * push then is one persistent launch with a work counter per configuration,
- * with the same results.
+ * with the same results.  So it is for chunks of up to half a million slots
+ * whose windows have few steps (at most 32 to 128, in mixed precision 64 to 256,
+ * more with more slots).
  * EINVAL on bad configurations or sizes; RPDLA_ENOMEM when ws_bytes is too
  * small; RPDLA_EUNSUPPORTED for n_cfg > 64.
  * ------------------------------------------------------------------------ */

@@ -102,7 +102,7 @@ rpdla_status check_laser(const rpdla_laser* L)
     for (int i = 0; i < 3; ++i)
         if (!(is_fin(L->test_E[i]) && is_fin(L->test_B[i])))
             return fail(RPDLA_EINVAL, "test fields must be finite");
-    const double panels = (L->t_before + L->t_after) / L->dt;
+    const double panels = (L->t_before + L->t_after) / L->dt;   // window_steps
     if (!(panels < 2.0e9)) return fail(RPDLA_ERANGE, "window / dt = %.3g steps is too many", panels);
     return RPDLA_OK;
 }
@@ -183,6 +183,9 @@ DevCfg make_cfg(const rpdla_laser* L, bool rates = false)
     c.ad_max_steps = 10000000;
     return c;
 }
+
+// The window in steps.
+double window_steps(const rpdla_laser* L) { return (L->t_before + L->t_after) / L->dt; }
 
 void laser_defaults(rpdla_laser* L, double lambda, double w0, double tau)
 {
@@ -624,7 +627,7 @@ rpdla_status rpdla_push(const rpdla_laser* L, int32_t precision, int64_t n_slots
                                       ux, uy, uz, xf, yf, zf);
     if (st != RPDLA_OK || n_slots == 0) return st;
     hipStream_t s = (hipStream_t)stream;
-    {
+    if (!rpdla::push_by_queue(n_slots, window_steps(L))) {
         const DevCfg c = make_cfg(L);
         const rpdla::PushIO io{t_birth, x0, y0, z0, slots_per_atom, n_slots, ux, uy, uz, xf, yf,
                                zf, nullptr};
@@ -687,18 +690,20 @@ rpdla_status rpdla_push_rr(const rpdla_laser* L, int32_t radiation_reaction, int
     rpdla::PushIO io{t_birth, x0, y0, z0, slots_per_atom, n_slots, ux, uy, uz, xf, yf, zf, nullptr,
                      chi_max};
     const bool rr = radiation_reaction == 1;
-    bool done = false;
-    switch (L->field) {
-    case 1: st = ordered_push_rr<1>(c, rr, io, s, &done); break;
-    case 3: st = ordered_push_rr<3>(c, rr, io, s, &done); break;
-    case 5: st = ordered_push_rr<5>(c, rr, io, s, &done); break;
-    case 10: st = ordered_push_rr<10>(c, rr, io, s, &done); break;
-    case 21: st = ordered_push_rr<21>(c, rr, io, s, &done); break;
-    case 23: st = ordered_push_rr<23>(c, rr, io, s, &done); break;
-    case 25: st = ordered_push_rr<25>(c, rr, io, s, &done); break;
-    default: st = ordered_push_rr<11>(c, rr, io, s, &done); break;
+    if (!rpdla::push_by_queue(n_slots, window_steps(L))) {
+        bool done = false;
+        switch (L->field) {
+        case 1: st = ordered_push_rr<1>(c, rr, io, s, &done); break;
+        case 3: st = ordered_push_rr<3>(c, rr, io, s, &done); break;
+        case 5: st = ordered_push_rr<5>(c, rr, io, s, &done); break;
+        case 10: st = ordered_push_rr<10>(c, rr, io, s, &done); break;
+        case 21: st = ordered_push_rr<21>(c, rr, io, s, &done); break;
+        case 23: st = ordered_push_rr<23>(c, rr, io, s, &done); break;
+        case 25: st = ordered_push_rr<25>(c, rr, io, s, &done); break;
+        default: st = ordered_push_rr<11>(c, rr, io, s, &done); break;
+        }
+        if (st != RPDLA_OK || done) return st;
     }
-    if (st != RPDLA_OK || done) return st;
     unsigned long long* q = nullptr;
     RPDLA_HIP(hipMallocAsync((void**)&q, rpdla::kQueueWords * sizeof(unsigned long long), s));
     hipLaunchKernelGGL(rpdla::zero_u64_kernel, dim3(1), dim3(rpdla::kQueueWords), 0, s, q,
@@ -1097,17 +1102,20 @@ rpdla_status rpdla_run_batched_range(const rpdla_laser* cfgs, int32_t n_cfg, uin
                        (unsigned long long)first_chunk);
     RPDLA_HIP(hipGetLastError());
     if (n_chunks == 0) return RPDLA_OK;
-    // the ordered push needs the whole workspace and 32-bit places; a smaller
-    // workspace that holds the chunk runs the queue push
+    // the ordered push needs the whole workspace and 32-bit places, and enough
+    // steps; a smaller workspace that holds the chunk runs the queue push
     rpdla::BatchPlanArgs P;
     memset(&P, 0, sizeof P);
-    if (ws_bytes >= w.total && (int64_t)n_cfg * atoms_per_chunk * K < (int64_t)UINT32_MAX) {
+    const int64_t slots = (int64_t)n_cfg * atoms_per_chunk * K;
+    double most_steps = 0.0;
+    for (int c = 0; c < n_cfg; ++c) most_steps = std::max(most_steps, window_steps(&cfgs[c]));
+    if (ws_bytes >= w.total && slots < (int64_t)UINT32_MAX &&
+        !rpdla::sweep_by_queue(n_cfg, slots, most_steps, precision == RPDLA_MIXED)) {
         P.plan = (rpdla::BatchPlan*)(base + w.plan);
         P.order = (uint32_t*)(base + w.order);
         P.groups = (rpdla::BatchGroup*)(base + w.groups);
         P.state = (uint64_t*)(base + w.state);
-        for (int c = 0; c < n_cfg; ++c)
-            P.n_max = std::max(P.n_max, ceil((cfgs[c].t_before + cfgs[c].t_after) / cfgs[c].dt) + 2.0);
+        P.n_max = ceil(most_steps) + 2.0;
     }
     const bool mixed = precision == RPDLA_MIXED;
     switch (cfgs[0].field) {

@@ -1,6 +1,6 @@
-// rpdla_plan.hpp -- how the groups of an ordered push are dealt to the waves:
-// plain integer arithmetic, shared by the plan kernels, the push kernels and the
-// host that sizes their scratch, and compiled for the host by its test.
+// rpdla_plan.hpp -- which pushes are ordered, and how their groups are dealt to
+// the waves: plain arithmetic, shared by the plan kernels, the push kernels and
+// the host that sizes their scratch, and compiled for the host by its test.
 #pragma once
 
 #include <stddef.h>
@@ -11,6 +11,39 @@
 namespace rpdla {
 
 constexpr int kPlanLaunches = 32;         // slice launches
+
+// Pushes of so few steps that putting the slots in order costs more than the
+// order gains.  `steps` is the window's length in steps, the bound of every
+// electron's.  The order costs two passes over the births, scattered loads and
+// stores and up to 37 launches: 0.2 ms for 1e6 slots, 0.8 ms for 4e6 and 3.4 ms
+// for 1e7, where the queue takes 0.07, 0.09 and 0.19 ms a step.  Queue / ordered,
+// in microseconds, double precision (the others cross at the same steps):
+// 2.6e5 slots of 2 steps 116 / 185, 1e6 of 2 158 / 286 and of 4 291 / 289, 4e6 of
+// 4 535 / 813 and of 8 950 / 850, 1e7 of 4 984 / 3476, of 12 2435 / 3615 and of 24
+// 4496 / 4013.  Below 2^18 slots the order is never slower.
+inline bool push_by_queue(int64_t n_slots, double steps)
+{
+    if (n_slots < (int64_t)1 << 18) return false;
+    const double most = 3.0 + (double)n_slots / (double)(1 << 20);
+    return steps <= (most < 16.0 ? most : 16.0);
+}
+
+// The same for a chunk of a sweep, `slots` of all its configurations together:
+// the plan of 64 configurations takes 0.14 ms, its launches 0.1 ms, and their
+// queues waste less than the single one.  A chunk's time with the queue over that
+// in order, double precision: 16 configurations of 20,480 slots 0.77 at 8 steps,
+// 0.87 at 64, 1.03 at 192; 64 of 5,120 0.69, 0.80, 0.98; 64 of 10,240 0.85, 0.92,
+// 1.05; 4 of 640 0.84 at 8, 1.09 at 64; with more slots in all (16 of 40,960, 64
+// of 20,480) 1.0 and more from the start.  Mixed precision, whose steps are
+// shorter, crosses at about twice the steps.
+inline bool sweep_by_queue(int n_cfg, int64_t slots, double steps, bool mixed)
+{
+    const int64_t many = 10240ll * n_cfg > (1 << 19) ? 10240ll * n_cfg : 1 << 19;
+    if (slots > many) return false;
+    const double most = mixed ? 64.0 + (double)slots / 1536.0 : 32.0 + (double)slots / 2560.0;
+    const double cap = mixed ? 256.0 : 128.0;
+    return steps <= (most < cap ? most : cap);
+}
 
 // Groups of 64 slots; no sum that could pass 2^32 on the way.
 RPDLA_HD inline uint32_t groups_of(uint32_t slots)

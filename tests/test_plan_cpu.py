@@ -30,6 +30,8 @@ int t_turn(unsigned l, unsigned w, unsigned W, unsigned rest, unsigned slices, u
     return t.any;
 }
 unsigned t_steps(double most, unsigned slices) { return plan_slice_steps(most, slices); }
+int t_queue(long long n, double steps) { return push_by_queue(n, steps); }
+int t_sweep(int c, long long n, double steps, int mixed) { return sweep_by_queue(c, n, steps, mixed); }
 int t_launches() { return kPlanLaunches; }
 }
 '''
@@ -45,6 +47,8 @@ def plan(tmp_path_factory):
     lib.t_groups.restype = C.c_uint
     lib.t_bound.restype = C.c_longlong
     lib.t_bound.argtypes = [C.c_longlong] * 3
+    lib.t_queue.argtypes = [C.c_longlong, C.c_double]
+    lib.t_sweep.argtypes = [C.c_int, C.c_longlong, C.c_double, C.c_int]
     lib.t_steps.restype = C.c_uint
     lib.t_steps.argtypes = [C.c_double, C.c_uint]
     return lib
@@ -86,3 +90,20 @@ def test_every_group_gets_its_turns(plan, simds, waves):
             assert all(seen == [(0, 0)] for seen in turns)
         for steps in (0.0, 1.0, 31.0, 22500.0, 2.0e9):
             assert plan.t_steps(steps, slices) * slices >= steps
+
+
+def test_which_pushes_are_ordered(plan):
+    """Few steps go to the queue, more of them with more slots; all others, the
+    default window at any size among them, are ordered."""
+    for n in (1, 64, 2**18 - 1):
+        assert not any(plan.t_queue(n, float(s)) for s in (1, 2, 4, 22500))
+    for n, steps in ((2**18, 3), (2**20, 4), (2**22, 7), (10**7, 12), (2**32, 16), (2**40, 16)):
+        assert plan.t_queue(n, float(steps)) and not plan.t_queue(n, steps + 1.0)
+    assert not any(plan.t_queue(n, 22500.0) for n in (1, 2**20, 2**32, 2**40))
+    for c, n, fp64, mixed in ((1, 10, 32, 64), (4, 40960, 48, 90), (64, 655360, 128, 256),
+                              (16, 2**19, 128, 256)):
+        assert plan.t_sweep(c, n, float(fp64), 0) and not plan.t_sweep(c, n, fp64 + 1.0, 0)
+        assert plan.t_sweep(c, n, float(mixed), 1) and not plan.t_sweep(c, n, mixed + 1.0, 1)
+    for c, n in ((1, 2**19 + 1), (51, 2**19 + 1), (64, 655361), (64, 2**33)):
+        assert not plan.t_sweep(c, n, 1.0, 0) and not plan.t_sweep(c, n, 1.0, 1)
+    assert not any(plan.t_sweep(c, 640 * c, 30000.0, m) for c in (1, 64) for m in (0, 1))
