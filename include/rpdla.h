@@ -212,7 +212,7 @@ rpdla_status rpdla_birth_phase(const rpdla_laser* L, int64_t n_slots, const doub
  * 20 KB and 4 bytes a slot; with slices, what two rounds of resident waves
  * hold in electrons of 72 (mixed), 128 or 136 bytes (radiation reaction): 64 to
  * 90 MB on 256 CUs, or less for fewer slots.  When that cannot be allocated, for
- * 2^18 slots and more of a window of at most 3 to 16 steps (more with more
+ * more than 2^16 slots of a window of at most 3 to 16 steps (more with more
  * slots), or from 2^32 - 1 slots on, lanes draw their slots from a work
  * queue instead, which needs 1 KiB (RPDLA_EHIP if that fails too): the slots are
  * split into eight contiguous parts with a counter each, and a wave draws from

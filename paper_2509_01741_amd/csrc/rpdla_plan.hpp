@@ -15,16 +15,17 @@ constexpr int kPlanLaunches = 32;         // slice launches
 // Pushes of so few steps that putting the slots in order costs more than the
 // order gains.  `steps` is the window's length in steps, the bound of every
 // electron's.  The order costs two passes over the births, scattered loads and
-// stores and up to 37 launches: 0.2 ms for 1e6 slots, 0.8 ms for 4e6 and 3.4 ms
-// for 1e7, where the queue takes 0.07, 0.09 and 0.19 ms a step.  Queue / ordered,
-// in microseconds, double precision (the others cross at the same steps):
-// 2.6e5 slots of 2 steps 116 / 185, 1e6 of 2 158 / 286 and of 4 291 / 289, 4e6 of
-// 4 535 / 813 and of 8 950 / 850, 1e7 of 4 984 / 3476, of 12 2435 / 3615 and of 24
-// 4496 / 4013.  Below 2^18 slots the order is never slower.
+// stores and, beyond one wave per SIMD (2^16 slots on 256 CUs), some 35 launches:
+// 0.15 ms for 1.3e5 slots, 0.3 for 1e6, 0.8 for 4e6 and 3.4 for 1e7, where the
+// queue takes 0.02, 0.07, 0.09 and 0.19 ms a step.  Queue / ordered, in
+// microseconds, double precision (the other forms cross at the same steps): 1.3e5
+// slots of 2 steps 69 / 154, of 4 123 / 154; 2.6e5 of 2 116 / 185, of 3 175 / 159;
+// 1e6 of 2 158 / 286, of 4 292 / 272 (mixed 441 / 516); 4e6 of 4 535 / 813, of 8 950 / 850; 1e7 of 4
+// 984 / 3476, of 16 3255 / 3491, of 24 4496 / 4013.
 inline bool push_by_queue(int64_t n_slots, double steps)
 {
-    if (n_slots < (int64_t)1 << 18) return false;
-    const double most = 3.0 + (double)n_slots / (double)(1 << 20);
+    if (n_slots <= 1 << 16) return false;
+    const double most = n_slots < 200000 ? 4.0 : 3.0 + 1.2 * (double)n_slots / (double)(1 << 20);
     return steps <= (most < 16.0 ? most : 16.0);
 }
 

@@ -61,8 +61,8 @@ FORMS = [("fp64", f) for f in (1, 3, 5, 10, 11, 21, 23, 25)] + \
 def test_few_steps(form, field):
     torch = require_gpu()
     from paper_2509_01741_amd import binding as B
-    # the last size below the rule, the first of it, and one with one step too many
-    for n, steps in ((2**18 - 1, 3), (2**18, 3), (2**18 + 7, 1), (2**18 + 65, 4)):
+    # the last size below the rule, the first of it, and some with one step too many
+    for n, steps in ((2**16, 4), (2**16 + 1, 4), (70001, 5), (2**18 + 7, 3), (2**18 + 65, 4)):
         print(f"{form} field {field}: {n} slots of {steps} steps", flush=True)
         L, (tb, *xyz) = _case(torch, B, n, 1, field, steps, 1.0, 1)
         _same(_push(B, form, L, tb, xyz, 1), _other(torch, B, form, L, tb, xyz, 1))

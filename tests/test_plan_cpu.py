@@ -95,9 +95,10 @@ def test_every_group_gets_its_turns(plan, simds, waves):
 def test_which_pushes_are_ordered(plan):
     """Few steps go to the queue, more of them with more slots; all others, the
     default window at any size among them, are ordered."""
-    for n in (1, 64, 2**18 - 1):
+    for n in (1, 64, 2**16):
         assert not any(plan.t_queue(n, float(s)) for s in (1, 2, 4, 22500))
-    for n, steps in ((2**18, 3), (2**20, 4), (2**22, 7), (10**7, 12), (2**32, 16), (2**40, 16)):
+    for n, steps in ((2**16 + 1, 4), (199999, 4), (200000, 3), (2**18, 3), (2**20, 4), (2**22, 7),
+                     (10**7, 14), (2**32, 16), (2**40, 16)):
         assert plan.t_queue(n, float(steps)) and not plan.t_queue(n, steps + 1.0)
     assert not any(plan.t_queue(n, 22500.0) for n in (1, 2**20, 2**32, 2**40))
     for c, n, fp64, mixed in ((1, 10, 32, 64), (4, 40960, 48, 90), (64, 655360, 128, 256),
