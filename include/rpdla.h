@@ -165,8 +165,12 @@ rpdla_status rpdla_sample_atoms_annulus(uint64_t seed, uint32_t cfg_id, uint64_t
  * (slot j*K + (k - k_first)), seconds, +INF where the state is not reached
  * in the window.  A state whose rate, bounded through the field's envelope,
  * cannot reach its threshold within the window is left unborn without
- * integrating its panels (the same result).  One wave per atom; no device
- * memory is allocated.  EINVAL: bad laser,
+ * integrating its panels (the same result).  A wave takes an atom; from 16384
+ * atoms on, where few atoms reach their first state, it looks at up to 64 and takes
+ * those, and where windows are short or the field is constant, a lane takes an atom,
+ * in the order of their work.  That order needs 6 bytes an atom and 16 KB of
+ * stream-ordered scratch (hipMallocAsync / hipFreeAsync on `stream`); without it a
+ * wave takes an atom.  Results do not depend on any of this.  EINVAL: bad laser,
  * 1 <= k_first <= k_last <= 10 violated, null pointers with
  * n_atoms > 0.
  * ------------------------------------------------------------------------ */

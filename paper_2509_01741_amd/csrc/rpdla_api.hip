@@ -246,17 +246,100 @@ constexpr int kKindPush = 0, kKindIonize = 1, kKindBatchPush = 2;
 // than 2^32 threads.
 constexpr int64_t kIonizeAtoms = (int64_t)1 << 25;
 
+// The largest |a|^2 bound over the atoms' positions (in the focal plane) and what
+// the first state's rate, bounded through it, adds up to over the window (see
+// never_reaches); infinite where the field does not depend on time, beyond 3e4, and
+// for windows of so many panels that the sum would take long.
+struct PeakBound { double b2, reach; };
+
+template <int FIELD>
+PeakBound peak_bound(const DevCfg& c, int k_first)
+{
+    PeakBound p{0.0, INFINITY};
+    if constexpr (FIELD == 11) return p;
+    const double w0n = 1.0 / c.inv_w0n;
+    for (int i = 0; i <= 32; ++i)
+        p.b2 = std::max(p.b2, rpdla::bound2_f64<FIELD>(c, w0n * i / 16.0, 0.0, 0.0));
+    const rpdla::AdkState st = rpdla::adk_state(c, k_first - 1);
+    const double d_s = -c.tb_n, d_e = c.ta_n, h = c.hn, m = ceil((d_e - d_s) / h);
+    if (m > 1.0e6) return p;
+    const int32_t M = (int32_t)m;
+    int32_t j0, j1;
+    p.reach = 0.0;
+    if (!rpdla::state_window(c, st, p.b2, 0.0, d_s, h, M, j0, j1)) return p;
+    const double la2pk = st.c1h > 0.0 ? 2.0 * log(st.c2 / (2.0 * st.c1h)) : INFINITY;
+    const int32_t groups = (j1 - j0) / rpdla::kBoundGroup + 1;
+    for (int32_t g = 0; g < groups; ++g) {
+        double da, db;
+        rpdla::bound_group(g, groups, j0, j1, M, d_s, d_e, h, d_s + j0 * h, da, db);
+        p.reach += rpdla::bound_group_rate(c, st, log(p.b2), la2pk, da, db);
+        if (!(p.reach < 3.0e4)) { p.reach = INFINITY; break; }
+    }
+    return p;
+}
+
+// Atoms by lanes, in the order of their work; *done false, and nothing enqueued,
+// where there is no room for the order.
+template <int FIELD>
+rpdla_status ionize_by_lanes(rpdla::IonizeArgs A, double peak, int block, hipStream_t st, bool* done)
+{
+    *done = false;
+    const size_t cursor = align256(rpdla::kIonizeBins * sizeof(uint32_t));
+    const size_t order = cursor + align256((size_t)A.n * sizeof(uint16_t));
+    char* base = nullptr;
+    if (hipMallocAsync((void**)&base, order + (size_t)A.n * sizeof(uint32_t), st) != hipSuccess) {
+        (void)hipGetLastError();
+        return RPDLA_OK;
+    }
+    A.order = (const uint32_t*)(base + order);
+    constexpr int64_t words = rpdla::kIonizeBins / 2;
+    static_assert(rpdla::kIonizeBins % 2 == 0, "cleared by words");
+    hipLaunchKernelGGL(rpdla::zero_u64_kernel, dim3((unsigned)cdiv(words, 256)), dim3(256), 0, st,
+                       (unsigned long long*)base, words);
+    hipLaunchKernelGGL(rpdla::ionize_key_kernel<FIELD>, dim3((unsigned)cdiv(A.n, rpdla::kIonizeBlock)),
+                       dim3(rpdla::kIonizeBlock), 0, st, A, 1.0 / peak, (uint16_t*)(base + cursor),
+                       (uint32_t*)base);
+    hipLaunchKernelGGL(rpdla::ionize_scan_kernel, dim3(1), dim3(rpdla::kIonizeBlock), 0, st,
+                       (uint32_t*)base);
+    hipLaunchKernelGGL(rpdla::ionize_place_kernel, dim3((unsigned)cdiv(A.n, rpdla::kIonizeChunk)),
+                       dim3(rpdla::kIonizeBlock), 0, st, A.n, (const uint16_t*)(base + cursor),
+                       (uint32_t*)base, (uint32_t*)(base + order));
+    hipLaunchKernelGGL(rpdla::ionize_lane_kernel<FIELD>, dim3((unsigned)cdiv(A.n, block)), dim3(block),
+                       0, st, A);
+    const hipError_t e = hipGetLastError();
+    const hipError_t fe = hipFreeAsync(base, st);
+    if (e != hipSuccess) return fail(RPDLA_EHIP, "ionize: %s", hipGetErrorString(e));
+    if (fe != hipSuccess) return fail(RPDLA_EHIP, "hipFreeAsync: %s", hipGetErrorString(fe));
+    *done = true;
+    return RPDLA_OK;
+}
+
 template <int FIELD>
 rpdla_status launch_ionize(const DevCfg& c, uint64_t seed, uint32_t cfg, uint64_t first,
                            int64_t n, const double* x, const double* y, const double* z, int kf,
                            int kl, double* tb, hipStream_t st)
 {
-    const int bs = get_shape(kKindIonize, FIELD, 0).block;
+    const int bs = get_shape(kKindIonize, FIELD, 0).block, K = kl - kf + 1;
+    PeakBound peak{0.0, INFINITY};
+    if (n >= 16384) peak = peak_bound<FIELD>(c, kf);
     for (int64_t i = 0; i < n; i += kIonizeAtoms) {
         const int64_t m = std::min(n - i, kIonizeAtoms);
-        hipLaunchKernelGGL(rpdla::ionize_kernel<FIELD>, dim3((unsigned)cdiv(m, bs / 64)), dim3(bs),
-                           0, st, c, seed, cfg, first + (uint64_t)i, m, x + i, y + i, z + i, kf,
-                           kl, tb + i * (kl - kf + 1));
+        const rpdla::IonizeForm form = rpdla::ionize_form(m, K, (c.ta_n + c.tb_n) / c.hn, peak.reach,
+                                                          FIELD == 11);
+        rpdla::IonizeArgs A{c, seed, cfg, first + (uint64_t)i, m, x + i, y + i, z + i, kf, K, tb + i * K,
+                            (int32_t)std::min<int64_t>(std::max<int64_t>(m / 4096, 1), 64), nullptr};
+        if (form == rpdla::kIonizeLane) {
+            bool done = false;
+            const rpdla_status s = ionize_by_lanes<FIELD>(A, peak.b2, bs, st, &done);
+            if (s != RPDLA_OK) return s;
+            if (done) continue;
+        }
+        if (form == rpdla::kIonizeFew)
+            hipLaunchKernelGGL(rpdla::ionize_few_kernel<FIELD>,
+                               dim3((unsigned)cdiv(cdiv(m, A.per_wave), bs / 64)), dim3(bs), 0, st, A);
+        else
+            hipLaunchKernelGGL(rpdla::ionize_kernel<FIELD>, dim3((unsigned)cdiv(m, bs / 64)), dim3(bs),
+                               0, st, c, seed, cfg, A.first_atom, m, A.x, A.y, A.z, kf, kl, A.out);
         RPDLA_HIP(hipGetLastError());
     }
     return RPDLA_OK;

@@ -236,7 +236,7 @@ __device__ inline void rp_field_f64(const CFG& c, double X, double Y, double Z, 
 // Spatial bound M with |a(X, tau)|^2 <= M^2 exp(-2 s^2): every C_n, S_n is
 // bounded by a0 exp(-rho^2/D) D^(-n/2); sum the coefficient magnitudes.
 template <int ORDER, class CFG>
-__device__ inline double rp_bound2(const CFG& c, double X, double Y, double Z)
+RPDLA_HD inline double rp_bound2(const CFG& c, double X, double Y, double Z)
 {
     const double r2 = (X * X + Y * Y) * c.inv_w0n2;
     const double zeta = Z * c.inv_zrn;
@@ -350,7 +350,7 @@ __device__ inline Cx<double> lp_sum_stated(const lp::Term (&T)[N], const double*
 // Upper bound of |sum_n c_n Q_n| / (g): sum of the coefficient magnitudes
 // times |q|^n.
 template <int N>
-__device__ inline double lp_bound_sum(const lp::Term (&T)[N], const double* sp, const double* ep,
+RPDLA_HD inline double lp_bound_sum(const lp::Term (&T)[N], const double* sp, const double* ep,
                                       double qabs)
 {
     double b = 0.0;
@@ -391,7 +391,7 @@ __device__ inline void lp_sums(const double* sp, const double* ep, Cx<double> q,
 }
 
 template <class CFG>
-__device__ inline void lp_powers(const CFG& c, double s, double* sp, double* ep)
+RPDLA_HD inline void lp_powers(const CFG& c, double s, double* sp, double* ep)
 {
     sp[0] = 1.0; sp[1] = s; sp[2] = s * s; sp[3] = sp[2] * s; sp[4] = sp[2] * sp[2];
     sp[5] = sp[4] * s;
@@ -465,7 +465,7 @@ __device__ inline void lp_field_stated(const CFG& c, double X, double Y, double 
 
 // Spatial bound M with |a(X, tau)|^2 <= M^2 exp(-2 s^2) for the linear focus.
 template <int ORDER, class CFG>
-__device__ inline double lp_bound2(const CFG& c, double X, double Y, double Z)
+RPDLA_HD inline double lp_bound2(const CFG& c, double X, double Y, double Z)
 {
     const double rx = fabs(X * c.inv_w0n), ry = fabs(Y * c.inv_w0n);
     const double s = rx * rx + ry * ry;
@@ -524,7 +524,7 @@ __device__ inline void field_f64(const CFG& c, double X, double Y, double Z, dou
 }
 
 template <int FIELD, class CFG>
-__device__ inline double bound2_f64(const CFG& c, double X, double Y, double Z)
+RPDLA_HD inline double bound2_f64(const CFG& c, double X, double Y, double Z)
 {
     if constexpr (FIELD == 11)
         return c.tE[0] * c.tE[0] + c.tE[1] * c.tE[1] + c.tE[2] * c.tE[2];
@@ -550,7 +550,7 @@ struct AdkState {
 };
 
 template <class CFG>
-__device__ inline AdkState adk_state(const CFG& c, int s)
+RPDLA_HD inline AdkState adk_state(const CFG& c, int s)
 {
     return AdkState{c.adk_c0[s], c.adk_c1h[s], c.adk_c2[s], c.adk_a2thr[s], c.lnw_zero};
 }

@@ -177,7 +177,7 @@ __device__ inline double emag2_atom(const CFG& c, const RCFG& rc, const AtomGeom
 // Panel range [j_lo, j_hi] outside which the state's ln w lies below the skip
 // level (adk_a2thr) at every node.
 template <class CFG>
-__device__ inline bool state_window(const CFG& c, const AdkState& st, double bound2, double Zc,
+RPDLA_HD inline bool state_window(const CFG& c, const AdkState& st, double bound2, double Zc,
                                     double tau_s, double h, int32_t M, int32_t& j_lo, int32_t& j_hi)
 {
     const double thr = st.a2thr;
@@ -210,7 +210,7 @@ constexpr int32_t kBoundGroup = 200;
 // Edges of group g (0-based) of panels j0..j1, as the panel loop forms its
 // panel edges: from d_from or panel j0 + g kBoundGroup to the start of the
 // next group or the end of panel j1.
-__device__ inline void bound_group(int32_t g, int32_t groups, int32_t j0, int32_t j1, int32_t M,
+RPDLA_HD inline void bound_group(int32_t g, int32_t groups, int32_t j0, int32_t j1, int32_t M,
                                    double d_s, double d_e, double h, double d_from, double& da,
                                    double& db)
 {
@@ -220,7 +220,7 @@ __device__ inline void bound_group(int32_t g, int32_t groups, int32_t j0, int32_
 }
 
 template <class CFG>
-__device__ inline double bound_group_rate(const CFG& c, const AdkState& st, double lb2, double la2pk,
+RPDLA_HD inline double bound_group_rate(const CFG& c, const AdkState& st, double lb2, double la2pk,
                                           double da, double db)
 {
     const double smin = (da <= 0.0 && db >= 0.0) ? 0.0 : fmin(fabs(da), fabs(db)) * c.inv_T0n;
@@ -336,8 +336,9 @@ struct RateRegs {
 // instructions for 64 panels go into the ordered sum).  With one lane per atom
 // a wave's lanes waited for one another (37 of 64 at work) and a small
 // ensemble left most of the chip idle behind one lane's serial chain: 1024
-// atoms x 10 states 19.6 -> 0.32 ms, 2e5 atoms x 1 state 11.8 -> 8.1 ms, 1e6
-// atoms x 10 states 147 -> 121 ms (and no sort of the atoms by work).
+// atoms x 8 states 11.7 -> 0.13 ms, 2e5 atoms x 1 state 11.8 -> 7.6 ms, 1e6
+// atoms x 10 states 147 -> 119 ms.  ionize_form says where the forms below take
+// its place.
 template <int FIELD, class CFG>
 __device__ void ionize_atom(const CFG& c, const RateRegs& R, uint64_t seed, uint32_t cfg,
                                  uint64_t atom, double X, double Y, double Z, int k_first, int K,
@@ -413,8 +414,9 @@ __device__ void ionize_atom(const CFG& c, const RateRegs& R, uint64_t seed, uint
                 break;
             }
             if (cross < 0) { j += 64; continue; }
-            // bracketed Newton for the crossing, as solve_crossing: lanes 0..3
-            // evaluate the Gauss nodes of [lo, t], lane 4 the rate at t
+            // Newton for the crossing, bracketed, halving where a step leaves the
+            // bracket: lanes 0..3 evaluate the Gauss nodes of [lo, t], lane 4 the
+            // rate at t
             const double clo = lane_value(lo, cross), chi = lane_value(b, cross);
             const double chw = lane_value(hw, cross), cacc = lane_value(acc, cross);
             const double need = target - I;
@@ -511,6 +513,287 @@ __global__ void __launch_bounds__(256, IonizeWaves<FIELD>::value) ionize_kernel(
     const RateRegs R(c);
     ionize_atom<FIELD>(c, R, seed, cfg, first_atom + (uint64_t)i, x[i] * c.k, y[i] * c.k,
                        z[i] * c.k, k_first, K, t_birth + i * K);
+}
+
+// ---------------------------------------------------------------------------
+// The other two forms of the ionization, for many atoms.  With a wave per atom
+// the set-up of an atom (threshold, window, rate bound) costs a wave whatever
+// comes of it, a birth throws away what was evaluated past it and its Newton
+// iterations have five lanes at work; with hundreds of atoms for every SIMD the
+// lanes have work of their own.  Each atom's arithmetic is the same in all forms.
+// With only the wave form, ensembles that reach few states or have short windows
+// took up to ten times what a lane per atom took before it (1e6 atoms at 7e14
+// W/cm^2 4.2 ms instead of 0.34, with 2 fs pulses 32 instead of 26; now 0.09, 20).
+// ---------------------------------------------------------------------------
+
+// Birth times of one atom, as ionize_atom, by one lane: panel after panel.
+template <int FIELD, class CFG>
+__device__ void ionize_atom_lane(const CFG& c, const RateRegs& R, uint64_t seed, uint32_t cfg,
+                                 uint64_t atom, double X, double Y, double Z, int k_first, int K,
+                                 double* __restrict__ out)
+{
+    for (int s = 0; s < K; ++s) out[s] = __builtin_inf();
+    const double dz = (c.window == 0) ? 0.0 : -Z;
+    const double d_s = dz - c.tb_n, d_e = dz + c.ta_n;
+    const double h = c.hn;
+    const int32_t M = (int32_t)ceil((d_e - d_s) / h);
+    const double b2 = bound2_f64<FIELD>(c, X, Y, Z);
+    const double lb2 = fm::log_pos_f64(b2);
+    auto threshold = [&](int s) { return -log(uniform_j(seed, cfg, atom, k_first + s + 2)); };
+    int s = 0;
+    double target = threshold(0);
+    while (!(target > 0.0)) {               // zero thresholds: born where they start
+        out[s] = (d_s + Z) * c.inv_omega;
+        if (++s >= K) return;
+        target = threshold(s);
+    }
+    AdkState st = adk_state(c, k_first - 1 + s);
+    int32_t j, j_hi;
+    if (!state_window(c, st, b2, 0.0, d_s, h, M, j, j_hi)) return;
+    if (FIELD != 11 &&
+        never_reaches(c, st, lb2, d_s, d_e, h, M, j, j_hi, d_s + (double)j * h, target))
+        return;
+    const AtomGeom ag = atom_geom<FIELD>(c, X, Y, Z);
+    st.lnw_zero = R.lnw_zero;
+    auto rate = [&](double d) {
+        return adk_rate_n(st, emag2_atom<FIELD>(c, R, ag, d, R.k), R.k, R.l);
+    };
+    // Gauss sum over [m - hw, m + hw], in units of hw
+    auto gauss = [&](double hw, double m) {
+        double acc = 0.0;
+#pragma unroll 1
+        for (int i = 0; i < 4; ++i) {
+            const double xn = i == 0 ? -R.gl_x[1] : i == 1 ? -R.gl_x[0] : i == 2 ? R.gl_x[0] : R.gl_x[1];
+            acc = fma(i == 0 || i == 3 ? R.gl_w[1] : R.gl_w[0], rate(fma(xn, hw, m)), acc);
+        }
+        return acc;
+    };
+    double I = 0.0, tstart = d_s;
+    while (j <= j_hi) {
+        const double a = fma((double)j, h, d_s);
+        const double b = (j == M - 1) ? d_e : fma((double)(j + 1), h, d_s);
+        const double lo = (tstart > a) ? tstart : a;
+        const double hw = 0.5 * (b - lo);
+        const double acc = gauss(hw, 0.5 * (lo + b));
+        const double In = fma(hw, acc, I);
+        if (In < target) {
+            I = In;
+            ++j;
+            continue;
+        }
+        // bracketed Newton for the crossing, as in ionize_atom
+        const double need = target - I;
+        double t = lo;
+        if (need > 0.0) {
+            double tl = lo, th = b;
+            t = fma(b - lo, need / (hw * acc), lo);
+            if (!(t > tl && t < th)) t = 0.5 * (tl + th);
+#pragma unroll 1
+            for (int it = 0; it < 100; ++it) {
+                const double hh = 0.5 * (t - lo);
+                const double gd = fma(hh, gauss(hh, 0.5 * (lo + t)), -need);
+                if (gd == 0.0) break;
+                if (gd > 0.0) th = t; else tl = t;
+                const double tol = ldexp(fmax(fabs(t), kTwoPi), -40);
+                const double w = rate(t);
+                double tn = __builtin_nan("");
+                if (w > 0.0) {
+                    const double dlt = gd / w;
+                    if (fabs(dlt) <= tol) { t = t - dlt; break; }
+                    tn = t - dlt;
+                }
+                if (!(tn > tl && tn < th)) tn = 0.5 * (tl + th);
+                const double step = fabs(tn - t);
+                t = tn;
+                if (step <= tol) break;
+            }
+        }
+        out[s] = (t + Z) * c.inv_omega;
+        if (++s >= K) return;
+        target = threshold(s);
+        while (!(target > 0.0)) {
+            out[s] = (t + Z) * c.inv_omega;
+            if (++s >= K) return;
+            target = threshold(s);
+        }
+        st = adk_state(c, k_first - 1 + s);
+        st.lnw_zero = R.lnw_zero;
+        I = 0.0;
+        tstart = t;
+        int32_t nlo;
+        if (!state_window(c, st, b2, 0.0, d_s, h, M, nlo, j_hi)) return;
+        const double d0 = nlo > j ? d_s + (double)nlo * h : t;
+        if (nlo > j) j = nlo;
+        if (FIELD != 11 && j <= j_hi &&
+            never_reaches(c, st, lb2, d_s, d_e, h, M, j, j_hi, d0, target))
+            return;
+    }
+}
+
+// Whether the rate bound leaves any state of an atom open (ionize_atom would
+// integrate, or write a birth at the window's start).
+template <int FIELD, class CFG>
+__device__ inline bool atom_open(const CFG& c, uint64_t seed, uint32_t cfg, uint64_t atom, double X,
+                                 double Y, double Z, int k_first)
+{
+    const double dz = (c.window == 0) ? 0.0 : -Z;
+    const double d_s = dz - c.tb_n, d_e = dz + c.ta_n;
+    const int32_t M = (int32_t)ceil((d_e - d_s) / c.hn);
+    const double b2 = bound2_f64<FIELD>(c, X, Y, Z);
+    const double target = -log(uniform_j(seed, cfg, atom, k_first + 2));
+    if (!(target > 0.0)) return true;
+    const AdkState st = adk_state(c, k_first - 1);
+    int32_t j_lo, j_hi;
+    if (!state_window(c, st, b2, 0.0, d_s, c.hn, M, j_lo, j_hi)) return false;
+    return FIELD == 11 || !never_reaches(c, st, fm::log_pos_f64(b2), d_s, d_e, c.hn, M, j_lo, j_hi,
+                                         d_s + (double)j_lo * c.hn, target);
+}
+
+struct IonizeArgs {
+    DevCfg c;
+    uint64_t seed;
+    uint32_t cfg;
+    uint64_t first_atom;
+    int64_t n;
+    const double* x;
+    const double* y;
+    const double* z;
+    int32_t k_first, K;
+    double* out;
+    int32_t per_wave;            // ionize_few_kernel: atoms of a wave, at most 64
+    const uint32_t* order;       // ionize_lane_kernel
+};
+
+// Few atoms reach their first state: a wave asks the bound for per_wave atoms,
+// one to a lane, and then takes those that it leaves open one after another.
+template <int FIELD>
+__global__ void __launch_bounds__(256, IonizeWaves<FIELD>::value) ionize_few_kernel(IonizeArgs A)
+{
+    const int lane = __lane_id();
+    const int64_t i0 = wave_index() * A.per_wave;
+    if (i0 >= A.n) return;
+    const int64_t i = i0 + lane;
+    const bool mine = lane < A.per_wave && i < A.n;
+    double X = 0.0, Y = 0.0, Z = 0.0;
+    bool open = false;
+    if (mine) {
+        X = A.x[i] * A.c.k; Y = A.y[i] * A.c.k; Z = A.z[i] * A.c.k;
+        open = atom_open<FIELD>(A.c, A.seed, A.cfg, A.first_atom + (uint64_t)i, X, Y, Z, A.k_first);
+        if (!open)
+            for (int s = 0; s < A.K; ++s) A.out[i * A.K + s] = __builtin_inf();
+    }
+    uint64_t todo = __ballot(open);
+    if (todo == 0) return;
+    const RateRegs R(A.c);
+#pragma unroll 1
+    while (todo) {
+        const int l = __ffsll((unsigned long long)todo) - 1;
+        todo &= todo - 1;
+        ionize_atom<FIELD>(A.c, R, A.seed, A.cfg, A.first_atom + (uint64_t)(i0 + l),
+                           lane_value(X, l), lane_value(Y, l), lane_value(Z, l), A.k_first, A.K,
+                           A.out + (i0 + l) * A.K);
+    }
+}
+
+// The order for ionize_lane_kernel, most work first: a counting sort by the
+// number of states that the rate bound leaves open from the window start, then by
+// the peak-field bound in sixteenths of a doubling (the windows, and so the panels
+// an atom integrates, grow with it).
+constexpr int kIonizeLevels = 372;
+constexpr int kIonizeBins = (kMaxStates + 1) * kIonizeLevels;   // 4092
+constexpr int kIonizeBlock = 1024;
+constexpr int kIonizeChunk = 16 * kIonizeBlock;   // atoms of one block of the last pass
+
+template <int FIELD>
+__global__ void __launch_bounds__(kIonizeBlock) ionize_key_kernel(IonizeArgs A, double inv_peak,
+                                                                  uint16_t* __restrict__ key,
+                                                                  uint32_t* __restrict__ cursor)
+{
+    __shared__ uint32_t bins[kIonizeBins];
+    for (int b = threadIdx.x; b < kIonizeBins; b += kIonizeBlock) bins[b] = 0;
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * kIonizeBlock + threadIdx.x;
+    if (i < A.n) {
+        const double X = A.x[i] * A.c.k, Y = A.y[i] * A.c.k, Z = A.z[i] * A.c.k;
+        const double b2 = bound2_f64<FIELD>(A.c, X, Y, Z);
+        const float depth = -16.0f * log2f((float)(b2 * inv_peak));
+        const int level = depth > 0.0f ? (depth < (float)(kIonizeLevels - 1) ? (int)depth : kIonizeLevels - 1)
+                                       : (depth <= 0.0f ? 0 : kIonizeLevels - 1);
+        int open = 0;
+        while (open < A.K && atom_open<FIELD>(A.c, A.seed, A.cfg, A.first_atom + (uint64_t)i, X, Y,
+                                              Z, A.k_first + open))
+            ++open;
+        const int bin = (kMaxStates - open) * kIonizeLevels + level;
+        key[i] = (uint16_t)bin;
+        atomicAdd(&bins[bin], 1u);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < kIonizeBins; b += kIonizeBlock)
+        if (bins[b]) atomicAdd(&cursor[b], bins[b]);
+}
+
+// Counts to first places (one block).
+__global__ void __launch_bounds__(kIonizeBlock) ionize_scan_kernel(uint32_t* __restrict__ cursor)
+{
+    constexpr int kPer = (kIonizeBins + kIonizeBlock - 1) / kIonizeBlock;
+    __shared__ uint32_t part[kIonizeBlock];
+    uint32_t n[kPer], sum = 0;
+    for (int k = 0; k < kPer; ++k) {
+        const int b = threadIdx.x * kPer + k;
+        sum += n[k] = b < kIonizeBins ? cursor[b] : 0;
+    }
+    part[threadIdx.x] = sum;
+    __syncthreads();
+    for (int d = 1; d < kIonizeBlock; d *= 2) {
+        const uint32_t add = (int)threadIdx.x >= d ? part[threadIdx.x - d] : 0;
+        __syncthreads();
+        part[threadIdx.x] += add;
+        __syncthreads();
+    }
+    uint32_t at = part[threadIdx.x] - sum;
+    for (int k = 0; k < kPer; ++k) {
+        const int b = threadIdx.x * kPer + k;
+        if (b < kIonizeBins) cursor[b] = at;
+        at += n[k];
+    }
+}
+
+__global__ void __launch_bounds__(kIonizeBlock) ionize_place_kernel(
+    int64_t n, const uint16_t* __restrict__ key, uint32_t* __restrict__ cursor,
+    uint32_t* __restrict__ order)
+{
+    constexpr int kPer = kIonizeChunk / kIonizeBlock;
+    __shared__ uint32_t bins[kIonizeBins], base[kIonizeBins];
+    for (int b = threadIdx.x; b < kIonizeBins; b += kIonizeBlock) bins[b] = 0;
+    __syncthreads();
+    const int64_t lo = (int64_t)blockIdx.x * kIonizeChunk;
+    uint32_t bin[kPer], rank[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int64_t i = lo + k * kIonizeBlock + threadIdx.x;
+        bin[k] = i < n ? (uint32_t)key[i] : (uint32_t)kIonizeBins;
+        if (bin[k] < kIonizeBins) rank[k] = atomicAdd(&bins[bin[k]], 1u);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < kIonizeBins; b += kIonizeBlock)
+        if (bins[b]) base[b] = atomicAdd(&cursor[b], bins[b]);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
+        if (bin[k] < kIonizeBins)
+            order[base[bin[k]] + rank[k]] = (uint32_t)(lo + k * kIonizeBlock + threadIdx.x);
+}
+
+// Atom order[i] to lane i: neighbours of the order have much the same work.
+template <int FIELD>
+__global__ void __launch_bounds__(256, IonizeWaves<FIELD>::value) ionize_lane_kernel(IonizeArgs A)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= A.n) return;
+    const int64_t a = (int64_t)A.order[i];
+    const RateRegs R(A.c);
+    ionize_atom_lane<FIELD>(A.c, R, A.seed, A.cfg, A.first_atom + (uint64_t)a, A.x[a] * A.c.k,
+                            A.y[a] * A.c.k, A.z[a] * A.c.k, A.k_first, A.K, A.out + a * A.K);
 }
 
 // Wave-cooperative refill: lanes with need == true get consecutive queue

@@ -12,6 +12,45 @@ namespace rpdla {
 
 constexpr int kPlanLaunches = 32;         // slice launches
 
+// Form of an ionization of n atoms (of one launch) and K states over `panels`
+// panels: a wave per atom, a wave per 64 (or fewer) atoms that asks the rate bound
+// lane by lane and takes the few atoms left open one by one, or a lane per atom in
+// the order of the work.  `reach` bounds the integral of the first state's rate for
+// the atom in the strongest field, so an atom has that state open with at most the
+// chance 1 - exp(-2 reach); infinite for a field constant in time (`uniform`).
+//
+// A wave per atom costs 2 to 4 us whatever the atom does, 12 us and more a birth;
+// it balances atoms of unequal work and has the shortest chain.  Milliseconds, wave
+// / few / lane (order 5, 30 fs and ten states unless said otherwise):
+//   reach 1e-5 (7e14 W/cm^2)  16384 atoms 0.082 / 0.036 / 0.055, 1e6 4.2 / 0.09 / 0.32
+//   reach 0.06 (2e15)         2e5 1.67 / 0.72 / 8.4,  1e6 7.6 / 1.5 / 8.6
+//   reach 2.2 (4e15)          2e5 7.2 / 6.1 / 9.4,    1e6 34.7 / 21 / 21
+//   reach 11 (6e15)           65536 3.8 / 4.2 / 10.3, 1e6 54 / 37 / 33
+//   reach 54 (1e16)           2e5 12.4 / 12.7 / 15.8, 1e6 61 / 48 / 51
+//   reach 137, one state      2e5 8.3 / 7.4 / 9.1,    1e6 40 / 27 / 28
+//   reach 317, linear focus   2e5 9.8 / 9.4 / 15,     1e6 47 / 37 / 39
+//   reach 1.2e4 (1e21)        2e5 24 / 31 / 31,       1e6 119 / 120 / 119, 3e6 358 / 337 / 340
+//     in a target of 8 waists 2e5 7.1 / 7.4 / 19,     1e6 34 / 23 / 30 (the host sees no atoms)
+//     linear focus            2e5 24 / 34 / 39,       1e6 117 / 133 / 125, 3e6 349 / 377 / 353
+//   2 fs at 1e21, 2249 panels 2e5 6.4 / 8.5 / 5.5, one state 1.18 / 1.56 / 1.27;
+//                             1e6 32 / 34 / 20,    one state 5.9 / 6.2 / 4.4
+//   5 fs at 1e21, 5622 panels 1e6 42 / 43 / 36,    at 1e18 31 / 32 / 32,
+//                             one state 8.0 / 8.4 / 6.7
+//   10 steps a period, 1687   2e5 6.9 / 9.2 / 5.6,    1e6 34 / 37 / 19
+//   uniform field, 1000       2e5 2.0 / 2.9 / 0.83,   1e6 10 / 11 / 2.5
+enum IonizeForm { kIonizeWave, kIonizeFew, kIonizeLane };
+
+inline IonizeForm ionize_form(int64_t n, int K, double panels, double reach, bool uniform)
+{
+    if (n < 16384) return kIonizeWave;
+    if (uniform) return n >= 100000 ? kIonizeLane : kIonizeWave;
+    if (reach <= (n < 65536 ? 0.01 : 0.5)) return kIonizeFew;
+    if (panels <= (K <= 2 ? 12000.0 : 5000.0) && (double)n >= 3.0e4 + 1.0e4 * K + 75.0 * panels)
+        return kIonizeLane;
+    if (reach <= 60.0 && n >= (reach <= 30.0 ? 200000 : 500000)) return kIonizeFew;
+    return reach <= (K <= 2 ? 2.0e4 : 1.0e3) && n >= 1000000 ? kIonizeFew : kIonizeWave;
+}
+
 // Pushes of so few steps that putting the slots in order costs more than the
 // order gains.  `steps` is the window's length in steps, the bound of every
 // electron's.  The order costs two passes over the births, scattered loads and

@@ -32,6 +32,8 @@ int t_turn(unsigned l, unsigned w, unsigned W, unsigned rest, unsigned slices, u
 unsigned t_steps(double most, unsigned slices) { return plan_slice_steps(most, slices); }
 int t_queue(long long n, double steps) { return push_by_queue(n, steps); }
 int t_sweep(int c, long long n, double steps, int mixed) { return sweep_by_queue(c, n, steps, mixed); }
+int t_form(long long n, int K, double panels, double reach, int uniform)
+{ return ionize_form(n, K, panels, reach, uniform); }
 int t_launches() { return kPlanLaunches; }
 }
 '''
@@ -47,6 +49,7 @@ def plan(tmp_path_factory):
     lib.t_groups.restype = C.c_uint
     lib.t_bound.restype = C.c_longlong
     lib.t_bound.argtypes = [C.c_longlong] * 3
+    lib.t_form.argtypes = [C.c_longlong, C.c_int, C.c_double, C.c_double, C.c_int]
     lib.t_queue.argtypes = [C.c_longlong, C.c_double]
     lib.t_sweep.argtypes = [C.c_int, C.c_longlong, C.c_double, C.c_int]
     lib.t_steps.restype = C.c_uint
@@ -108,3 +111,29 @@ def test_which_pushes_are_ordered(plan):
     for c, n in ((1, 2**19 + 1), (51, 2**19 + 1), (64, 655361), (64, 2**33)):
         assert not plan.t_sweep(c, n, 1.0, 0) and not plan.t_sweep(c, n, 1.0, 1)
     assert not any(plan.t_sweep(c, 640 * c, 30000.0, m) for c in (1, 64) for m in (0, 1))
+
+
+def test_ionization_forms(plan):
+    """Few atoms always take a wave each, so do many on the default window at the
+    intensities of the ensembles; the other forms begin where the rule says."""
+    wave, few, lane = 0, 1, 2
+    for n in (1, 1024, 16383):
+        for reach in (0.0, 0.1, 1e9, float("inf")):
+            assert plan.t_form(n, 10, 22500.0, reach, 0) == wave
+    for n in (16384, 200_000, 1_000_000, 2**25):
+        assert plan.t_form(n, 10, 33727.0, 1.2e4, 0) == wave
+        assert plan.t_form(n, 1, 59584.0, float("inf"), 0) == wave
+        assert plan.t_form(n, 10, 33727.0, 1e-3, 0) == few
+    assert plan.t_form(65535, 10, 33727.0, 0.1, 0) == wave
+    assert plan.t_form(65536, 10, 33727.0, 0.5, 0) == few
+    for K, panels, n in ((10, 256.0, 149200), (1, 256.0, 59200), (10, 5000.0, 505000), (2, 12000.0, 950000)):
+        assert plan.t_form(n, K, panels, 1e3, 0) == lane
+        assert plan.t_form(n - 1, K, panels, 1e9, 0) == wave
+    assert plan.t_form(2**25, 10, 5001.0, float("inf"), 0) == wave
+    assert plan.t_form(200_000, 10, 33727.0, 30.0, 0) == few
+    assert plan.t_form(500_000, 10, 33727.0, 60.0, 0) == few
+    assert plan.t_form(1_000_000, 2, 33727.0, 2e4, 0) == few
+    assert plan.t_form(1_000_000, 10, 33727.0, 1e3, 0) == few
+    assert plan.t_form(999_999, 10, 33727.0, 61.0, 0) == wave
+    assert plan.t_form(99_999, 10, 1000.0, float("inf"), 1) == wave
+    assert plan.t_form(100_000, 10, 1000.0, float("inf"), 1) == lane
