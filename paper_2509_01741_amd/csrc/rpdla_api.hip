@@ -248,18 +248,19 @@ constexpr int64_t kIonizeAtoms = (int64_t)1 << 25;
 
 // The largest |a|^2 bound over the atoms' positions (in the focal plane) and what
 // the first state's rate, bounded through it, adds up to over the window (see
-// never_reaches); infinite where the field does not depend on time, beyond 3e4, and
-// for windows of so many panels that the sum would take long.
+// never_reaches), the group at the envelope's peak first, and that group for all
+// where that is next to nothing; infinite beyond `most`, where the field does not
+// depend on time, and for windows of so many panels that the sum would take long.
 struct PeakBound { double b2, reach; };
 
 template <int FIELD>
-PeakBound peak_bound(const DevCfg& c, int k_first)
+PeakBound peak_bound(const DevCfg& c, int k_first, double most)
 {
     PeakBound p{0.0, INFINITY};
     if constexpr (FIELD == 11) return p;
     const double w0n = 1.0 / c.inv_w0n;
-    for (int i = 0; i <= 32; ++i)
-        p.b2 = std::max(p.b2, rpdla::bound2_f64<FIELD>(c, w0n * i / 16.0, 0.0, 0.0));
+    for (int i = 0; i <= 8; ++i)
+        p.b2 = std::max(p.b2, rpdla::bound2_f64<FIELD>(c, w0n * i / 4.0, 0.0, 0.0));
     const rpdla::AdkState st = rpdla::adk_state(c, k_first - 1);
     const double d_s = -c.tb_n, d_e = c.ta_n, h = c.hn, m = ceil((d_e - d_s) / h);
     if (m > 1.0e6) return p;
@@ -267,13 +268,18 @@ PeakBound peak_bound(const DevCfg& c, int k_first)
     int32_t j0, j1;
     p.reach = 0.0;
     if (!rpdla::state_window(c, st, p.b2, 0.0, d_s, h, M, j0, j1)) return p;
+    const double lb2 = log(p.b2);
     const double la2pk = st.c1h > 0.0 ? 2.0 * log(st.c2 / (2.0 * st.c1h)) : INFINITY;
     const int32_t groups = (j1 - j0) / rpdla::kBoundGroup + 1;
-    for (int32_t g = 0; g < groups; ++g) {
+    const int32_t at_peak = std::min(std::max((int32_t)(-d_s / h) - j0, 0) / rpdla::kBoundGroup,
+                                     groups - 1);
+    for (int32_t i = 0; i < groups; ++i) {
+        const int32_t g = (at_peak + i) % groups;
         double da, db;
         rpdla::bound_group(g, groups, j0, j1, M, d_s, d_e, h, d_s + j0 * h, da, db);
-        p.reach += rpdla::bound_group_rate(c, st, log(p.b2), la2pk, da, db);
-        if (!(p.reach < 3.0e4)) { p.reach = INFINITY; break; }
+        p.reach += rpdla::bound_group_rate(c, st, lb2, la2pk, da, db);
+        if (!(p.reach <= most)) { p.reach = INFINITY; break; }
+        if (i == 0 && p.reach * groups <= 1.0e-2) { p.reach *= groups; break; }
     }
     return p;
 }
@@ -321,7 +327,7 @@ rpdla_status launch_ionize(const DevCfg& c, uint64_t seed, uint32_t cfg, uint64_
 {
     const int bs = get_shape(kKindIonize, FIELD, 0).block, K = kl - kf + 1;
     PeakBound peak{0.0, INFINITY};
-    if (n >= 16384) peak = peak_bound<FIELD>(c, kf);
+    if (n >= 16384) peak = peak_bound<FIELD>(c, kf, 3.0e4);
     for (int64_t i = 0; i < n; i += kIonizeAtoms) {
         const int64_t m = std::min(n - i, kIonizeAtoms);
         const rpdla::IonizeForm form = rpdla::ionize_form(m, K, (c.ta_n + c.tb_n) / c.hn, peak.reach,
@@ -950,9 +956,35 @@ std::vector<std::pair<std::string, hipGraphExec_t>> g_graphs;  // small cache, p
 // further ones are enqueued directly, without a graph.
 constexpr size_t kMaxGraphs = 32;
 
+// The ionization's form for all of a sweep's configurations together, by the one
+// of the strongest field and the one of the longest window, where it differs much
+// from a wave per atom: many atoms to a wave where no configuration reaches a state
+// (64 x 8192 atoms 1.75 -> 0.86 ms; with some that do, their waves are the last:
+// 64 x 1024 atoms up to reach 0.06 8.2 -> 9.3 ms, so not there), and a lane per atom
+// in windows of at most 300 panels and in a uniform field (64 x 8192 atoms of 32
+// panels 14.4 -> 4.2 ms with the push), where atoms differ little: a chunk has no
+// room for an order.
+struct BatchIonize { int32_t form, per_wave; };
+
+template <int FIELD>
+BatchIonize batch_ionize_form(const DevCfg* cfgs, int n_cfg, int64_t atoms, int k_first, int K)
+{
+    BatchIonize f{rpdla::kIonizeWave, (int32_t)std::min<int64_t>(std::max<int64_t>(atoms / 4096, 1), 64)};
+    if (atoms < 16384) return f;
+    double panels = 0.0, reach = 0.0;
+    for (int c = 0; c < n_cfg; ++c)
+        panels = std::max(panels, (cfgs[c].ta_n + cfgs[c].tb_n) / cfgs[c].hn);
+    for (int c = 0; c < n_cfg && reach <= 1.0; ++c)
+        reach = std::max(reach, peak_bound<FIELD>(cfgs[c], k_first, 1.0).reach);
+    f.form = rpdla::ionize_form(atoms, K, panels, reach, FIELD == 11);
+    if (f.form == rpdla::kIonizeLane ? panels > 300.0 && FIELD != 11 : reach > 0.02)
+        f.form = rpdla::kIonizeWave;
+    return f;
+}
+
 template <int FIELD, class ELEC>
-rpdla_status run_batched_impl(const rpdla::BatchArgs& A, rpdla::BatchPlanArgs P, int64_t n_chunks,
-                              hipStream_t s)
+rpdla_status run_batched_impl(const rpdla::BatchArgs& A, rpdla::BatchPlanArgs P,
+                              const DevCfg* cfgs, int64_t n_chunks, hipStream_t s)
 {
     const size_t lds_p = (size_t)A.n_cfg * sizeof(unsigned long long);
     auto* kpush = rpdla::batch_push_kernel<FIELD, ELEC>;
@@ -962,6 +994,7 @@ rpdla_status run_batched_impl(const rpdla::BatchArgs& A, rpdla::BatchPlanArgs P,
     const int64_t grid_p = persistent_blocks(kpush, slots, sh.block, sh.grid_factor, lds_p);
     const unsigned grid_a = (unsigned)cdiv((int64_t)A.n_cfg * A.apc, 256);
     const int64_t atoms = (int64_t)A.n_cfg * A.apc;
+    const BatchIonize form = batch_ionize_form<FIELD>(cfgs, A.n_cfg, atoms, A.k_first, A.K);
     int64_t grid_h = cdiv(slots, 256);
     if (grid_h > 8192) grid_h = 8192;
 
@@ -1002,7 +1035,15 @@ rpdla_status run_batched_impl(const rpdla::BatchArgs& A, rpdla::BatchPlanArgs P,
     auto enqueue_chunk = [&](hipStream_t st) -> rpdla_status {
         hipLaunchKernelGGL(rpdla::batch_zero_queue_kernel, dim3(1), dim3(64), 0, st, A.ctl);
         hipLaunchKernelGGL(rpdla::batch_sample_kernel, dim3(grid_a), dim3(256), 0, st, A);
-        for (int64_t i = 0; i < atoms; i += kIonizeAtoms)
+        if (form.form == rpdla::kIonizeFew)
+            hipLaunchKernelGGL(rpdla::batch_ionize_few_kernel<FIELD>,
+                               dim3((unsigned)cdiv(cdiv(A.apc, form.per_wave), 4), (unsigned)A.n_cfg),
+                               dim3(256), 0, st, A, A.cfgs, form.per_wave);
+        else if (form.form == rpdla::kIonizeLane)
+            hipLaunchKernelGGL(rpdla::batch_ionize_lane_kernel<FIELD>,
+                               dim3((unsigned)cdiv(A.apc, 256), (unsigned)A.n_cfg), dim3(256), 0, st,
+                               A, A.cfgs);
+        else for (int64_t i = 0; i < atoms; i += kIonizeAtoms)
             hipLaunchKernelGGL(kion, dim3((unsigned)cdiv(std::min(atoms - i, kIonizeAtoms), 4)),
                                dim3(256), 0, st, A, A.cfgs, i);
         if (P.plan) enqueue_ordered(st);
@@ -1031,6 +1072,7 @@ rpdla_status run_batched_impl(const rpdla::BatchArgs& A, rpdla::BatchPlanArgs P,
     key.append(reinterpret_cast<const char*>(&grid_p), sizeof grid_p);
     key.append(reinterpret_cast<const char*>(&sh), sizeof sh);
     key.append(reinterpret_cast<const char*>(&P), sizeof P);
+    key.append(reinterpret_cast<const char*>(&form), sizeof form);
     hipGraphExec_t exec = nullptr;
     bool full = false;
     {
@@ -1174,8 +1216,9 @@ rpdla_status rpdla_run_batched_range(const rpdla_laser* cfgs, int32_t n_cfg, uin
     A.tallies = (unsigned long long*)tallies;
     A.steps = (unsigned long long*)electron_steps;
     // configuration table: written by tiny kernels (arguments copied at launch)
+    DevCfg consts[rpdla::kMaxCfg];
     for (int c = 0; c < n_cfg; ++c) {
-        const DevCfg dc = make_cfg(&cfgs[c], true);
+        const DevCfg& dc = consts[c] = make_cfg(&cfgs[c], true);
         const double rmax = r_factor * cfgs[c].w0;
         const double zh = rpdla_rayleigh(&cfgs[c]);
         hipLaunchKernelGGL(rpdla::batch_set_cfg_kernel, dim3(1), dim3(64), 0, s, dc, rmax, zh,
@@ -1202,19 +1245,19 @@ rpdla_status rpdla_run_batched_range(const rpdla_laser* cfgs, int32_t n_cfg, uin
     }
     const bool mixed = precision == RPDLA_MIXED;
     switch (cfgs[0].field) {
-    case 1: return mixed ? run_batched_impl<1, rpdla::ElecMixed>(A, P, n_chunks, s)
-                         : run_batched_impl<1, rpdla::ElecF64>(A, P, n_chunks, s);
-    case 3: return mixed ? run_batched_impl<3, rpdla::ElecMixed>(A, P, n_chunks, s)
-                         : run_batched_impl<3, rpdla::ElecF64>(A, P, n_chunks, s);
-    case 5: return mixed ? run_batched_impl<5, rpdla::ElecMixed>(A, P, n_chunks, s)
-                         : run_batched_impl<5, rpdla::ElecF64>(A, P, n_chunks, s);
-    case 10: return mixed ? run_batched_impl<10, rpdla::ElecMixed>(A, P, n_chunks, s)
-                          : run_batched_impl<10, rpdla::ElecF64>(A, P, n_chunks, s);
-    case 21: return run_batched_impl<21, rpdla::ElecF64>(A, P, n_chunks, s);
-    case 23: return run_batched_impl<23, rpdla::ElecF64>(A, P, n_chunks, s);
-    case 25: return run_batched_impl<25, rpdla::ElecF64>(A, P, n_chunks, s);
-    default: return mixed ? run_batched_impl<11, rpdla::ElecMixed>(A, P, n_chunks, s)
-                          : run_batched_impl<11, rpdla::ElecF64>(A, P, n_chunks, s);
+    case 1: return mixed ? run_batched_impl<1, rpdla::ElecMixed>(A, P, consts, n_chunks, s)
+                         : run_batched_impl<1, rpdla::ElecF64>(A, P, consts, n_chunks, s);
+    case 3: return mixed ? run_batched_impl<3, rpdla::ElecMixed>(A, P, consts, n_chunks, s)
+                         : run_batched_impl<3, rpdla::ElecF64>(A, P, consts, n_chunks, s);
+    case 5: return mixed ? run_batched_impl<5, rpdla::ElecMixed>(A, P, consts, n_chunks, s)
+                         : run_batched_impl<5, rpdla::ElecF64>(A, P, consts, n_chunks, s);
+    case 10: return mixed ? run_batched_impl<10, rpdla::ElecMixed>(A, P, consts, n_chunks, s)
+                          : run_batched_impl<10, rpdla::ElecF64>(A, P, consts, n_chunks, s);
+    case 21: return run_batched_impl<21, rpdla::ElecF64>(A, P, consts, n_chunks, s);
+    case 23: return run_batched_impl<23, rpdla::ElecF64>(A, P, consts, n_chunks, s);
+    case 25: return run_batched_impl<25, rpdla::ElecF64>(A, P, consts, n_chunks, s);
+    default: return mixed ? run_batched_impl<11, rpdla::ElecMixed>(A, P, consts, n_chunks, s)
+                          : run_batched_impl<11, rpdla::ElecF64>(A, P, consts, n_chunks, s);
     }
 }
 

@@ -100,6 +100,56 @@ __global__ void __launch_bounds__(256, IonizeWaves<FIELD>::value) batch_ionize_k
                        A.tb + i * A.K);
 }
 
+// The other forms (see ionize_form), a configuration per blockIdx.y.
+template <int FIELD>
+__global__ void __launch_bounds__(256, IonizeWaves<FIELD>::value) batch_ionize_few_kernel(
+    BatchArgs A, const DevCfg* __restrict__ cfgs, int32_t per_wave)
+{
+    const int c = blockIdx.y, lane = __lane_id();
+    const int64_t first = (int64_t)A.ctl->chunk * A.apc;
+    const int64_t n = A.atoms_per_cfg - first < A.apc ? A.atoms_per_cfg - first : A.apc;
+    const int64_t a0 = wave_index() * per_wave, base = (int64_t)c * A.apc;
+    if (a0 >= n) return;
+    const DevCfg& cf = cfgs[c];
+    const int64_t a = a0 + lane;
+    double X = 0.0, Y = 0.0, Z = 0.0;
+    bool open = false;
+    if (lane < per_wave && a < n) {
+        X = A.x[base + a] * cf.k; Y = A.y[base + a] * cf.k; Z = A.z[base + a] * cf.k;
+        open = atom_open<FIELD>(cf, A.seed, A.cfg_base + (uint32_t)c, (uint64_t)(first + a), X, Y, Z,
+                                A.k_first);
+        if (!open)
+            for (int s = 0; s < A.K; ++s) A.tb[(base + a) * A.K + s] = __builtin_inf();
+    }
+    uint64_t todo = __ballot(open);
+    if (todo == 0) return;
+    const RateRegs R(cf);
+#pragma unroll 1
+    while (todo) {
+        const int l = __ffsll((unsigned long long)todo) - 1;
+        todo &= todo - 1;
+        ionize_atom<FIELD>(cf, R, A.seed, A.cfg_base + (uint32_t)c, (uint64_t)(first + a0 + l),
+                           lane_value(X, l), lane_value(Y, l), lane_value(Z, l), A.k_first, A.K,
+                           A.tb + (base + a0 + l) * A.K);
+    }
+}
+
+template <int FIELD>
+__global__ void __launch_bounds__(256, IonizeWaves<FIELD>::value) batch_ionize_lane_kernel(
+    BatchArgs A, const DevCfg* __restrict__ cfgs)
+{
+    const int c = blockIdx.y;
+    const int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t first = (int64_t)A.ctl->chunk * A.apc;
+    if (a >= A.apc || first + a >= A.atoms_per_cfg) return;
+    const DevCfg& cf = cfgs[c];
+    const int64_t i = (int64_t)c * A.apc + a;
+    const RateRegs R(cf);
+    ionize_atom_lane<FIELD>(cf, R, A.seed, A.cfg_base + (uint32_t)c, (uint64_t)(first + a),
+                            A.x[i] * cf.k, A.y[i] * cf.k, A.z[i] * cf.k, A.k_first, A.K,
+                            A.tb + i * A.K);
+}
+
 // The queue push: one persistent launch over n_cfg * apc * K slots.  Slot j belongs to
 // configuration j / (apc K) and atom (j / K) % apc of the chunk.  Every
 // configuration has its own work counter, and a wave works on ONE

@@ -94,3 +94,37 @@ def test_capture_and_streams(I, panels, n):
         torch.cuda.synchronize()
         for a, b in zip(got, want):
             assert torch.equal(a.view(torch.int64), b.view(torch.int64))
+
+
+@pytest.mark.parametrize("field,I,panels,n_cfg,n,apc", [
+    (5, 1e14, None, 3, 6001, 6001),        # no state reached: many atoms to a wave
+    (5, 1e14, None, 2, 20000, 9001),       # a partial last chunk
+    (5, 1e21, 200, 2, 80001, 80001),       # few panels: a lane per atom
+    (25, 1e21, 200, 1, 170000, 150001),
+    (11, 1e21, 150, 2, 60000, 60000),      # uniform field
+])
+def test_sweep_forms_agree(field, I, panels, n_cfg, n, apc):
+    """A sweep's births against those of the single calls' wave form, on its last
+    chunk, captured and replayed."""
+    torch = require_gpu()
+    from paper_2509_01741_amd import binding as B
+    kf, kl, seed = 1, 3, 11
+    lasers = [_laser(B, field, I, panels, 0) for _ in range(n_cfg)]
+    ws = torch.zeros(B.rpdla_batched_workspace_bytes(n_cfg, apc, kf, kl), dtype=torch.uint8, device="cuda")
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    print(f"sweep field {field} I {I:g} panels {panels}: {n_cfg} x {n} by {apc}", flush=True)
+    first = (n - 1) // apc * apc
+    for _ in range(2):
+        B.rpdla_run_batched(lasers, seed, 40, n, apc, 2.0, kf, kl, 0,
+                            B.rpdla_hist_spec(8, 4, -6.0, 3.0, 0), workspace=ws, stream=s)
+        s.synchronize()
+        a = B.batched_chunk_arrays(ws, n_cfg, apc, kf, kl)
+        for c in range(n_cfg):
+            m = n - first
+            x, y, z = (a[k][c, :m].contiguous() for k in ("x", "y", "z"))
+            ref = torch.cat([B.rpdla_ionize(lasers[c], seed, 40 + c, first + i, x[i:i + PIECE].contiguous(),
+                                            y[i:i + PIECE].contiguous(), z[i:i + PIECE].contiguous(), kf, kl)
+                             for i in range(0, m, PIECE)])
+            got = a["t_birth"][c, :m].reshape(-1).contiguous()
+            assert torch.equal(got.view(torch.int64), ref.view(torch.int64))
