@@ -1820,20 +1820,13 @@ __device__ inline uint32_t fresh_lane()
 // it.  The alignment and the words below move the loop to the best of the eight.
 // The compiler puts the loop's first instructions between, so the number holds
 // for the kernels as they stand: after a change to them it is measured again.
-// What only the last step of an electron needs waits in LDS during the loop
-// without tests, and what a lane needs before and after its steps (its number,
-// its slot) is formed anew: held in registers, these put 28 to 52 bytes a lane
-// into scratch (at order 5, 4 and 7 waves).  ElecRR's loop came out with spills
-// inside it that way and without any when the last step stays in registers.
+// What a lane needs before its steps and after them (its number, its slot) is
+// formed anew: held over the loops in registers, these put 28 to 52 bytes a lane
+// into scratch (at order 5, 4 and 7 waves).
 template <int FIELD, bool BATCH, class CFG, class ELEC>
 __device__ inline void run_steps(const CFG& c, ELEC& e, const fm::Coef& k, int32_t steps)
 {
     if constexpr (!std::is_same<ELEC, ElecMixed>::value) {
-        // what the loop without tests does not read waits in LDS
-        constexpr bool kPark = std::is_same<ELEC, ElecF64>::value;
-        __shared__ double park_last[256];
-        __shared__ int32_t park_left[256];
-        const uint32_t park = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
         int32_t least = e.left > 0 ? e.left : 0x7fffffff;
         for (int o = 32; o > 0; o >>= 1) {
             const int32_t other = __shfl_xor(least, o);
@@ -1843,23 +1836,13 @@ __device__ inline void run_steps(const CFG& c, ELEC& e, const fm::Coef& k, int32
         if (least == 0x7fffffff) return;
         const int32_t full = least - 1 < steps ? least - 1 : steps;
         int32_t n = full;
-        if (e.left > 0) e.left -= full;
-        if constexpr (kPark) {
-            const uint32_t at = park + fresh_lane();
-            park_last[at] = e.h_last;
-            park_left[at] = e.left;
-        }
 #pragma unroll 1
         for (; n > 1; n -= 2) {
             elec_step<FIELD, true, BATCH>(c, e, k);
             elec_step<FIELD, true, BATCH>(c, e, k);
         }
         if (n > 0) elec_step<FIELD, true, BATCH>(c, e, k);
-        if constexpr (kPark) {
-            const uint32_t at = park + fresh_lane();
-            e.h_last = park_last[at];
-            e.left = park_left[at];
-        }
+        if (e.left > 0) e.left -= full;
         steps -= full;
     }
     if constexpr (std::is_same<ELEC, ElecMixed>::value) {
@@ -1918,8 +1901,8 @@ __global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_gro
     for (; group < end; group += W) {
         ELEC e;
         e.left = 0;
+        const uint32_t lane = fresh_lane(), at = group * 64u + lane;
         {
-            const uint32_t lane = fresh_lane(), at = group * 64u + lane;
             const GroupArgsPtr ga = group_args();
             const size_t stride = (size_t)rest * 64;
             if (!first) {
@@ -1940,7 +1923,6 @@ __global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_gro
         const bool runs = e.left > 0;
         run_steps<FIELD, false>(R.c, e, R.k, steps);
         {
-            const uint32_t lane = fresh_lane(), at = group * 64u + lane;
             const GroupArgsPtr ga = group_args();
             if (runs && e.left == 0) {
                 const PushIO io = ga->io;
