@@ -563,8 +563,9 @@ __device__ void ionize_atom_lane(const CFG& c, const RateRegs& R, uint64_t seed,
         double acc = 0.0;
 #pragma unroll 1
         for (int i = 0; i < 4; ++i) {
-            const double xn = i == 0 ? -R.gl_x[1] : i == 1 ? -R.gl_x[0] : i == 2 ? R.gl_x[0] : R.gl_x[1];
-            acc = fma(i == 0 || i == 3 ? R.gl_w[1] : R.gl_w[0], rate(fma(xn, hw, m)), acc);
+            const bool outer = i == 0 || i == 3;
+            const double x = outer ? R.gl_x[1] : R.gl_x[0];
+            acc = fma(outer ? R.gl_w[1] : R.gl_w[0], rate(fma(i < 2 ? -x : x, hw, m)), acc);
         }
         return acc;
     };
