@@ -265,8 +265,8 @@ def rpdla_push(L, precision, t_birth, x0, y0, z0, slots_per_atom, out=None, stre
 
 def rpdla_push_noalloc(L, precision, t_birth, x0, y0, z0, slots_per_atom, out, stream=None):
     """rpdla_push without device allocation: the caller passes the six output
-    tensors ``out`` = (ux, uy, uz, xf, yf, zf); the library's own 256-byte
-    device array holds the work counter (overlapping calls on one GPU race)."""
+    tensors ``out`` = (ux, uy, uz, xf, yf, zf); the library's own 1 KiB
+    device array holds the work counters (overlapping calls on one GPU race)."""
     n = t_birth.numel()
     na = (n + slots_per_atom - 1) // slots_per_atom
     ux, uy, uz, xf, yf, zf = out

@@ -19,8 +19,9 @@ namespace rpdla {
 constexpr int kMaxStates = 10;
 
 // Per-configuration constants, built on the host (rpdla_api.hip) and passed
-// by value to kernels, staged in LDS by the batched ionization kernel and read
-// with scalar loads by the batched push.
+// by value to the kernels of one configuration; those of a sweep read an array
+// of them in device memory, the ionization and the ordered push from the
+// configuration that a block or group belongs to.
 struct DevCfg {
     double omega, inv_omega;     // carrier angular frequency [rad/s]
     double k, inv_k;             // wavenumber [1/m]

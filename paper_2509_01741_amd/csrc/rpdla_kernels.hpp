@@ -1402,8 +1402,8 @@ __device__ inline void elec_final(const CFG& c, const ElecMixed& e, double& ux, 
 
 // ---------------------------------------------------------------------------
 // Persistent push over one configuration, for the controlled-step form, whose
-// step counts are not known beforehand, and where the ordered push below has no
-// scratch.  A lane whose electron has reached
+// step counts are not known beforehand, for pushes of few steps, and where the
+// ordered push below has no scratch.  A lane whose electron has reached
 // its window end writes it out and takes the next slot from a global counter
 // (one atomic per wave per refill, ranks from the ballot), so lanes stay busy
 // however uneven the step counts are.  Unborn slots are written as NaN when
@@ -1939,9 +1939,10 @@ __global__ void __launch_bounds__(256, (ElecWaves<ELEC, FIELD>::value)) push_gro
 }
 
 // ---------------------------------------------------------------------------
-// Histogram.  Each lane computes its bin key; lanes of a wave that share a
-// key are merged (leader takes the key, ballot finds the matches, one atomic
-// per distinct key); the six tallies are ballot-counted per wave.
+// Histogram.  Each lane computes its bin key and counts it in LDS: all bins
+// where they fit, else a table of places that the first bin owns, the rest in
+// global memory; the six tallies are ballot-counted per wave.  (Only the
+// sweep's binning pass merges the lanes of a wave that share a key.)
 // ---------------------------------------------------------------------------
 struct HistArgs {
     int32_t nE, nA, angle;
